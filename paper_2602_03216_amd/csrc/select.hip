@@ -1,7 +1,7 @@
 // Head-wise top-k selection: Algorithm 1 of the paper, S_h = TopK(s_h, k_keep).
 // Exact: the k_keep largest scores, ties to the lowest token index, emitted in ascending
 // token order together with the inverse map.  Integer work on the order-preserving uint32
-// image of the fp32 score:
+// image of the fp32 score.  Rows of up to 65536 tokens take one launch (select_row_kernel, below); longer ones:
 //   1. radix select, 4 passes of 8 bits, most significant first: every pass histograms the
 //      digit of the keys that still match the prefix found so far (LDS histograms per
 //      wavefront), and the next kernel derives the digit of the k-th largest key from the
@@ -19,13 +19,10 @@
 // to go below a few tokens per thread.
 #include "tsa_internal.h"
 
-#include <mutex>
-
 namespace tsa {
 
 namespace {
 
-constexpr int kMaxDevices = 64;
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMinSlice = 2048, kMaxSlice = 16384;   // tokens per workgroup (SelArgs::slice), unless a row needs more
@@ -303,103 +300,283 @@ __global__ __launch_bounds__(kThreads) void write_kernel(SelArgs a) {
   }
 }
 
-// Short rows (L <= kSmallL): the whole selection of a row in ONE launch by one workgroup.  The
-// order-preserving keys of the row are kept in LDS (4 bytes per token), the four radix passes, the
-// counting and the stable compaction all run out of LDS; same arithmetic and same result as the
-// sliced kernels above, without six launches whose fixed cost dominates at this size.
-constexpr int kSmallL = 16384;
+// Rows of up to kRowMaxL tokens: the whole selection of a row in ONE launch by one workgroup.  The keys of the row
+// stay in registers (4 J per lane; a wavefront owns 256 J consecutive tokens, lane l of step j the four tokens
+// 256 j + 4 l ..), and the threshold comes from a radix descent over the RANGE the row's keys span: the first
+// pass cuts [smallest key, largest key] into kBins equal bins, so the keys spread over the bins whatever their
+// magnitude (equal 8-bit digits of softmax scores fall into a handful of bins, and LDS atomics on one
+// address run one after the other).  A pass narrows the range by 2^12; as soon as the bin with the k-th key
+// holds at most kRank keys, they are ranked against each other directly.  At most three
+// passes, one or two in practice.  With per-group sets the sum over the g heads happens in the key load.
+// Bound: one CU's share of a row: 4 bytes per token into one CU and the vector instructions per key (at 32768 tokens
+// of 15 us: 3 launch, 4 load, 3 keys and range, 3 histogram and ranking, 3 counting and compaction).
+// Measured on softmax-like scores, 32 rows, against the former kernels (8-bit digits: one workgroup per row with the
+// keys in LDS up to 16384 tokens, the five sliced launches above that): 3001 tokens 10.6 -> 6.9 us, 8192: 18.2 -> 8.1,
+// 12345: 24.6 -> 10.1, 32768: 28.8 -> 15.3, 28 rows of 65536: 33.7 -> 28.4, 96 rows of 65536: 72 -> 32 us.
+// 65536 tokens are what the registers of 16 wavefronts hold; longer rows take the sliced kernels.
+constexpr int kBins = 4096;
+constexpr int kRank = 256;          // that many keys are ranked against each other instead of binned again
+constexpr int kRowMaxL = 65536;
 
-__global__ __launch_bounds__(kThreads) void select_small_kernel(SelArgs a) {
-  extern __shared__ uint32_t dyn[];
-  uint32_t* keys = dyn;                                   // [L]
-  uint32_t* hist = dyn + a.L;                             // [kWaves][256], then reused
-  __shared__ uint32_t tot[256];
-  __shared__ SelState sh_state;
-  __shared__ uint2 cnt[kWaves];
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, d));
+  return v;
+}
+
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+
+// order_key without its branches: adding +0 turns -0 into +0 and leaves every other value as it is
+__device__ __forceinline__ uint32_t order_key_fast(float f) {
+  const uint32_t u = __float_as_uint(f + 0.0f);
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+
+// set bits of a ballot below this lane
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+typedef uint32_t __attribute__((ext_vector_type(4), aligned(4))) u32x4_a4;   // rows start at any multiple of 4 bytes
+typedef float __attribute__((ext_vector_type(4), aligned(4))) f32x4_a4;
+
+template <int J>
+__global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) {
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kBins];
+  __shared__ __attribute__((aligned(16))) uint32_t cand[kRank];
+  __shared__ uint32_t wtot[kWaves], wlo[kWaves];
+  __shared__ uint32_t sh_bin, sh_rem, sh_cnt, sh_n, sh_T, sh_eq;
   const long long row = blockIdx.x;
-  const float* s = a.scores + row * a.L;
+  const float* s = a.scores + row * g * a.L;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int t0 = wave * 256 * J + 4 * lane;
+  uint32_t key[J][4];
+  uint32_t kmax = 0u, kmin = 0xffffffffu;
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int t = t0 + 256 * j;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (t + 3 < a.L) {
+      v = *(const f32x4_a4*)(s + t);
+      for (int h = 1; h < g; ++h) v += *(const f32x4_a4*)(s + (long long)h * a.L + t);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (t + e < a.L) {
+          v[e] = s[t + e];
+          for (int h = 1; h < g; ++h) v[e] += s[(long long)h * a.L + t + e];
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) key[j][e] = __float_as_uint(v[e]);
+  }
+  // Ordinary keys lie in [1, 0xfffffffe] (which only NaNs would leave); 0 = beyond the row, 0xffffffff = always
+  // kept: both stay outside the descent.  Few steps of a row hold such a token.
+  const uint32_t n_forced = (uint32_t)(a.ff + a.fl);
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) key[j][e] = min(max(order_key_fast(__uint_as_float(key[j][e])), 1u), 0xfffffffeu);
+    const int first = wave * 256 * J + 256 * j;
+    if (first < a.ff || first + 256 > a.L - a.fl) {        // the same for the whole wavefront
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int t = t0 + 256 * j + e;
+        const bool special = t < a.ff || t >= a.L - a.fl;
+        kmax = max(kmax, special ? 0u : key[j][e]);
+        kmin = min(kmin, special ? 0xffffffffu : key[j][e]);
+        if (special) key[j][e] = t < a.L ? 0xffffffffu : 0u;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        kmax = max(kmax, key[j][e]);
+        kmin = min(kmin, key[j][e]);
+      }
+    }
+  }
+  kmax = wave_max(kmax);
+  kmin = ~wave_max(~kmin);
+  if (lane == 0) { wtot[wave] = kmax; wlo[wave] = kmin; }
+  for (int i = tid; i < kBins; i += kThreads) hist[i] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) { kmax = max(kmax, wtot[w]); kmin = min(kmin, wlo[w]); }
+  kmax = uniform(kmax);
+  kmin = uniform(kmin);
+
+  uint32_t rem = uniform(a.k_of(row)) - n_forced;                  // wanted among the keys in [lo, lo + 2^bits)
+  uint32_t T = 0xfffffffeu, need_eq = 0u;                 // nothing but the always-kept tokens
+  if (rem > 0u) {
+    uint32_t lo = kmin, n_in = (uint32_t)a.L - n_forced;
+    int bits = kmax > kmin ? 32 - __clz((int)(kmax - kmin)) : 0;
+    while (true) {
+      if (rem >= n_in) { T = lo - 1u; need_eq = 0u; break; }           // every key of the range
+      if (bits == 0) { T = lo; need_eq = rem; break; }                 // one value
+      // members: k - lo <= width (keys beyond the row and always-kept ones lie outside [kmin, kmax])
+      const uint32_t width = min(bits >= 32 ? 0xffffffffu : (1u << bits) - 1u, kmax - lo);
+      if (n_in <= (uint32_t)kRank) {
+        // few keys: collect them and rank every one against all (0 in the places that stay empty ranks below them)
+        if (tid == 0) sh_n = 0u;
+        if (tid < kRank) cand[tid] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t k = key[j][e];
+            if (k - lo <= width) cand[atomicAdd(&sh_n, 1u)] = k;
+          }
+        __syncthreads();
+        if (tid < (int)n_in) {
+          const uint32_t mine = cand[tid];
+          uint32_t above = 0u, same = 0u;
+          for (uint32_t i = 0; i < n_in; i += 4) {
+            const u32x4 o = *(const u32x4*)&cand[i];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              above += o[q] > mine ? 1u : 0u;
+              same += o[q] == mine ? 1u : 0u;
+            }
+          }
+          // equal keys write the same; where all of them are taken there is no tie to resolve: T just below them
+          if (above < rem && rem <= above + same) {
+            const bool all = rem == above + same;
+            sh_T = all ? mine - 1u : mine;
+            sh_eq = all ? 0u : rem - above;
+          }
+        }
+        __syncthreads();
+        T = uniform(sh_T);
+        need_eq = uniform(sh_eq);
+        break;
+      }
+      const int shift = bits > 12 ? bits - 12 : 0;
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t k = key[j][e];
+          if (k - lo <= width) atomicAdd(&hist[(k - lo) >> shift], 1u);
+        }
+      __syncthreads();
+      // bin of the rem-th largest: thread i owns the bins 4095 - 4 i .. 4092 - 4 i
+      const u32x4 c = *(const u32x4*)&hist[kBins - 4 - 4 * tid];
+      const uint32_t mine = c[0] + c[1] + c[2] + c[3];
+      uint32_t incl = mine;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t up = __shfl_up(incl, d);
+        if (lane >= d) incl += up;
+      }
+      if (lane == 63) wtot[wave] = incl;
+      __syncthreads();
+      *(u32x4*)&hist[kBins - 4 - 4 * tid] = u32x4{0u, 0u, 0u, 0u};     // clean for the next pass
+      uint32_t above = incl - mine;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) above += w < wave ? wtot[w] : 0u;
+      if (above < rem && rem <= above + mine) {
+        uint32_t bin = kBins - 1 - 4 * tid;
+#pragma unroll
+        for (int q = 3; q >= 1; --q)
+          if (bin == (uint32_t)(kBins - 4 - 4 * tid + q) && above + c[q] < rem) { above += c[q]; --bin; }
+        sh_bin = bin;
+        sh_rem = rem - above;
+        sh_cnt = c[bin & 3u];
+      }
+      __syncthreads();
+      lo += uniform(sh_bin) << shift;
+      rem = uniform(sh_rem);
+      n_in = uniform(sh_cnt);
+      bits = shift;
+    }
+  }
+
+  // stable compaction: keys above T, and the first need_eq keys equal to T, in token order
+  uint32_t n_gt = 0, n_eq = 0;
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) n_gt += key[j][e] > T ? 1u : 0u;
+  if (need_eq > 0u) {
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) n_eq += key[j][e] == T ? 1u : 0u;
+  }
+  uint32_t n_both = n_gt | (n_eq << 16);                   // at most 4096 tokens per wavefront
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) n_both += __shfl_xor(n_both, d);
+  __syncthreads();                                         // wtot / wlo of the passes above are read
+  if (lane == 0) { wtot[wave] = n_both & 0xffffu; wlo[wave] = n_both >> 16; }
+  __syncthreads();
+  uint32_t gt_before = 0, eq_run = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    gt_before += w < wave ? wtot[w] : 0u;
+    eq_run += w < wave ? wlo[w] : 0u;
+  }
+  uint32_t out_run = gt_before + min(need_eq, eq_run);
   int32_t* out_idx = a.idx + row * a.k_stride;
   int32_t* out_inv = a.inv ? a.inv + row * a.L : nullptr;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  for (int t = tid; t < a.L; t += kThreads) keys[t] = key_at(s, t, a.L, a.ff, a.fl);
-  SelState st;
-  st.prefix = 0u;
-  st.krem = a.k_of(row);
-#pragma unroll 1
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    const uint32_t himask = pass == 0 ? 0u : (0xffffffffu << (shift + 8));
-    for (int i = tid; i < kWaves * 256; i += kThreads) hist[i] = 0u;
-    __syncthreads();                                      // keys (first pass) and cleared histograms are visible
-    for (int base = 0; base < a.L; base += kThreads) {
-      const int t = base + tid;
-      bool valid = false;
-      uint32_t dg = 0;
-      if (t < a.L) {
-        const uint32_t key = keys[t];
-        valid = (key & himask) == st.prefix;
-        dg = (key >> shift) & 255u;
-      }
-      const unsigned long long act = __ballot(valid);
-      if (act == 0ull) continue;
-      const int leader = __ffsll((long long)act) - 1;
-      const uint32_t dg0 = __shfl(dg, leader);
-      const unsigned long long same = __ballot(valid && dg == dg0);
-      if (same == act) {
-        if (lane == leader) atomicAdd(&hist[wave * 256 + dg0], (uint32_t)__popcll(act));
-      } else if (valid) {
-        atomicAdd(&hist[wave * 256 + dg], 1u);
-      }
-    }
-    __syncthreads();
-    if (tid < 256) {
-      uint32_t c = 0;
+  asm volatile("" : "+s"(T));                              // the comparisons below are made afresh: 8 J masks do not fit the scalar registers
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) c += hist[w * 256 + tid];
-      tot[tid] = c;
+  for (int j = 0; j < J; ++j) {
+    const int t = t0 + 256 * j;
+    if (wave * 256 * J + 256 * j >= a.L) break;            // the same for the whole wavefront
+    // tokens of a step are in (lane, element) order: counts of the lanes below, then the lane's own elements
+    bool take[4];
+    uint32_t below = 0, total = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) take[e] = key[j][e] > T;
+    if (need_eq > 0u) {                                    // ties are taken in token order until need_eq of them are used up
+      bool eq[4];
+      uint32_t er = eq_run;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        eq[e] = key[j][e] == T;
+        const unsigned long long m = __ballot(eq[e]);
+        er += lanes_below(m);
+        eq_run += (uint32_t)__popcll(m);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        take[e] = take[e] || (eq[e] && er < need_eq);
+        er += eq[e] ? 1u : 0u;
+      }
     }
-    __syncthreads();
-    if (wave == 0) {
-      const SelState nx = next_state(tot, st, shift, lane);
-      if (lane == 0) sh_state = nx;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const unsigned long long m = __ballot(take[e]);
+      below += lanes_below(m);
+      total += (uint32_t)__popcll(m);
     }
-    __syncthreads();
-    st = sh_state;
+    uint32_t pos = out_run + below;
+    u32x4 iv;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      iv[e] = take[e] ? pos : 0xffffffffu;
+      if (take[e]) out_idx[pos++] = t + e;
+    }
+    if (out_inv) {
+      if (t + 3 < a.L) *(u32x4_a4*)(out_inv + t) = iv;
+      else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (t + e < a.L) out_inv[t + e] = (int32_t)iv[e];
+      }
+    }
+    out_run += total;
   }
-  // st.prefix = threshold key T, st.krem = number of keys equal to T to take (in token order)
-  const uint32_t T = st.prefix, need_eq = st.krem;
-  const int seg = ((a.L + kWaves - 1) / kWaves + 63) & ~63;
-  const int t_lo = wave * seg, t_hi = min(a.L, t_lo + seg);
-  uint32_t n_gt = 0, n_eq = 0;
-  for (int base = t_lo; base < t_hi; base += 64) {
-    const int t = base + lane;
-    const bool in = t < t_hi;
-    const uint32_t key = in ? keys[t] : 0u;
-    n_gt += (uint32_t)__popcll(__ballot(in && key > T));
-    n_eq += (uint32_t)__popcll(__ballot(in && key == T));
+}
+
+// J with 4096 J >= L, from the built ones
+template <int J = 1>
+void run_select_row(const SelArgs& a, int g, int rows, hipStream_t st) {
+  if constexpr (J < 16) {
+    if (a.L > 4096 * J) return run_select_row<(J < 4 ? J + 1 : J < 8 ? J + 2 : J + 4)>(a, g, rows, st);
   }
-  if (lane == 0) cnt[wave] = make_uint2(n_gt, n_eq);
-  __syncthreads();
-  uint32_t gt_before = 0, eq_before = 0;
-  for (int w = 0; w < wave; ++w) { gt_before += cnt[w].x; eq_before += cnt[w].y; }
-  uint32_t eq_run = eq_before, out_run = gt_before + min(need_eq, eq_before);
-  const unsigned long long lt_mask = (1ull << lane) - 1ull;
-  for (int base = t_lo; base < t_hi; base += 64) {
-    const int t = base + lane;
-    const bool in = t < t_hi;
-    const uint32_t key = in ? keys[t] : 0u;
-    const bool gt = in && key > T;
-    const bool eq = in && key == T;
-    const unsigned long long m_eq = __ballot(eq);
-    const uint32_t eq_rank = eq_run + (uint32_t)__popcll(m_eq & lt_mask);
-    const bool take = gt || (eq && eq_rank < need_eq);
-    const unsigned long long m_take = __ballot(take);
-    const uint32_t pos = out_run + (uint32_t)__popcll(m_take & lt_mask);
-    if (take) out_idx[pos] = t;
-    if (in && out_inv) out_inv[t] = take ? (int32_t)pos : -1;
-    out_run += (uint32_t)__popcll(m_take);
-    eq_run += (uint32_t)__popcll(m_eq);
-  }
+  select_row_kernel<J><<<rows, kThreads, 0, st>>>(a, g);
 }
 
 // scores [B,Hq,L] -> [B,Hkv,L]: sum of the g heads of each KV group, in head order
@@ -441,35 +618,19 @@ hipError_t launch_select(const Dims& dm, const float* scores, int k_keep, int32_
   a.rows = (RowWs*)ws;
   a.slices = (SliceWs*)((char*)ws + align256((size_t)rows * sizeof(RowWs)));
   a.scores = scores;
+  a.idx = idx; a.inv = inv;
+  a.L = dm.L; a.k = k_keep; a.ff = dm.force_first; a.fl = dm.force_last; a.nslices = n_slices(dm);
+  a.k_dev = k_dev; a.k_stride = k_keep; a.rows_per_b = rows / dm.B;
+  a.slice = slice_for(dm);
+  if (dm.L <= kRowMaxL) {
+    run_select_row(a, dm.group_mode ? dm.Hq / dm.Hkv : 1, rows, st);
+    return hipGetLastError();
+  }
   if (dm.group_mode) {
     float* gs = (float*)((char*)a.slices + align256((size_t)rows * n_slices(dm) * sizeof(SliceWs)));
     const long long n = (long long)rows * dm.L;
     group_sum_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(scores, gs, dm.Hq / dm.Hkv, dm.L, n);
     a.scores = gs;
-  }
-  a.idx = idx; a.inv = inv;
-  a.L = dm.L; a.k = k_keep; a.ff = dm.force_first; a.fl = dm.force_last; a.nslices = n_slices(dm);
-  a.k_dev = k_dev; a.k_stride = k_keep; a.rows_per_b = rows / dm.B;
-  a.slice = slice_for(dm);
-  if (dm.L <= kSmallL) {
-    const size_t lds = ((size_t)dm.L + kWaves * 256) * sizeof(uint32_t);
-    // the attribute belongs to the kernel as loaded on ONE device: set it once per device, under a lock
-    {
-      static std::mutex mu;
-      static bool attr_set[kMaxDevices] = {};
-      int dev = 0;
-      hipError_t e = hipGetDevice(&dev);
-      if (e != hipSuccess) return e;
-      if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-      std::lock_guard<std::mutex> lock(mu);
-      if (!attr_set[dev]) {
-        e = hipFuncSetAttribute((const void*)select_small_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
-        if (e != hipSuccess) return e;
-        attr_set[dev] = true;
-      }
-    }
-    select_small_kernel<<<rows, kThreads, lds, st>>>(a);
-    return hipGetLastError();
   }
   const dim3 grid(a.nslices, rows);
   hist_kernel<0><<<grid, kThreads, 0, st>>>(a);

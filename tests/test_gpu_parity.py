@@ -152,6 +152,25 @@ def test_select_forced_tokens_and_group_mode(tsa):
     assert np.array_equal(idx, widx) and np.array_equal(inv, winv)
 
 
+@pytest.mark.parametrize("L", [1, 255, 257, 4096, 4097, 12288, 16385, 24577, 32768, 49153, 65535, 65536, 65537])
+def test_select_row_edges(tsa, L):
+    """Edges of the one-workgroup-per-row kernel's steps, sizes and largest row (and the first row beyond it), on scores
+    that drive each branch of its descent: a wide range with both signs (several passes), a cluster of near-equal
+    values beside outliers, a few hundred ties around the boundary; with and without always-kept tokens."""
+    r = _rng(900 + L)
+    wide = (r.standard_normal(L) * 10.0 ** r.uniform(-30, 30, L)).astype(np.float32)
+    near = (1.0 + r.integers(0, 3000, L) * 2.0 ** -23).astype(np.float32)
+    near[r.integers(0, L, 3)] = (-1e30, 1e30, 0.0)
+    ties = r.random(L).astype(np.float32)
+    ties[r.random(L) < 0.3] = 0.5
+    s = np.stack([wide, near, ties])[None]
+    for k in sorted({1, max(1, L // 3), max(1, L // 2), L}):
+        ff, fl = (min(3, k // 2), min(2, k // 2)) if k != L // 2 else (0, 0)
+        idx, inv = _run_select(tsa, s, k, force_first=ff, force_last=fl)
+        widx, winv = orc.select(s, k, ff, fl)
+        assert np.array_equal(idx, widx) and np.array_equal(inv, winv), (L, k)
+
+
 # ------------------------------------------------------------------ compress / decompress
 
 # k = 201 of 777 rows kept: the two-stream scatter kernel (copies driven by idx, zeros by inv);
