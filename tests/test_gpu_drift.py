@@ -35,6 +35,19 @@ def test_layer_drift(tsa, n_tokens, width, eps):
     assert out.item() == 0.0
 
 
+@pytest.mark.parametrize("n_tokens,width", [(33, 2040), (63, 2048), (2049, 2056), (2100, 24)])
+def test_layer_drift_edges(tsa, n_tokens, width):
+    """Rows that end just before, at and after a batch of loads; row counts around the shares of the workgroups (32
+    shares at least, 64 rows each at most).  fp32 sums of `width` squares: relative 2e-6 as above."""
+    r = np.random.Generator(np.random.PCG64(850 + n_tokens))
+    hin = gu.rand_bits(r, (n_tokens, width))
+    hout = orc.f64_to_bf16(orc.bf16_to_f64(hin) + 0.3 * r.standard_normal((n_tokens, width)))
+    out = torch.full((1,), -1.0, dtype=torch.float32, device=gu.DEV)
+    tsa.tsa_layer_drift(gu.to_dev(hin), gu.to_dev(hout), 1e-3, out)
+    want = orc.layer_drift(orc.bf16_to_f64(hin), orc.bf16_to_f64(hout), 1e-3)
+    assert abs(out.item() - want) <= 2e-6 * abs(want) + 1e-9
+
+
 def test_mfma_probe_runs_and_reports_clocks(tsa):
     """The roofline calibration loop: queues, finishes, and reports a plausible shader clock."""
     ops = torch.zeros(1 << 15, dtype=torch.bfloat16, device=gu.DEV)
