@@ -375,7 +375,7 @@ int tsa_compress_v_tiles(const tsa_desc* desc, const void* V, const int32_t* idx
   if ((rc = check_desc(desc, &dm)) || (rc = check_k(dm, k_keep))) return rc;
   if ((rc = check_ptr(V, "V")) || (rc = check_ptr(idx, "idx"))) return rc;
   if ((rc = check_ws(Vt, vt_bytes, tsa::v_tiles_bytes(dm.B, dm.group_mode ? dm.Hkv : dm.Hq, k_keep, dm.d)))) return rc;
-  return hip_status(tsa::launch_compress_tiled(dm, nullptr, nullptr, V, idx, k_keep, nullptr, nullptr, Vt, (hipStream_t)stream),
+  return hip_status(tsa::launch_compress_v_tiles(dm, V, idx, k_keep, Vt, (hipStream_t)stream),
                     "tsa_compress_v_tiles");
 }
 
@@ -416,12 +416,11 @@ int tsa_forward(const tsa_desc* desc, const void* Q, const void* K, const void* 
   void* Vt = base + w.Vt;
   hipStream_t st = (hipStream_t)stream;
   if ((rc = hip_status(tsa::launch_score(dm, Q, K, scores, base + w.score_ws, st), "tsa_forward(score)"))) return rc;
-  if ((rc = hip_status(tsa::launch_select(dm, scores, k_keep, idx, inv, base + w.select_ws, st), "tsa_forward(select)"))) return rc;
+  if ((rc = hip_status(tsa::launch_select(dm, scores, k_keep, idx, inv, base + w.select_ws, st, nullptr, V, Vt), "tsa_forward(select)"))) return rc;
   // Compression and decompression are folded into the attention kernel: it gathers Q and K rows
   // through idx in its loads, writes the rows of O in its epilogue and clears the other rows; only
-  // V is gathered beforehand (into the transposed tiles the kernel's operands want).  The compacted
+  // V is gathered beforehand (with the selection, into the transposed tiles the kernel's operands want).  The compacted
   // output is materialised only for the residual update.
-  if ((rc = hip_status(tsa::launch_compress_tiled(dm, Q, K, V, idx, k_keep, nullptr, nullptr, Vt, st), "tsa_forward(V tiles)"))) return rc;
   if ((rc = hip_status(tsa::launch_attend_fused(dm, Q, K, Vt, idx, inv, k_keep, block_list, block_size,
                                                 max_blocks_per_row, nullptr, O, residual, st), "tsa_forward(attend)"))) return rc;
   if (idx_out) {
@@ -466,8 +465,7 @@ int tsa_forward_dynamic(const tsa_desc* desc, const void* Q, const void* K, cons
   if ((rc = hip_status(tsa::launch_score(dm, Q, K, scores, base + w.score_ws, st), "tsa_forward_dynamic(score)"))) return rc;
   if ((rc = hip_status(tsa::launch_budget(dm, scores, tau_cov, k_dev, base + w.budget_ws, st, k_max, dm.force_first + dm.force_last),
                        "tsa_forward_dynamic(budget)"))) return rc;
-  if ((rc = hip_status(tsa::launch_select(dm, scores, k_max, idx, inv, base + w.select_ws, st, k_dev), "tsa_forward_dynamic(select)"))) return rc;
-  if ((rc = hip_status(tsa::launch_compress_tiled(dm, Q, K, V, idx, k_max, nullptr, nullptr, Vt, st, k_dev), "tsa_forward_dynamic(V tiles)"))) return rc;
+  if ((rc = hip_status(tsa::launch_select(dm, scores, k_max, idx, inv, base + w.select_ws, st, k_dev, V, Vt), "tsa_forward_dynamic(select)"))) return rc;
   if ((rc = hip_status(tsa::launch_attend_fused(dm, Q, K, Vt, idx, inv, k_max, block_list, block_size, max_blocks_per_row,
                                                 nullptr, O, residual, st, k_dev),
                        "tsa_forward_dynamic(attend)"))) return rc;

@@ -17,7 +17,7 @@
 // threads each), sized so that a launch has about 512 workgroups: each of the five small kernels
 // is a chain of dependent steps per thread, so it pays to spread it over the whole chip, but not
 // to go below a few tokens per thread.
-#include "tsa_internal.h"
+#include "v_tiles.h"
 
 namespace tsa {
 
@@ -60,6 +60,9 @@ struct SelArgs {
   // entry b (NULL: every row takes k); a row of idx is k_stride entries long either way.
   const int32_t* k_dev;
   int k_stride, rows_per_b;
+  // select_row_kernel only: `parts` workgroups share a row; with tiles.Vt they also gather the row's V tiles
+  int parts, n_rows;
+  VTiles tiles;
   __device__ __forceinline__ uint32_t k_of(long long row) const {
     return (uint32_t)(k_dev ? k_dev[row / rows_per_b] : k);
   }
@@ -314,9 +317,17 @@ __global__ __launch_bounds__(kThreads) void write_kernel(SelArgs a) {
 // keys in LDS up to 16384 tokens, the five sliced launches above that): 3001 tokens 10.6 -> 6.9 us, 8192: 18.2 -> 8.1,
 // 12345: 24.6 -> 10.1, 32768: 28.8 -> 15.3, 28 rows of 65536: 33.7 -> 28.4, 96 rows of 65536: 72 -> 32 us.
 // 65536 tokens are what the registers of 16 wavefronts hold; longer rows take the sliced kernels.
+// A launch of few rows leaves most CUs idle, and the gather of the selected V rows that follows in the whole layer is
+// a launch of its own that waits for the last row.  With up to 128 rows, `parts` workgroups therefore take the same row
+// where the caller wants the V tiles: each of them finds the threshold (the scores come out of the L2 that the parts of
+// a row share), writes its share of idx and inv, and builds the V tiles of its share of idx.  More rows fill the chip
+// by themselves (one workgroup per CU is resident) and keep the separate gather.
+// Selection + gather, 32 rows: 901 of 3001 tokens 14.0 -> 10.6 us, 4096 of 8192: 21.9 -> 20.4, 3277 of 32768: 27.4 -> 26.2,
+// 16384 of 32768: 65.3 -> 63.7 (the last one and the second at the rate of HBM).
 constexpr int kBins = 4096;
 constexpr int kRank = 256;          // that many keys are ranked against each other instead of binned again
 constexpr int kRowMaxL = 65536;
+constexpr int kCUs = 256;
 
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 #pragma unroll
@@ -337,16 +348,20 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-typedef uint32_t __attribute__((ext_vector_type(4), aligned(4))) u32x4_a4;   // rows start at any multiple of 4 bytes
-typedef float __attribute__((ext_vector_type(4), aligned(4))) f32x4_a4;
+typedef float __attribute__((ext_vector_type(4), aligned(4))) f32x4_a4;      // rows start at any multiple of 4 bytes
 
-template <int J>
+template <int J, bool TILES>
 __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) {
   __shared__ __attribute__((aligned(16))) uint32_t hist[kBins];
   __shared__ __attribute__((aligned(16))) uint32_t cand[kRank];
   __shared__ uint32_t wtot[kWaves], wlo[kWaves];
   __shared__ uint32_t sh_bin, sh_rem, sh_cnt, sh_n, sh_T, sh_eq;
-  const long long row = blockIdx.x;
+  // consecutive workgroup ids go to different XCDs: id % 8 picks a contiguous range of (row, part), so that the
+  // workgroups of a row share an L2
+  const unsigned at = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (at >= (unsigned)(a.n_rows * a.parts)) return;
+  const long long row = at / (unsigned)a.parts;
+  const int part = at % (unsigned)a.parts;
   const float* s = a.scores + row * g * a.L;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int t0 = wave * 256 * J + 4 * lane;
@@ -405,7 +420,8 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
   kmax = uniform(kmax);
   kmin = uniform(kmin);
 
-  uint32_t rem = uniform(a.k_of(row)) - n_forced;                  // wanted among the keys in [lo, lo + 2^bits)
+  const uint32_t k_row = uniform(a.k_of(row));
+  uint32_t rem = k_row - n_forced;                                 // wanted among the keys in [lo, lo + 2^bits)
   uint32_t T = 0xfffffffeu, need_eq = 0u;                 // nothing but the always-kept tokens
   if (rem > 0u) {
     uint32_t lo = kmin, n_in = (uint32_t)a.L - n_forced;
@@ -519,6 +535,10 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
   uint32_t out_run = gt_before + min(need_eq, eq_run);
   int32_t* out_idx = a.idx + row * a.k_stride;
   int32_t* out_inv = a.inv ? a.inv + row * a.L : nullptr;
+  // this workgroup's share of the row: whole tiles of idx, every parts-th step of inv
+  const uint32_t n_tiles = (k_row + kKeyTile - 1) / kKeyTile;
+  const uint32_t tile_lo = n_tiles * part / a.parts, tile_hi = n_tiles * (part + 1) / a.parts;
+  const uint32_t pos_lo = tile_lo * kKeyTile, pos_n = (tile_hi - tile_lo) * kKeyTile;
   asm volatile("" : "+s"(T));                              // the comparisons below are made afresh: 8 J masks do not fit the scalar registers
 #pragma unroll
   for (int j = 0; j < J; ++j) {
@@ -556,9 +576,12 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       iv[e] = take[e] ? pos : 0xffffffffu;
-      if (take[e]) out_idx[pos++] = t + e;
+      if (take[e]) {
+        if (pos - pos_lo < pos_n) out_idx[pos] = t + e;
+        ++pos;
+      }
     }
-    if (out_inv) {
+    if (out_inv && (wave * J + j) % a.parts == part) {
       if (t + 3 < a.L) *(u32x4_a4*)(out_inv + t) = iv;
       else {
 #pragma unroll
@@ -568,15 +591,23 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
     }
     out_run += total;
   }
+  if constexpr (!TILES) return;
+  __shared__ __attribute__((aligned(16))) char vt_lds[TILES ? kWaves * kVtLds : 16];
+  __syncthreads();                                         // the share of idx is written: all of this workgroup's wavefronts read it
+  const uint32_t halves = (tile_hi - tile_lo) * a.tiles.halves;
+  for (uint32_t i = wave; i < halves; i += kWaves)
+    v_half_tile(a.tiles, row, tile_lo + i / a.tiles.halves, i % a.tiles.halves, out_idx, (int)k_row, lane, vt_lds + wave * kVtLds);
 }
 
 // J with 4096 J >= L, from the built ones
 template <int J = 1>
-void run_select_row(const SelArgs& a, int g, int rows, hipStream_t st) {
+void run_select_row(const SelArgs& a, int g, hipStream_t st) {
   if constexpr (J < 16) {
-    if (a.L > 4096 * J) return run_select_row<(J < 4 ? J + 1 : J < 8 ? J + 2 : J + 4)>(a, g, rows, st);
+    if (a.L > 4096 * J) return run_select_row<(J < 4 ? J + 1 : J < 8 ? J + 2 : J + 4)>(a, g, st);
   }
-  select_row_kernel<J><<<rows, kThreads, 0, st>>>(a, g);
+  const unsigned grid = 8u * (unsigned)((a.n_rows * a.parts + 7) / 8);
+  if (a.tiles.Vt) select_row_kernel<J, true><<<grid, kThreads, 0, st>>>(a, g);
+  else select_row_kernel<J, false><<<grid, kThreads, 0, st>>>(a, g);
 }
 
 // scores [B,Hq,L] -> [B,Hkv,L]: sum of the g heads of each KV group, in head order
@@ -612,7 +643,7 @@ size_t select_ws_bytes(const Dims& dm) {
 }
 
 hipError_t launch_select(const Dims& dm, const float* scores, int k_keep, int32_t* idx, int32_t* inv,
-                         void* ws, hipStream_t st, const int32_t* k_dev) {
+                         void* ws, hipStream_t st, const int32_t* k_dev, const void* V, void* Vt) {
   const int rows = n_rows(dm);
   SelArgs a;
   a.rows = (RowWs*)ws;
@@ -623,7 +654,12 @@ hipError_t launch_select(const Dims& dm, const float* scores, int k_keep, int32_
   a.k_dev = k_dev; a.k_stride = k_keep; a.rows_per_b = rows / dm.B;
   a.slice = slice_for(dm);
   if (dm.L <= kRowMaxL) {
-    run_select_row(a, dm.group_mode ? dm.Hq / dm.Hkv : 1, rows, st);
+    const bool with_tiles = Vt && 2 * rows <= kCUs;
+    a.tiles = v_tiles_of(dm, k_keep, V, with_tiles ? Vt : nullptr);
+    a.n_rows = rows;
+    a.parts = with_tiles ? min(kCUs / rows, a.tiles.nk_tiles) : 1;
+    run_select_row(a, dm.group_mode ? dm.Hq / dm.Hkv : 1, st);
+    if (Vt && !with_tiles) return launch_compress_v_tiles(dm, V, idx, k_keep, Vt, st, k_dev);
     return hipGetLastError();
   }
   if (dm.group_mode) {
@@ -638,6 +674,7 @@ hipError_t launch_select(const Dims& dm, const float* scores, int k_keep, int32_
   hist_kernel<2><<<grid, kThreads, 0, st>>>(a);
   hist_kernel<3><<<grid, kThreads, 0, st>>>(a);
   write_kernel<<<grid, kThreads, 0, st>>>(a);
+  if (Vt) return launch_compress_v_tiles(dm, V, idx, k_keep, Vt, st, k_dev);
   return hipGetLastError();
 }
 

@@ -60,8 +60,9 @@ hipError_t launch_pool_queries(const Dims& dm, const void* Q, int n_pool, void* 
 size_t select_ws_bytes(const Dims& dm);
 // k_dev (device, [B], may be NULL): the count of every batch entry as decided on the device; k_keep is
 // then the capacity (row stride of idx), and entries of idx past a row's count are left untouched.
+// Vt (may be NULL): also gather the selected rows of V into the tiles of launch_compress_v_tiles.
 hipError_t launch_select(const Dims& dm, const float* scores, int k_keep, int32_t* idx, int32_t* inv,
-                         void* ws, hipStream_t st, const int32_t* k_dev = nullptr);
+                         void* ws, hipStream_t st, const int32_t* k_dev = nullptr, const void* V = nullptr, void* Vt = nullptr);
 
 // budget.hip
 size_t budget_ws_bytes(const Dims& dm);
@@ -90,11 +91,10 @@ inline size_t v_tiles_bytes(int B, int kv_heads, int Lc, int d) {
   return (size_t)B * kv_heads * ((Lc + kKeyTile - 1) / kKeyTile) * kKeyTile * d * 2;
 }
 
-// gather_scatter.hip (continued): row-major V -> tiled V^T; and Stage 1 compression writing
-// Qc, Kc row-major and V directly as tiled V^T (the form tsa_forward uses).
+// gather_scatter.hip (continued): row-major V -> tiled V^T; and the rows of V selected by idx -> tiled V^T.
 hipError_t launch_v_tiles(int B, int kv_heads, int Lc, int d, const void* V, void* Vt, hipStream_t st);
-hipError_t launch_compress_tiled(const Dims& dm, const void* Q, const void* K, const void* V, const int32_t* idx,
-                                 int k_keep, void* Qc, void* Kc, void* Vt, hipStream_t st, const int32_t* k_dev = nullptr);
+hipError_t launch_compress_v_tiles(const Dims& dm, const void* V, const int32_t* idx, int k_keep, void* Vt, hipStream_t st,
+                                   const int32_t* k_dev = nullptr);
 
 // attend.hip
 hipError_t launch_attend(int B, int Hq, int kv_heads, int Lc, int d, float scale, const void* Qc, const void* Kc,
@@ -102,8 +102,7 @@ hipError_t launch_attend(int B, int Hq, int kv_heads, int Lc, int d, float scale
                          int block_list_per_head, void* Oc, float* lse, hipStream_t st);
 
 // attend.hip, fused form used by tsa_forward: Q and K are the original tensors, rows are gathered
-// through idx inside the kernel's loads; Vt = tiles of the gathered V (launch_compress_tiled with
-// Qc = Kc = NULL); O [B,Hq,L,d] (may be NULL) receives the rows of selected tokens from the
+// through idx inside the kernel's loads; Vt = tiles of the gathered V (launch_compress_v_tiles); O [B,Hq,L,d] (may be NULL) receives the rows of selected tokens from the
 // epilogue and zeros elsewhere; Oc [B,Hq,k,d] (may be NULL) the compacted output; residual [B,L,Hq*d]
 // (may be NULL) gets the output rows added in place.
 hipError_t launch_attend_fused(const Dims& dm, const void* Q, const void* K, const void* Vt, const int32_t* idx,

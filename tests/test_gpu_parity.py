@@ -506,6 +506,39 @@ def test_fused_path_equals_the_separate_calls(tsa, attend_form, B, Hq, Hkv, L, d
     assert torch.equal(O2, O1) and torch.equal(O3, O1)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,k,group_mode", [
+    (1, 1, 1, 70, 64, 64, 0), (1, 1, 1, 5000, 128, 1, 0), (1, 7, 7, 4097, 64, 65, 0), (2, 50, 10, 600, 128, 129, 0),
+    (4, 32, 32, 300, 64, 300, 0), (3, 43, 43, 200, 64, 63, 0), (1, 8, 2, 8193, 128, 1000, 1),
+])
+def test_selection_with_v_tiles(tsa, B, Hq, Hkv, L, d, k, group_mode):
+    """The selection that also gathers V (up to 128 rows: several workgroups per row; above: two launches), against
+    the separate calls bit for bit: ragged last tiles, more workgroups than tiles, 128 and 129 rows; and the tiles
+    of the separate call against torch's gather and transpose."""
+    r = _rng(970 + L + k)
+    Q, K, V = (gu.to_dev(gu.rand_bits(r, (B, h, L, d))) for h in (Hq, Hkv, Hkv))
+    desc = tsa.make_desc(B, Hq, Hkv, L, d, 16, group_mode=group_mode)
+    Hs = Hkv if group_mode else Hq
+    ws = _ws(tsa, desc, k)
+    s = torch.empty((B, Hq, L), dtype=torch.float32, device=gu.DEV)
+    idx = torch.empty((B, Hs, k), dtype=torch.int32, device=gu.DEV)
+    inv = torch.empty((B, Hs, L), dtype=torch.int32, device=gu.DEV)
+    Vt = tsa.alloc_attend_workspace(desc, k, Hs, gu.DEV)
+    O1 = torch.full((B, Hq, L, d), 5.0, dtype=torch.bfloat16, device=gu.DEV)
+    O2, idx2 = torch.full_like(O1, 7.0), torch.empty_like(idx)
+    tsa.tsa_score(desc, Q, K, s, ws)
+    tsa.tsa_select(desc, s, k, idx, inv, ws)
+    tsa.tsa_compress_v_tiles(desc, V, idx, k, Vt)
+    tsa.tsa_attend_fused(desc, Q, K, Vt, idx, inv, k, O=O1)
+    tsa.tsa_forward(desc, Q, K, V, k, O2, ws, idx_out=idx2)
+    nt = (k + 63) // 64
+    want = torch.zeros((B, Hs, nt * 64, d), dtype=torch.bfloat16, device=gu.DEV)
+    Vs = V.repeat_interleave(Hs // Hkv, dim=1)
+    want[:, :, :k] = torch.gather(Vs, 2, idx.long()[..., None].expand(B, Hs, k, d))
+    tiles = Vt.view(torch.bfloat16)[: B * Hs * nt * d * 64].view(B, Hs, nt, d, 64)
+    assert torch.equal(tiles, want.view(B, Hs, nt, 64, d).transpose(3, 4))
+    assert torch.equal(idx2, idx) and torch.equal(O2, O1)
+
+
 @pytest.mark.parametrize("Hq,Hk,Lc,d,Bs", [(4, 2, 1000, 128, 128), (3, 3, 1500, 64, 128), (2, 1, 2600, 128, 128),
                                            (4, 2, 1100, 128, 64), (2, 2, 1900, 64, 256)])
 def test_attend_per_head_block_lists(tsa, attend_form, Hq, Hk, Lc, d, Bs):
