@@ -5,7 +5,7 @@
 // Exact two-pass softmax, both passes on bf16 MFMA with fp32 accumulation:
 //   pass 1  S^T = K Q^T   (lane = query, registers = keys): per-query running max / sum of
 //           exponentials over a chunk of keys -> partial (max, sum) per (head, query, chunk)
-//   lse     combine the chunk partials into one log2-sum-exp per (head, query)
+//   lse     combine the chunk partials into one log2-sum-exp per (head, query); few partials at the start of pass 2
 //   pass 2  S = Q K^T     (lane = key, registers = queries): p = exp2(x - lse) summed over the
 //           queries inside the lane, one cross-half add, coalesced store of s[h, t]
 // The two orientations use the same register fragments (a lane holds 8 consecutive d-values of
@@ -43,6 +43,10 @@ constexpr float kNegBig = -1.0e30f;
 constexpr float kSumLimit = 1073741824.0f;   // 2^30: a unit's sum of exponentials beyond this means the running max lags too far
 
 constexpr int kMaxQueries = 128;
+// Up to that many chunk partials per query are folded at the start of pass 2 instead of in a launch of their own (5 us):
+// 16 chunks cost pass 2 about 2 us (8K tokens x 32 KV heads: 4.7 + 15.8 -> 18.0 us for both), 49 to 64 chunks what the
+// launch costs (12345 tokens x 8: 23.7 -> 24.3, 128K: 80.9 -> 82.1).
+constexpr int kFoldChunks = 32;
 
 struct ScoreArgs {
   const __bf16* Q;             // scoring queries: row i of head (b, h) at Q + qs.head(b, h) + (q_row0 + i) * qs.l
@@ -78,13 +82,15 @@ __device__ __forceinline__ void load_q_frags(const ScoreArgs& a, int b, int h, i
 
 // How a workgroup of (KV head, chunk of keys) spreads its four wavefronts over the g query heads
 // that share the KV head: `hpw` heads are processed at a time, one per wavefront, and the
-// remaining factor splits the keys of every staged tile.  Heads beyond hpw take further rounds.
+// remaining factor splits the keys of every staged tile.  Heads beyond hpw take further rounds, which the
+// workgroups of the grid's third dimension share.
 struct WaveRole {
   int hpw, ksplit, hslot, kpart;
 };
-__device__ __forceinline__ WaveRole wave_role(int g, int wave) {
+template <int HPW>
+__device__ __forceinline__ WaveRole wave_role(int wave) {
   WaveRole r;
-  r.hpw = g >= 4 ? 4 : (g >= 2 ? 2 : 1);
+  r.hpw = HPW;
   r.ksplit = kWaves / r.hpw;
   r.hslot = wave % r.hpw;
   r.kpart = wave / r.hpw;
@@ -380,7 +386,7 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass1(ScoreA
   const int kv = bkv % a.Hkv, b = bkv / a.Hkv;
   const int g = a.Hq / a.Hkv;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
-  const WaveRole role = wave_role(g, wave);              // role.hpw == HPW (chosen by the host from g)
+  const WaveRole role = wave_role<HPW>(wave);
   const int c_begin = chunk * a.chunk, c_end = min(c_begin + a.chunk, a.L);
   const int n_tiles = (c_end - c_begin + TK - 1) / TK;
   const int n_fast = fast_tiles<TK>(a, c_begin, n_tiles);
@@ -392,7 +398,7 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass1(ScoreA
   ring.init(a.K + a.ks.head(b, kv), a.ks.l, a.L, tid, Ks, c_begin, n_tiles);
   const int fbase = G::frag_base(lo, hi);
 
-  for (int r0 = 0; r0 < g; r0 += role.hpw) {
+  for (int r0 = blockIdx.z * HPW; r0 < g; r0 += gridDim.z * HPW) {
     const int hh = r0 + role.hslot;
     const bool act = hh < g;
     const int head = kv * g + (act ? hh : 0);
@@ -513,6 +519,31 @@ __global__ __launch_bounds__(256) void score_lse(ScoreArgs a, int QP, long long 
   if (lane == 0) a.lse2[i] = mn + log2f(zs);
 }
 
+// The same fold inside pass 2, one thread per (head, query): sixteen partials at a time, all requested at once (more
+// at a time, and the registers spill).
+__device__ __forceinline__ float fold_chunks(const float2* __restrict__ p, int stride, int n) {
+  constexpr int N = 16;
+  float mn = kNegBig, zs = 0.f;
+#pragma unroll 1
+  for (int c0 = 0; c0 < n; c0 += N) {
+    float2 v[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) v[c] = p[min(c0 + c, n - 1) * stride];
+    float mx = mn;
+#pragma unroll
+    for (int c = 0; c < N; ++c) mx = fmaxf(mx, v[c].x);
+#pragma unroll
+    for (int c = 0; c < N; ++c) v[c].y = c0 + c < n ? v[c].y * exp2f(v[c].x - mx) : 0.f;
+#pragma unroll
+    for (int off = N / 2; off > 0; off >>= 1)
+#pragma unroll
+      for (int c = 0; c < off; ++c) v[c].y += v[c + off].y;
+    zs = zs * exp2f(mn - mx) + v[0].y;
+    mn = mx;
+  }
+  return mn + log2f(zs);
+}
+
 template <int D, int NQT, int HPW>
 __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreArgs a) {
   using C = TileCfg<HPW>;
@@ -520,6 +551,7 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
   using G = Geo<D, TK>;
   constexpr int QP = 32 * NQT;
   __shared__ __attribute__((aligned(1024))) __bf16 Ks[NB * G::TILE];
+  __shared__ float lse_s[HPW * QP];
   __shared__ int qpos_s[kMaxQueries];                  // the position table, for the search of the masked tiles
   if (threadIdx.x < kMaxQueries) qpos_s[threadIdx.x] = a.qpos[threadIdx.x];   // visible after the first barrier below
   // Pass 2 walks the (KV head, chunk) pairs in the reverse of pass 1's order: the workgroups that start
@@ -530,7 +562,7 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
   const int kv = bkv % a.Hkv, b = bkv / a.Hkv;
   const int g = a.Hq / a.Hkv;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
-  const WaveRole role = wave_role(g, wave);              // role.hpw == HPW (chosen by the host from g)
+  const WaveRole role = wave_role<HPW>(wave);
   const int c_begin = chunk * a.chunk, c_end = min(c_begin + a.chunk, a.L);
   const int n_tiles = (c_end - c_begin + TK - 1) / TK;
   const int n_fast = fast_tiles<TK>(a, c_begin, n_tiles);
@@ -539,21 +571,32 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
   ring.init(a.K + a.ks.head(b, kv), a.ks.l, a.L, tid, Ks, c_begin, n_tiles);
   const int fbase = G::frag_base(lo, hi);
 
-  for (int r0 = 0; r0 < g; r0 += role.hpw) {
+  for (int r0 = blockIdx.z * HPW; r0 < g; r0 += gridDim.z * HPW) {
     const int hh = r0 + role.hslot;
     const bool act = hh < g;
     const int head = kv * g + (act ? hh : 0);
     const long long bh = (long long)b * a.Hq + head;
-    __syncthreads();                                   // the previous round is done with the ring
+    __syncthreads();                                   // the previous round is done with the ring and with lse_s
     bf16x8 qf[NQT][D / 16];
-    load_q_frags<D, NQT>(a, b, head, lo, hi, qf);           // Q fragments and lse (served by the L2) ahead of the first K tiles
-    // log2-sum-exp of the queries this lane sees as accumulator rows
+    load_q_frags<D, NQT>(a, b, head, lo, hi, qf);           // Q fragments (served by the L2) ahead of the first K tiles
+    ring.start();
+    // log2-sum-exp of the round's queries, through LDS: a few partials per query are folded here, many by score_lse
+    for (int i = tid; i < HPW * QP; i += kThreads) {
+      const int slot = i / QP, q = i % QP;
+      if (r0 + slot >= g) break;
+      const long long bhs = (long long)b * a.Hq + kv * g + r0 + slot;
+      float x = INFINITY;
+      if (a.nchunks > kFoldChunks) x = a.lse2[bhs * QP + q];
+      else if (q < a.Lq) x = fold_chunks(a.part + bhs * a.nchunks * QP + q, QP, a.nchunks);
+      lse_s[i] = x;
+    }
+    __syncthreads();
+    // ... of the queries this lane sees as accumulator rows
     float lse[NQT][16];
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) lse[qt][r] = a.lse2[bh * QP + 32 * qt + c_row(r, hi)];
-    ring.start();
+      for (int r = 0; r < 16; ++r) lse[qt][r] = lse_s[role.hslot * QP + 32 * qt + c_row(r, hi)];
     UnitPipe<D, NQT, SPT, false> pp;
     pp.fbase = fbase;
     pp.first_sub = first_sub;
@@ -630,13 +673,22 @@ __global__ void pool_kernel(const float* __restrict__ raw, float* __restrict__ o
   out[i] = acc / (float)w;
 }
 
+constexpr int kCUs = 256;
+// workgroups that the LDS tiles and the registers allow to be resident: two per CU with up to 64 queries, else one
+inline int resident_workgroups(int QP) { return QP <= 64 ? 2 * kCUs : kCUs; }
+
 template <int D, int NQT, int HPW>
 hipError_t run_split(const ScoreArgs& a, int BH, hipStream_t st) {
   constexpr int QP = 32 * NQT;
-  dim3 grid(a.nchunks, BH / (a.Hq / a.Hkv));             // one workgroup per (KV head, chunk)
+  const int g = a.Hq / a.Hkv;
+  // One workgroup per (KV head, chunk); its rounds of heads go to workgroups of their own as long as all of them are
+  // resident at once (NQT <= 2: two per CU).
+  dim3 grid(a.nchunks, BH / g);
+  const int rounds = (g + HPW - 1) / HPW;
+  grid.z = (unsigned)max(1, min(rounds, resident_workgroups(32 * NQT) / (int)(grid.x * grid.y)));
   score_pass1<D, NQT, HPW><<<grid, kThreads, 0, st>>>(a);
   const long long n = (long long)BH * QP;
-  score_lse<<<(unsigned)((n + 3) / 4), 256, 0, st>>>(a, QP, n);
+  if (a.nchunks > kFoldChunks) score_lse<<<(unsigned)((n + 3) / 4), 256, 0, st>>>(a, QP, n);
   score_pass2<D, NQT, HPW><<<grid, kThreads, 0, st>>>(a);
   if (a.pool_w > 1) {
     const long long nt = (long long)BH * a.L;
@@ -645,28 +697,34 @@ hipError_t run_split(const ScoreArgs& a, int BH, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The kernels are built per number of query heads a workgroup serves at a time (wave_role: 4, 2 or 1).
+// The kernels are built per number of query heads a workgroup serves at a time (wave_role: 4, 2 or 1).  As many as
+// the group has, unless the chunks leave CUs idle: then a workgroup takes fewer heads, and its wavefronts split the keys of
+// every tile instead.  8 KV heads x 3001 tokens are 96 workgroups with four heads each: passes of 11.4 and 12.0 us; 192 with
+// two: 9.8 and 9.8; 384 with one: 10.2 and 11.3, so half the CUs busy is where the line lies.
 template <int D, int NQT>
 hipError_t run(const ScoreArgs& a, int BH, hipStream_t st) {
   const int g = a.Hq / a.Hkv;
-  if (g >= 4) return run_split<D, NQT, 4>(a, BH, st);
-  if (g >= 2) return run_split<D, NQT, 2>(a, BH, st);
+  const long long wgs = (long long)a.nchunks * (BH / g);
+  int hpw = g >= 4 ? 4 : (g >= 2 ? 2 : 1);
+  while (hpw > 1 && wgs * ((g + hpw - 1) / hpw) <= kCUs / 2) hpw /= 2;
+  if (hpw == 4) return run_split<D, NQT, 4>(a, BH, st);
+  if (hpw == 2) return run_split<D, NQT, 2>(a, BH, st);
   return run_split<D, NQT, 1>(a, BH, st);
 }
 
 // Keys per workgroup: long enough that the start-up of a workgroup (Q fragments, first K tile)
-// is amortised, short enough for two workgroups per CU (as many as the LDS tiles allow to be
-// resident, so the launch runs as a single round).
+// is amortised, short enough for as many workgroups as are resident, so the launch runs as a single round (65..128
+// queries, one per CU, 2 x 6001 tokens x 8 KV heads: 1.5 rounds of 256 keys 35.0 and 31.2 us, one round of 384 keys 24.8 and 22.3).
+inline int nqt_for(int last_q) { return last_q <= 32 ? 1 : (last_q <= 64 ? 2 : 4); }
 inline int chunk_for(const Dims& dm) {
   const long long total = (long long)dm.L * dm.B * dm.Hkv;
-  long long c = total / (256 * 2);
+  long long c = total / resident_workgroups(32 * nqt_for(dm.last_q));
   c = (c + 127) / 128 * 128;
   if (c < kMinChunk) c = kMinChunk;
   if (c > 8192) c = 8192;
   return (int)c;
 }
 
-inline int nqt_for(int last_q) { return last_q <= 32 ? 1 : (last_q <= 64 ? 2 : 4); }
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace

@@ -63,6 +63,15 @@ def test_score(tsa, B, Hq, Hkv, L, d, Lq):
     assert np.allclose(s.sum(-1).cpu().numpy(), Lq, rtol=1e-4)
 
 
+@pytest.mark.parametrize("Hq,Hkv,L,d,Lq", [
+    (2, 2, 8192, 64, 33), (4, 1, 8193, 64, 64),        # 32 and 33 partials per query: the last folded inside pass 2, the first that is not
+    (4, 1, 4096, 128, 16), (5, 1, 257, 128, 64),       # 16 partials (one batch of the fold); heads dealt over workgroups, the last one's idle
+    (16, 16, 4500, 64, 100),                           # chunks above the smallest, one workgroup per CU
+])
+def test_score_split_and_fold_edges(tsa, Hq, Hkv, L, d, Lq):
+    test_score(tsa, 1, Hq, Hkv, L, d, Lq)
+
+
 def test_score_custom_scale_and_determinism(tsa):
     r = _rng(7)
     B, Hq, Hkv, L, d, Lq = 1, 4, 2, 3000, 128, 64
