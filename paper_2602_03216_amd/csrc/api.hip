@@ -540,7 +540,7 @@ int tsa_read_probe(const void* src, size_t bytes, void* sink, void* stream) {
 }
 
 int tsa_bench_set_attend_form(int32_t form) {
-  if (form < 0 || form > 2) return fail(TSA_ERR_ARG, "form must be 0, 1 or 2");
+  if (form < 0 || form > 3) return fail(TSA_ERR_ARG, "form must be 0, 1, 2 or 3");
   tsa::set_attend_form(form);
   return TSA_OK;
 }

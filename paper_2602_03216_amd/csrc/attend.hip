@@ -2,8 +2,8 @@
 // operation on Q^, K^, V^ with cost O(L'^2 d)), also used unchanged as the dense baseline.
 //
 // Flash-style: one workgroup owns 256 query rows (8 wavefronts x 32 rows, two wavefronts per
-// SIMD), streams 64-key tiles through LDS (K in a ring of three tiles, V in a ring of two, one
-// barrier per tile), keeps the running max / sum and the output accumulator in registers
+// SIMD), streams 64-key tiles through LDS (K in a ring of five half tiles, V in a ring of two tiles, one
+// barrier per tile; with four wavefronts 128 rows), keeps the running max / sum and the output accumulator in registers
 // (online softmax) and never materialises the score matrix.
 //
 // Both products run on v_mfma_f32_32x32x16_bf16 in the TRANSPOSED orientation:
@@ -25,7 +25,7 @@
 // score, in fp32, in place, next to MFMAs that have little other vector work beside them), so the
 // blocks with the exponentials apply exp2 to the half tile as it is; a raise of m in between shifts the
 // waiting half tile by the same amount.
-// Very short compacted sets (about 2000 tokens at 32 heads) take the 128-row form of attend_split.hip
+// Very short compacted sets (up to 2000 tokens at 32 heads) take the 128-row form of attend_split.hip
 // instead (use_split_form below).
 // The template also holds the layout with 64 rows per wavefront (QS = 2: four wavefronts, one
 // per SIMD, every LDS fragment feeds two MFMAs); it measures slower and is not instantiated
@@ -38,17 +38,22 @@ using namespace attend_detail;
 
 namespace {
 
-// QS = query sub-tiles (of 32 rows) per wavefront.  QS = 2: 4 wavefronts of 64 rows, one per SIMD,
-// every LDS fragment feeds two MFMAs.  QS = 1: 8 wavefronts of 32 rows, two per SIMD, which share
+// QS = query sub-tiles (of 32 rows) per wavefront, NW = wavefronts per workgroup.  QS = 2, NW = 4: wavefronts of 64
+// rows, one per SIMD, every LDS fragment feeds two MFMAs.  QS = 1: wavefronts of 32 rows, which share
 // the SIMD's issue slots (a lone wavefront issues one vector instruction every ~8 clocks, two
-// together one every ~5) at the price of one LDS fragment per MFMA.
+// together one every ~5) at the price of one LDS fragment per MFMA.  NW = 8: 256 rows, the two wavefronts of a SIMD
+// belong to one workgroup.  NW = 4: 128 rows; the LDS holds two such workgroups (2 x 80384 bytes of 160 KiB, with K
+// in a ring of five half tiles instead of three tiles), three at d = 64 (168 VGPRs: the fused forms spill one to six), which wait
+// at their own barriers and start and end one under the other; every K / V tile is staged for half as many rows.
+// Which one runs, and what both measured: use_pair_form below.
 // LISTS: the launch has a block list.  The plain causal form is a kernel of its own: the look-ups of the tile
 // generator would otherwise sit in the tile loop as loads that may be pending, and the compiler's wait for
 // them (before it reuses their registers) also waits for the K / V prefetches of the tile just requested.
-template <int D, int QS, bool FUSED, bool LISTS>
-__global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) {
-  constexpr int kThreads = 512 / QS;
+template <int D, int QS, int NW, bool FUSED, bool LISTS>
+__global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void attend_kernel(AttendArgs a) {
+  constexpr int kThreads = 64 * NW;
   constexpr int RW = 32 * QS;                     // query rows per wavefront
+  constexpr int BM = RW * NW;                     // query rows per workgroup
   // LDS row stride of a K tile in elements.  K rows are read 16 bytes per lane by 16 lanes of
   // different keys: a 16-byte pad walks them over all 64 banks.
   constexpr int KS = D + 8;
@@ -57,7 +62,8 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
   constexpr int NS = D / 16;                      // MFMA k-steps of the QK product
   constexpr int ND = D / 32;                      // d sub-tiles of the output
   constexpr int ROWB = D * 2;                     // bytes of one row in global memory
-  __shared__ __attribute__((aligned(16))) __bf16 smem[3 * KTILE + 2 * VTILE];   // K ring [3], V ring [2]
+  constexpr int KHALF = KTILE / 2;
+  __shared__ __attribute__((aligned(16))) __bf16 smem[5 * KHALF + 2 * VTILE];   // K ring [5 half tiles], V ring [2 tiles]
 
   // ---- workgroup -> (head, query tile).  Consecutive workgroup ids go to different XCDs, so
   // id % 8 picks the XCD; all tiles of a head (and all heads of a KV group) stay on one XCD to
@@ -111,12 +117,12 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
   // look-up in inv for the next pass is in flight meanwhile), so the stores drain under the compute
   // instead of holding up the start of the workgroup; what is left when the tiles run out is flushed
   // before the epilogue.
-  constexpr int LPR = D / 8, RPP = kThreads / LPR;
+  constexpr int LPR = D / 8, ZR = 512 / kThreads, RPT = kThreads / LPR, RPP = ZR * RPT;   // a pass: ZR rows per thread
   const bool zfill = FUSED && a.Of != nullptr;
   const long long o_pitch16 = FUSED ? a.os.l / 8 : LPR;          // 16-byte pieces between rows of the full-length output
   const int32_t* inv_row = nullptr;
   u32x4* zrow = nullptr;
-  int z_hi = 0, zt = 0, zr = 0;                          // end of the range, next row of this thread, its inv entry
+  int z_hi = 0, zt = 0, zr[ZR] = {};                     // end of the range, next rows of this thread, their inv entries
   int z_every = 1, z_count = 1, z_passes = 1;
   if (zfill) {
     inv_row = a.inv + bkv * a.L;
@@ -128,34 +134,18 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
     z_hi = (int)((long long)a.L * ((long long)(qt + 1) * (qt + 2) / 2) / wt);
     zrow = (u32x4*)(a.Of + a.os.head(b, h)) + (tid % LPR);
     zt = tok_lo + tid / LPR;
-    zr = zt < z_hi ? inv_row[zt] : 0;
+#pragma unroll
+    for (int j = 0; j < ZR; ++j) zr[j] = zt + j * RPT < z_hi ? inv_row[zt + j * RPT] : 0;
     z_passes = (z_hi - tok_lo + RPP - 1) / RPP;
   }
   auto zero_step = [&]() {
-    if (zr < 0) __builtin_nontemporal_store(u32x4{0u, 0u, 0u, 0u}, zrow + (long long)zt * o_pitch16);
+#pragma unroll
+    for (int j = 0; j < ZR; ++j)
+      if (zr[j] < 0) __builtin_nontemporal_store(u32x4{0u, 0u, 0u, 0u}, zrow + (long long)(zt + j * RPT) * o_pitch16);
     zt += RPP;
-    zr = zt < z_hi ? inv_row[zt] : 0;
+#pragma unroll
+    for (int j = 0; j < ZR; ++j) zr[j] = zt + j * RPT < z_hi ? inv_row[zt + j * RPT] : 0;
   };
-
-  // Q^T operand fragments (two 32-row sub-tiles) stay in registers for the whole kernel
-  bf16x8 qf[QS][NS];
-#pragma unroll
-  for (int qs = 0; qs < QS; ++qs) {
-    int qrow_off = (wrow0 + 32 * qs + lo) * ROWB;
-    if (FUSED) {
-      const int qr = wrow0 + 32 * qs + lo;
-      qrow_off = qr < Lc ? (int)__umul24(idx_row[qr], q_pitch) : a.L * q_pitch;   // past the end: out of the buffer's range, reads zeros
-    }
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(Qr, qrow_off + 16 * hi + 32 * s, 0, 0);
-      qf[qs][s] = __builtin_bit_cast(bf16x8, v);
-    }
-  }
-  // Wait for Q here, on every path: otherwise the compiler's wait-count bookkeeping carries these
-  // loads as "possibly pending" into the main loop and makes every MFMA that reads a Q fragment
-  // wait for the oldest in-flight K/V prefetch as well.
-  __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0)
 
   TileGen gen;
   gen.plain = !LISTS;
@@ -171,14 +161,14 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
   for (int j = 0; j < kMaxLists; ++j) { gen.list[j] = nullptr; gen.cnt[j] = gen.pos[j] = 0; gen.cur[j] = INT_MAX; }
   if (!gen.plain) {
     gen.block = a.block;
-    gen.n_lists = BM / a.block;
+    gen.n_lists = max(1, BM / a.block);
     gen.tiles_per_block = a.block / BN;
     gen.full = 0;
     const int nqb = (Lc + a.block - 1) / a.block;
     const int32_t* bl = a.block_list + bh * a.bl_head_stride;
 #pragma unroll
     for (int j = 0; j < kMaxLists; ++j) {
-      const int qb = qt * gen.n_lists + j;
+      const int qb = q0 / a.block + j;
       if (j < gen.n_lists && qb < nqb) {
         gen.list[j] = bl + (long long)qb * a.max_blocks;
         gen.cnt[j] = count_valid(gen.list[j], a.max_blocks, qb);
@@ -200,9 +190,10 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
   // A V tile is one contiguous [d][64] block of the tiled V^T tensor (64 keys = 64 * ROWB bytes as
   // well): thread chunk i is 16-byte piece tid + i * kThreads, i.e. d-row piece / 8, keys
   // 8 * (piece % 8).. .  The tile's first key goes into the scalar offset of the buffer load.
-  constexpr int kRowsPerPass = kThreads / (D / 8);
-  const int st_row = tid / (D / 8), st_col = tid % (D / 8);
-  const int lk_off = k_row_perm(st_row) * KS + 8 * st_col;        // elements, LDS side (K): permuted row order
+  const int st_row = CH * (tid / (D / 8)), st_col = tid % (D / 8);   // K rows st_row .. st_row + CH - 1 of the tile
+  const bool st_half = __builtin_amdgcn_readfirstlane(st_row) >= 32; // (a wavefront's rows lie in one half tile)
+  const int lk_off = k_row_perm(st_row & 31) * KS + 8 * st_col;   // elements, LDS side (K): permuted row order (which leaves
+                                                                  // the CH <= 4 rows of a thread next to each other)
   const int gv_off = 16 * tid;                                    // bytes, global side (V^T)
   const int lv_off = (tid >> 3) * VS + 8 * (tid & 7);             // elements, LDS side (V^T)
   constexpr int kVRowsPerPass = kThreads / 8;
@@ -210,14 +201,25 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
   // compacted row stands for, fetched from idx one tile ahead of the K load that uses it).
   int ktok[CH];
   auto row_off = [&](int tok) -> int { return FUSED ? (int)__umul24(tok, k_pitch) : tok * ROWB; };
-  auto fetch_tok = [&](int k0) {
+  auto fetch_tok = [&](int k0, int (&ktok)[CH]) {
+    if (FUSED) {
+      if (CH == 4) {
+        const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(Ir, st_row * 4, k0 * 4, 0);
 #pragma unroll
-    for (int i = 0; i < CH; ++i) {
-      if (FUSED) ktok[i] = __builtin_amdgcn_raw_buffer_load_b32(Ir, (st_row + i * kRowsPerPass) * 4, k0 * 4, 0);
-      else ktok[i] = k0 + st_row + i * kRowsPerPass;
+        for (int i = 0; i < CH; ++i) ktok[i] = t[i & 3];
+      } else if (CH == 2) {
+        const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(Ir, st_row * 4, k0 * 4, 0);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) ktok[i] = t[i & 1];
+      } else {
+        ktok[0] = __builtin_amdgcn_raw_buffer_load_b32(Ir, st_row * 4, k0 * 4, 0);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < CH; ++i) ktok[i] = k0 + st_row + i;
     }
   };
-  auto load_k = [&](u32x4 (&reg)[CH]) {
+  auto load_k = [&](const int (&ktok)[CH], u32x4 (&reg)[CH]) {
 #pragma unroll
     for (int i = 0; i < CH; ++i)
       reg[i] = __builtin_amdgcn_raw_buffer_load_b128(Kr, row_off(ktok[i]) + 16 * st_col, 0, 0);
@@ -227,9 +229,13 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
     for (int i = 0; i < CH; ++i)
       reg[i] = __builtin_amdgcn_raw_buffer_load_b128(Vr, gv_off + i * kThreads * 16, k0 * ROWB, 0);
   };
-  auto store_k = [&](__bf16* dst, const u32x4 (&reg)[CH]) {
+  // thread chunk i of a K tile goes to the first or the second half tile (half0, half1: slots of the ring)
+  auto store_k_chunk = [&](__bf16* half0, __bf16* half1, int i, const u32x4& v) {
+    *(u32x4*)(&(st_half ? half1 : half0)[lk_off + i * KS]) = v;
+  };
+  auto store_k = [&](__bf16* half0, __bf16* half1, const u32x4 (&reg)[CH]) {
 #pragma unroll
-    for (int i = 0; i < CH; ++i) *(u32x4*)(&dst[lk_off + i * kRowsPerPass * KS]) = reg[i];
+    for (int i = 0; i < CH; ++i) store_k_chunk(half0, half1, i, reg[i]);
   };
   auto store_v = [&](__bf16* dst, const u32x4 (&reg)[CH]) {
 #pragma unroll
@@ -253,15 +259,17 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
     for (int dt = 0; dt < ND; ++dt) o[qs][dt] = f32x16{0};
   }
 
-  // ring slots: K(t) in kc, K(t+1) in kn, K(t+2) goes to kf; V(t) in vc, V(t+1) goes to vn
-  __bf16* kc = smem;
-  __bf16* kn = smem + KTILE;
-  __bf16* kf = smem + 2 * KTILE;
-  __bf16* vc = smem + 3 * KTILE;
-  __bf16* vn = smem + 3 * KTILE + VTILE;
+  // Ring slots.  K half tiles: kh[0] = K(t) half 1, kh[1] and kh[2] = K(t+1), K(t+2) goes to kh[3] and kh[4]
+  // (whose last readers were in iteration t - 1); V tiles: V(t) in vc, V(t+1) goes to vn.
+  __bf16* kh[5];
+#pragma unroll
+  for (int j = 0; j < 5; ++j) kh[j] = smem + j * KHALF;
+  __bf16* vc = smem + 5 * KHALF;
+  __bf16* vn = smem + 5 * KHALF + VTILE;
   auto rotate = [&]() {
-    __bf16* t = kc; kc = kn; kn = kf; kf = t;
-    t = vc; vc = vn; vn = t;
+    __bf16 *t0 = kh[0], *t1 = kh[1];
+    kh[0] = kh[2]; kh[1] = kh[3]; kh[2] = kh[4]; kh[3] = t0; kh[4] = t1;
+    t0 = vc; vc = vn; vn = t0;
   };
 
   // ---- prologue
@@ -269,35 +277,60 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
   u32x4 kreg[CH], vreg[CH];
   f32x16 sA[QS], sB[QS];
   uint32_t pA[QS][8], pB[QS][8];
-  if (T0.k0 >= 0) {
-    fetch_tok(T0.k0);
-    load_k(kreg);
-    load_v(T0.k0, vreg);
-    store_k(kc, kreg);
-    store_v(vc, vreg);
-    if (T1.k0 >= 0) {
-      fetch_tok(T1.k0);
-      load_k(kreg);
-      store_k(kn, kreg);
+  bf16x8 qf[QS][NS];             // Q^T operand fragments, in registers for the whole kernel
+  {
+    // Everything the first iterations need is requested in two rounds, first the look-ups (and V, which needs
+    // none), then the rows they name: two memory latencies instead of six (0.5 to 1 % of a launch up to 32 x 16384 rows).  Tiles that do not exist are
+    // replaced by tile 0: loaded, never used.
+    int qtok[QS], k0tok[CH], k1tok[CH], k2tok[CH];
+    u32x4 kreg0[CH], kreg1[CH], vreg0[CH];
+#pragma unroll
+    for (int qs = 0; qs < QS; ++qs) {
+      const int qr = wrow0 + 32 * qs + lo;
+      qtok[qs] = FUSED ? __builtin_amdgcn_raw_buffer_load_b32(Ir, qr * 4, 0, 0) : qr;
     }
+    fetch_tok(max(T0.k0, 0), k0tok);
+    fetch_tok(max(T1.k0, 0), k1tok);
+    fetch_tok(max(T2.k0, 0), k2tok);
+    fetch_tok(max(T3.k0, 0), ktok);
+    load_v(max(T0.k0, 0), vreg0);
+    load_v(max(T1.k0, 0), vreg);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int qs = 0; qs < QS; ++qs) {
+      const int qr = wrow0 + 32 * qs + lo;
+      int qrow_off = qr * ROWB;
+      if (FUSED) qrow_off = qr < Lc ? (int)__umul24(qtok[qs], q_pitch) : a.L * q_pitch;   // past the end: out of the buffer's range, reads zeros
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(Qr, qrow_off + 16 * hi + 32 * s, 0, 0);
+        qf[qs][s] = __builtin_bit_cast(bf16x8, v);
+      }
+    }
+    load_k(k0tok, kreg0);
+    load_k(k1tok, kreg1);
+    load_k(k2tok, kreg);
+    __builtin_amdgcn_sched_barrier(0);
+    store_v(vc, vreg0);
+    store_k(kh[3], kh[0], kreg0);                          // the first half is read by the prologue alone
+    store_k(kh[1], kh[2], kreg1);
   }
-  __syncthreads();
+  // (the stores have waited for everything but the last tile of K, on every path: otherwise the compiler would
+  // carry the Q fragments as "possibly pending" into the loop, and every MFMA that reads one would wait for
+  // the oldest K / V prefetch in flight)
+  __builtin_amdgcn_s_waitcnt(0x0F70 | CH);               // vmcnt(CH)
+  lds_barrier();
+  if (T0.k0 >= 0) qk_half<D, QS>(kh[3], k_rd, qf, sA);
+  lds_barrier();                                         // kh[3] is written in the first iteration
   auto wave_active = [&](const Tile& t) -> bool { return t.k0 >= 0 && (t.use & half_bit) && t.k0 <= wrow0 + RW - 1; };
-  if (T0.k0 >= 0) qk_half<D, QS>(kc, k_rd, qf, sA);
-  if (T2.k0 >= 0) {
-    fetch_tok(T2.k0);
-    load_k(kreg);
-  }
-  if (T1.k0 >= 0) load_v(T1.k0, vreg);
-  if (T3.k0 >= 0) fetch_tok(T3.k0);
   if (wave_active(T0)) {
     if (T0.k0 + 31 > wrow0) mask_half<QS>(sA, T0.k0, hi, wrow0 + lo);
     softmax_max<ND, QS>(sA, c, m, l, o);
   }
 
   // Invariant at the top of an iteration: sA = S^T of the first half of tile T0, already masked
-  // and already covered by the running max m (if this wavefront takes part in T0); K(T0) in kc,
-  // K(T1) in kn, V(T0) in vc; kreg = K(T2) and vreg = V(T1) are in flight; ktok = rows of T3.
+  // and already covered by the running max m (if this wavefront takes part in T0); K(T0)'s second half in
+  // kh[0], K(T1) in kh[1] and kh[2], V(T0) in vc; kreg = K(T2) and vreg = V(T1) are in flight; ktok = rows of T3.
   //
   // Order inside an iteration: every block of 16 MFMAs is issued next to vector work that does
   // not depend on it, so the matrix pipe and the VALU overlap within the wavefront:
@@ -330,12 +363,13 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
   // must all belong to block 0 (K of the next tile, complete since the previous barrier), not to
   // the V tile that this iteration is still writing
   static_assert(kChunks % kRing == 0 && kRing > kPF && kPF <= CPB, "fragment ring does not fit the chunk stream");
+  constexpr int kZChunk = 2 * CH < CPB ? 2 * CH : CPB - 1;
   bf16x8 kfr[kRing];
-  // fragment fetch for chunk c of the iteration whose tiles sit in (kc_, kn_, vc_)
-  auto fetch = [&](int c, const __bf16* kc_, const __bf16* kn_, const __bf16* vc_) {
+  // fragment fetch for chunk c of the iteration whose half tiles of K and tile of V sit in (k1_, k2_, vc_)
+  auto fetch = [&](int c, const __bf16* k1_, const __bf16* k2_, const __bf16* vc_) {
     const int blk = c / CPB, i = c % CPB, slot = c % kRing;
-    if (blk == 0) kfr[slot] = *(const bf16x8*)(&kc_[32 * KS + k_rd + 16 * i]);
-    else if (blk == 2) kfr[slot] = *(const bf16x8*)(&kn_[k_rd + 16 * i]);
+    if (blk == 0) kfr[slot] = *(const bf16x8*)(&k1_[k_rd + 16 * i]);
+    else if (blk == 2) kfr[slot] = *(const bf16x8*)(&k2_[k_rd + 16 * i]);
     else {
       const int hf = i / ND, dt = i % ND;
       kfr[slot] = *(const bf16x8*)(&vc_[v_rd + (32 * dt) * VS + (blk == 3 ? 32 : 0) + 16 * hf]);
@@ -343,7 +377,7 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
   };
   auto prime_ring = [&]() {
 #pragma unroll
-    for (int c = 0; c < kPF; ++c) fetch(c, kc, kn, vc);
+    for (int c = 0; c < kPF; ++c) fetch(c, kh[0], kh[1], vc);
   };
   // vload: byte offset of the V tile to prefetch (tile T2), tokload: first compacted row of the
   // K tile whose rows are looked up (tile T4)
@@ -361,8 +395,8 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
         else __builtin_amdgcn_s_setprio(0);
       }
       // prefetch kPF chunks ahead; the first chunks of the next iteration read the rotated slots
-      if (c + kPF < kChunks) fetch(c + kPF, kc, kn, vc);
-      else fetch(c + kPF - kChunks, kn, kf, vn);
+      if (c + kPF < kChunks) fetch(c + kPF, kh[0], kh[1], vc);
+      else fetch(c + kPF - kChunks, kh[2], kh[3], vn);
       if (blk == 0 || blk == 2) {
         const f32x16 (&s_in)[QS] = blk == 0 ? sA : sB;
         uint32_t (&p_out)[QS][8] = blk == 0 ? pA : pB;
@@ -413,18 +447,17 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
           }
           if (qs + 1 < QS) __builtin_amdgcn_sched_barrier(0);
         }
-        if (blk == 3) {                 // K(t+2) -> kf, V(t+1) -> vn, then refill the registers
-          if (i < CH) {
-            *(u32x4*)(&kf[lk_off + i * kRowsPerPass * KS]) = kreg[i];
-            kreg[i] = __builtin_amdgcn_raw_buffer_load_b128(Kr, row_off(ktok[i]) + 16 * st_col, 0, 0);
-            if (FUSED) ktok[i] = __builtin_amdgcn_raw_buffer_load_b32(Ir, (st_row + i * kRowsPerPass) * 4, tokload * 4, 0);
-            else ktok[i] = tokload + st_row + i * kRowsPerPass;
-          } else if (i < 2 * CH) {
-            *(u32x4*)(&vn[lv_off + (i - CH) * kVRowsPerPass * VS]) = vreg[i - CH];
-            vreg[i - CH] = __builtin_amdgcn_raw_buffer_load_b128(Vr, gv_off + (i - CH) * kThreads * 16, vload, 0);
-          }
+        // K(t+2) -> kh[3], kh[4], V(t+1) -> vn, then refill the registers
+        if (blk == 3 && i < CH) {
+          store_k_chunk(kh[3], kh[4], i, kreg[i]);
+          kreg[i] = __builtin_amdgcn_raw_buffer_load_b128(Kr, row_off(ktok[i]) + 16 * st_col, 0, 0);
+          if (i == CH - 1) fetch_tok(tokload, ktok);
         }
-        if (FUSED && blk == 3 && i == (2 * CH < CPB ? 2 * CH : CPB - 1) && zfill && --z_count <= 0) {
+        if (blk == 3 && i >= CH && i < 2 * CH) {
+          *(u32x4*)(&vn[lv_off + (i - CH) * kVRowsPerPass * VS]) = vreg[i - CH];
+          vreg[i - CH] = __builtin_amdgcn_raw_buffer_load_b128(Vr, gv_off + (i - CH) * kThreads * 16, vload, 0);
+        }
+        if (FUSED && blk == 3 && i == kZChunk && zfill && --z_count <= 0) {
           zero_step();
           z_count = z_every;
         }
@@ -469,7 +502,7 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
 #pragma unroll
         for (int r = 0; r < 16; ++r) sA[qs][r] = (sA[qs][r] + m[qs]) * inv_c;
     }
-    qk_half<D, QS>(kc + 32 * KS, k_rd, qf, sB);
+    qk_half<D, QS>(kh[0], k_rd, qf, sB);
     if (wave_active(T0)) {
       if (T0.k0 + BN - 1 > wrow0) mask_half<QS>(sB, T0.k0 + 32, hi, wrow0 + lo);
       softmax_exp<QS>(sA, c, m, l, pA);
@@ -478,17 +511,17 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
       softmax_exp<QS>(sB, c, m, l, pB);
       pv_half<D, QS>(vc + 32, v_rd, pB, o);
     }
-    if (T1.k0 >= 0) qk_half<D, QS>(kn, k_rd, qf, sA);
+    if (T1.k0 >= 0) qk_half<D, QS>(kh[1], k_rd, qf, sA);
     if (wave_active(T1)) {
       if (T1.k0 + 31 > wrow0) mask_half<QS>(sA, T1.k0, hi, wrow0 + lo);
       softmax_max<ND, QS>(sA, c, m, l, o);
     }
-    if (T2.k0 >= 0) store_k(kf, kreg);
+    if (T2.k0 >= 0) store_k(kh[3], kh[4], kreg);
     if (T1.k0 >= 0) store_v(vn, vreg);
-    if (T3.k0 >= 0) load_k(kreg);
+    if (T3.k0 >= 0) load_k(ktok, kreg);
     if (T2.k0 >= 0) load_v(T2.k0, vreg);
     const Tile T4 = gen.next();
-    if (T4.k0 >= 0) fetch_tok(T4.k0);
+    if (T4.k0 >= 0) fetch_tok(T4.k0, ktok);
     lds_barrier();
     T0 = T1; T1 = T2; T2 = T3; T3 = T4;
     rotate();
@@ -500,19 +533,21 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
     // look-ups of the next batch requested before the stores of the current one (so that waiting for them
     // never includes waiting for those stores to be acknowledged).
     constexpr int kBatch = 16;
-    if (zr < 0) __builtin_nontemporal_store(u32x4{0u, 0u, 0u, 0u}, zrow + (long long)zt * o_pitch16);
+#pragma unroll
+    for (int j = 0; j < ZR; ++j)
+      if (zr[j] < 0) __builtin_nontemporal_store(u32x4{0u, 0u, 0u, 0u}, zrow + (long long)(zt + j * RPT) * o_pitch16);
     int t0 = zt + RPP;
     int r[kBatch];
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) r[j] = t0 + j * RPP < z_hi ? inv_row[t0 + j * RPP] : 0;
+    for (int j = 0; j < kBatch; ++j) r[j] = t0 + j * RPT < z_hi ? inv_row[t0 + j * RPT] : 0;
     while (t0 < z_hi) {
-      const int t1 = t0 + kBatch * RPP;
+      const int t1 = t0 + kBatch * RPT;
       int rn[kBatch];
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) rn[j] = t1 + j * RPP < z_hi ? inv_row[t1 + j * RPP] : 0;
+      for (int j = 0; j < kBatch; ++j) rn[j] = t1 + j * RPT < z_hi ? inv_row[t1 + j * RPT] : 0;
 #pragma unroll
       for (int j = 0; j < kBatch; ++j)
-        if (r[j] < 0) __builtin_nontemporal_store(u32x4{0u, 0u, 0u, 0u}, zrow + (long long)(t0 + j * RPP) * o_pitch16);
+        if (r[j] < 0) __builtin_nontemporal_store(u32x4{0u, 0u, 0u, 0u}, zrow + (long long)(t0 + j * RPT) * o_pitch16);
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) r[j] = rn[j];
       t0 = t1;
@@ -557,43 +592,68 @@ __global__ __launch_bounds__(512 / QS, 2 / QS) void attend_kernel(AttendArgs a) 
 
 namespace {
 
-#ifndef TSA_SPLIT_RATIO
-#define TSA_SPLIT_RATIO 1.5
-#endif
-constexpr double kSplitRatio = TSA_SPLIT_RATIO;
-
 // Which form runs: 0 = chosen per launch, 1 = always 256 rows per workgroup, 2 = always 128 rows with
-// the keys split over two groups of wavefronts (measurement support: set_attend_form).
+// the keys split over two groups of wavefronts, 3 = always 128 rows with four wavefronts (measurement
+// support: set_attend_form).
 int g_attend_form = 0;
 
-// The 128-row form pays when the longest chain of a launch (the last query tile of a head: 4 nq tiles
-// of 64 keys for nq tiles of 256 rows) is long against the work the chip has per CU (BH * 2 nq (nq + 1)
-// tile steps over 256 CUs), i.e. for very short compacted sets.  Its iteration stages every K / V tile
-// for half as many rows, which costs about 15 % of the rate: measured at 32 heads, d = 128, it wins up
-// to 2048 compacted tokens (0.064 against 0.071 ms) and loses from 3277 on (0.139 against 0.118 ms), and
-// it loses on sink + window block lists at every block size.
-bool use_split_form(const AttendArgs& a) {
-  if (g_attend_form == 1) return false;
-  if (g_attend_form == 2) return true;
+// Longest chain of a launch (the last query tile of a head: 4 nq tiles of 64 keys for nq tiles of 256 rows) over
+// the work the chip has per CU (BH * 2 nq (nq + 1) tile steps over 256 CUs).
+double chain_ratio(const AttendArgs& a) {
   const long long nq = (a.Lc + BM - 1) / BM;
-  return 512 >= kSplitRatio * (long long)a.BH * (nq + 1);          // chain / work per CU = 512 / (BH (nq + 1))
+  return 512.0 / (double)(a.BH * (nq + 1));
+}
+
+// The split form pays for very short compacted sets, where the longest chain and not the chip's throughput is the
+// launch: it halves that chain, and stages every K / V tile for half as many rows and half as many keys per
+// wavefront.  us of the fused launch, split / four wavefronts / 256 rows: 32 heads, d = 128, 901 rows 26.3 / 28 / 35.4
+// (ratio 3.2); 8 heads x 8192 160 / 190 / 208 (1.94); 4 x 16384 285 / 348 / 366 (1.97); 32 x 2048 56.7 / 56.3 / 62.5
+// (1.78); 16 x 5000 142 / 132 / 136 (1.52).  d = 64: 8 x 8000 112 / 125 / 169 (1.94), 32 x 2000 42.5 / 40.5 / 49 (1.78).
+bool use_split_form(const AttendArgs& a) {
+  if (g_attend_form) return g_attend_form == 2;
+  return chain_ratio(a) >= 1.8;
+}
+
+// Four wavefronts per workgroup (two or three workgroups per CU) against 256 rows, us of the fused launch:
+//   d = 64 (three wavefronts per SIMD instead of two): 32 heads x 4096 rows 91.9 / 104.7, x 8192 328 / 372, x 16384
+//     1209 / 1384, sink + window lists 28 x 16384 575 / 662 (blocks of 256), 598 / 714 (128): always.
+//   d = 128, block lists with blocks of 64 or 128: a workgroup walks the lists of one or two row blocks instead of the
+//     union of up to four: 28 x 16384 598 / 696 (blocks of 64), 958 / 997 (128), 28 x 4096 89 / 113 (64); not with blocks of 256
+//     (955 / 940).
+//   d = 128, plain: a start and an end hidden under the other workgroup are worth more than the second staging of
+//     the tiles as long as the chains are short: 128 heads x 600 rows 45.4 / 56.0, 96 x 1000 50 / 55, 64 x 1500 56 / 59,
+//     32 x 2500 71.5 / 76.2, 96 x 2400 171 / 187, 40 x 3000 112 / 114, 64 x 3300 198 / 200; 32 x 3500 115 / 113,
+//     64 x 4000 282 / 279, 32 x 8192 537 / 522, x 32768 8000 / 7750; and where few heads leave the longest chain
+//     in charge (16 x 5000 132 / 136, ratio 1.52).
+constexpr int kPairRows = 3328;
+
+bool use_pair_form(const AttendArgs& a, int d) {
+  if (g_attend_form) return g_attend_form == 3;
+  return d == 64 || (a.block_list && a.block < 256) || (!a.block_list && a.Lc <= kPairRows) || chain_ratio(a) >= 1.3;
+}
+
+template <bool FUSED, int NW>
+hipError_t launch_rows(AttendArgs& a, int d, hipStream_t st) {
+  constexpr int rows = 32 * kQS * NW;
+  a.nq_tiles = (a.Lc + rows - 1) / rows;
+  a.nk_tiles = (a.Lc + BN - 1) / BN;
+  map_workgroups(a);
+  const unsigned grid = grid_for(a);
+  if (a.block_list) {
+    if (d == 128) attend_kernel<128, kQS, NW, FUSED, true><<<grid, 64 * NW, 0, st>>>(a);
+    else attend_kernel<64, kQS, NW, FUSED, true><<<grid, 64 * NW, 0, st>>>(a);
+  } else {
+    if (d == 128) attend_kernel<128, kQS, NW, FUSED, false><<<grid, 64 * NW, 0, st>>>(a);
+    else attend_kernel<64, kQS, NW, FUSED, false><<<grid, 64 * NW, 0, st>>>(a);
+  }
+  return hipGetLastError();
 }
 
 template <bool FUSED>
 hipError_t launch_any(AttendArgs& a, int d, hipStream_t st) {
   if (kQS == 1 && use_split_form(a)) return launch_attend_split(a, d, FUSED, st);
-  a.nq_tiles = (a.Lc + BM - 1) / BM;
-  a.nk_tiles = (a.Lc + BN - 1) / BN;
-  map_workgroups(a);
-  const unsigned grid = grid_for(a);
-  if (a.block_list) {
-    if (d == 128) attend_kernel<128, kQS, FUSED, true><<<grid, 512 / kQS, 0, st>>>(a);
-    else attend_kernel<64, kQS, FUSED, true><<<grid, 512 / kQS, 0, st>>>(a);
-  } else {
-    if (d == 128) attend_kernel<128, kQS, FUSED, false><<<grid, 512 / kQS, 0, st>>>(a);
-    else attend_kernel<64, kQS, FUSED, false><<<grid, 512 / kQS, 0, st>>>(a);
-  }
-  return hipGetLastError();
+  if (kQS == 1 && use_pair_form(a, d)) return launch_rows<FUSED, 4>(a, d, st);
+  return launch_rows<FUSED, 8 / kQS>(a, d, st);
 }
 
 }  // namespace

@@ -111,7 +111,7 @@ hipError_t launch_attend_fused(const Dims& dm, const void* Q, const void* K, con
                                const int32_t* k_dev = nullptr);
 
 // attend.hip: 0 = the form of the attention kernel is chosen per launch (default), 1 = 256 query rows per
-// workgroup always, 2 = 128 rows with split keys always (measurement support)
+// workgroup always, 2 = 128 rows with split keys always, 3 = 128 rows with four wavefronts always (measurement support)
 void set_attend_form(int form);
 
 // probe.hip: bare MFMA loop, 8 * iters MFMAs per wavefront, 4 wavefronts per workgroup
