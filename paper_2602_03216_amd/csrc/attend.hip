@@ -63,7 +63,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   constexpr int ND = D / 32;                      // d sub-tiles of the output
   constexpr int ROWB = D * 2;                     // bytes of one row in global memory
   constexpr int KHALF = KTILE / 2;
-  __shared__ __attribute__((aligned(16))) __bf16 smem[5 * KHALF + 2 * VTILE];   // K ring [5 half tiles], V ring [2 tiles]
+  constexpr int KRING = NW == 8 ? 6 : 5;          // half tiles of the K ring
+  __shared__ __attribute__((aligned(16))) __bf16 smem[KRING * KHALF + 2 * VTILE];   // K ring, V ring [2 tiles]
 
   // ---- workgroup -> (head, query tile).  Consecutive workgroup ids go to different XCDs, so
   // id % 8 picks the XCD; all tiles of a head (and all heads of a KV group) stay on one XCD to
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   // 8 * (piece % 8).. .  The tile's first key goes into the scalar offset of the buffer load.
   const int st_row = CH * (tid / (D / 8)), st_col = tid % (D / 8);   // K rows st_row .. st_row + CH - 1 of the tile
   const bool st_half = __builtin_amdgcn_readfirstlane(st_row) >= 32; // (a wavefront's rows lie in one half tile)
-  const int lk_off = k_row_perm(st_row & 31) * KS + 8 * st_col;   // elements, LDS side (K): permuted row order (which leaves
+  const int lk_off = k_row_perm(NW == 8 ? st_row : st_row & 31) * KS + 8 * st_col;   // elements, LDS side (K): permuted row order (which leaves
                                                                   // the CH <= 4 rows of a thread next to each other)
   const int gv_off = 16 * tid;                                    // bytes, global side (V^T)
   const int lv_off = (tid >> 3) * VS + 8 * (tid & 7);             // elements, LDS side (V^T)
@@ -229,9 +230,10 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
     for (int i = 0; i < CH; ++i)
       reg[i] = __builtin_amdgcn_raw_buffer_load_b128(Vr, gv_off + i * kThreads * 16, k0 * ROWB, 0);
   };
-  // thread chunk i of a K tile goes to the first or the second half tile (half0, half1: slots of the ring)
+  // thread chunk i of a K tile goes to the first or the second half tile (half0, half1: slots of the ring; with eight
+  // wavefronts half1 follows half0)
   auto store_k_chunk = [&](__bf16* half0, __bf16* half1, int i, const u32x4& v) {
-    *(u32x4*)(&(st_half ? half1 : half0)[lk_off + i * KS]) = v;
+    *(u32x4*)(&(NW == 4 && st_half ? half1 : half0)[lk_off + i * KS]) = v;
   };
   auto store_k = [&](__bf16* half0, __bf16* half1, const u32x4 (&reg)[CH]) {
 #pragma unroll
@@ -259,16 +261,20 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
     for (int dt = 0; dt < ND; ++dt) o[qs][dt] = f32x16{0};
   }
 
-  // Ring slots.  K half tiles: kh[0] = K(t) half 1, kh[1] and kh[2] = K(t+1), K(t+2) goes to kh[3] and kh[4]
-  // (whose last readers were in iteration t - 1); V tiles: V(t) in vc, V(t+1) goes to vn.
-  __bf16* kh[5];
+  // Ring slots.  K half tiles: kh(0) = K(t) half 1, kh(1) and kh(2) = K(t+1), K(t+2) goes to kh(3) and kh(4)
+  // (whose last readers were in iteration t - 1); V tiles: V(t) in vc, V(t+1) goes to vn.  With eight wavefronts the
+  // LDS has room for three whole tiles, whose halves are one address register and an offset (0.4 % of a long launch).
+  __bf16* kr[5];
 #pragma unroll
-  for (int j = 0; j < 5; ++j) kh[j] = smem + j * KHALF;
-  __bf16* vc = smem + 5 * KHALF;
-  __bf16* vn = smem + 5 * KHALF + VTILE;
+  for (int j = 0; j < 5; ++j) kr[j] = smem + (NW == 8 ? 2 * j : j) * KHALF;   // (eight wavefronts: tiles t, t + 1, t + 2)
+  auto kh = [&](int j) -> __bf16* { return NW == 8 ? kr[(j + 1) >> 1] + ((j + 1) & 1) * KHALF : kr[j]; };
+  auto k_first = [&]() -> __bf16* { return NW == 8 ? kr[0] : kr[3]; };         // K(0) half 0, read by the prologue alone
+  __bf16* vc = smem + KRING * KHALF;
+  __bf16* vn = smem + KRING * KHALF + VTILE;
   auto rotate = [&]() {
-    __bf16 *t0 = kh[0], *t1 = kh[1];
-    kh[0] = kh[2]; kh[1] = kh[3]; kh[2] = kh[4]; kh[3] = t0; kh[4] = t1;
+    __bf16 *t0 = kr[0], *t1 = kr[1];
+    if (NW == 8) { kr[0] = kr[1]; kr[1] = kr[2]; kr[2] = t0; }
+    else { kr[0] = kr[2]; kr[1] = kr[3]; kr[2] = kr[4]; kr[3] = t0; kr[4] = t1; }
     t0 = vc; vc = vn; vn = t0;
   };
 
@@ -312,16 +318,16 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
     load_k(k2tok, kreg);
     __builtin_amdgcn_sched_barrier(0);
     store_v(vc, vreg0);
-    store_k(kh[3], kh[0], kreg0);                          // the first half is read by the prologue alone
-    store_k(kh[1], kh[2], kreg1);
+    store_k(k_first(), kh(0), kreg0);
+    store_k(kh(1), kh(2), kreg1);
   }
   // (the stores have waited for everything but the last tile of K, on every path: otherwise the compiler would
   // carry the Q fragments as "possibly pending" into the loop, and every MFMA that reads one would wait for
   // the oldest K / V prefetch in flight)
   __builtin_amdgcn_s_waitcnt(0x0F70 | CH);               // vmcnt(CH)
   lds_barrier();
-  if (T0.k0 >= 0) qk_half<D, QS>(kh[3], k_rd, qf, sA);
-  lds_barrier();                                         // kh[3] is written in the first iteration
+  if (T0.k0 >= 0) qk_half<D, QS>(k_first(), k_rd, qf, sA);
+  if (NW != 8) lds_barrier();                            // that slot is written in the first iteration
   auto wave_active = [&](const Tile& t) -> bool { return t.k0 >= 0 && (t.use & half_bit) && t.k0 <= wrow0 + RW - 1; };
   if (wave_active(T0)) {
     if (T0.k0 + 31 > wrow0) mask_half<QS>(sA, T0.k0, hi, wrow0 + lo);
@@ -330,7 +336,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
 
   // Invariant at the top of an iteration: sA = S^T of the first half of tile T0, already masked
   // and already covered by the running max m (if this wavefront takes part in T0); K(T0)'s second half in
-  // kh[0], K(T1) in kh[1] and kh[2], V(T0) in vc; kreg = K(T2) and vreg = V(T1) are in flight; ktok = rows of T3.
+  // kh(0), K(T1) in kh(1) and kh(2), V(T0) in vc; kreg = K(T2) and vreg = V(T1) are in flight; ktok = rows of T3.
   //
   // Order inside an iteration: every block of 16 MFMAs is issued next to vector work that does
   // not depend on it, so the matrix pipe and the VALU overlap within the wavefront:
@@ -377,7 +383,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   };
   auto prime_ring = [&]() {
 #pragma unroll
-    for (int c = 0; c < kPF; ++c) fetch(c, kh[0], kh[1], vc);
+    for (int c = 0; c < kPF; ++c) fetch(c, kh(0), kh(1), vc);
   };
   // vload: byte offset of the V tile to prefetch (tile T2), tokload: first compacted row of the
   // K tile whose rows are looked up (tile T4)
@@ -395,8 +401,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
         else __builtin_amdgcn_s_setprio(0);
       }
       // prefetch kPF chunks ahead; the first chunks of the next iteration read the rotated slots
-      if (c + kPF < kChunks) fetch(c + kPF, kh[0], kh[1], vc);
-      else fetch(c + kPF - kChunks, kh[2], kh[3], vn);
+      if (c + kPF < kChunks) fetch(c + kPF, kh(0), kh(1), vc);
+      else fetch(c + kPF - kChunks, kh(2), kh(3), vn);
       if (blk == 0 || blk == 2) {
         const f32x16 (&s_in)[QS] = blk == 0 ? sA : sB;
         uint32_t (&p_out)[QS][8] = blk == 0 ? pA : pB;
@@ -447,9 +453,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
           }
           if (qs + 1 < QS) __builtin_amdgcn_sched_barrier(0);
         }
-        // K(t+2) -> kh[3], kh[4], V(t+1) -> vn, then refill the registers
+        // K(t+2) -> kh(3), kh(4), V(t+1) -> vn, then refill the registers
         if (blk == 3 && i < CH) {
-          store_k_chunk(kh[3], kh[4], i, kreg[i]);
+          store_k_chunk(kh(3), kh(4), i, kreg[i]);
           kreg[i] = __builtin_amdgcn_raw_buffer_load_b128(Kr, row_off(ktok[i]) + 16 * st_col, 0, 0);
           if (i == CH - 1) fetch_tok(tokload, ktok);
         }
@@ -502,7 +508,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
 #pragma unroll
         for (int r = 0; r < 16; ++r) sA[qs][r] = (sA[qs][r] + m[qs]) * inv_c;
     }
-    qk_half<D, QS>(kh[0], k_rd, qf, sB);
+    qk_half<D, QS>(kh(0), k_rd, qf, sB);
     if (wave_active(T0)) {
       if (T0.k0 + BN - 1 > wrow0) mask_half<QS>(sB, T0.k0 + 32, hi, wrow0 + lo);
       softmax_exp<QS>(sA, c, m, l, pA);
@@ -511,12 +517,12 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
       softmax_exp<QS>(sB, c, m, l, pB);
       pv_half<D, QS>(vc + 32, v_rd, pB, o);
     }
-    if (T1.k0 >= 0) qk_half<D, QS>(kh[1], k_rd, qf, sA);
+    if (T1.k0 >= 0) qk_half<D, QS>(kh(1), k_rd, qf, sA);
     if (wave_active(T1)) {
       if (T1.k0 + 31 > wrow0) mask_half<QS>(sA, T1.k0, hi, wrow0 + lo);
       softmax_max<ND, QS>(sA, c, m, l, o);
     }
-    if (T2.k0 >= 0) store_k(kh[3], kh[4], kreg);
+    if (T2.k0 >= 0) store_k(kh(3), kh(4), kreg);
     if (T1.k0 >= 0) store_v(vn, vreg);
     if (T3.k0 >= 0) load_k(ktok, kreg);
     if (T2.k0 >= 0) load_v(T2.k0, vreg);
