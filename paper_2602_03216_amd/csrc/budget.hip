@@ -80,17 +80,30 @@ __device__ __forceinline__ double bin_mass(unsigned long long isum, uint32_t key
 }
 
 // s_l = sum over heads, fp32, in head order; also clears the histograms of the four passes
-__global__ __launch_bounds__(kThreads) void head_sum_kernel(BudArgs a) {
+// Bound by memory latency (a few MB of scores): small workgroups, so that every CU has one from 16K tokens up, and the
+// loads of eight heads requested together; the additions stay in head order.  12345 tokens x
+// 32 heads: 11.2 -> 4.8 us (1024 threads, one load at a time before).
+constexpr int kSumThreads = 64, kSumHeads = 8;
+__global__ __launch_bounds__(kSumThreads) void head_sum_kernel(BudArgs a) {
   const long long b = blockIdx.y;
-  const int t = blockIdx.x * kThreads + threadIdx.x;
+  const int t = blockIdx.x * kSumThreads + threadIdx.x;
   if (t < a.L) {
+    const float* p = a.scores + b * a.Hq * a.L + t;
     float acc = 0.f;
-    for (int h = 0; h < a.Hq; ++h) acc += a.scores[(b * a.Hq + h) * a.L + t];
+    int h = 0;
+    for (; h + kSumHeads <= a.Hq; h += kSumHeads) {
+      float v[kSumHeads];
+#pragma unroll
+      for (int j = 0; j < kSumHeads; ++j) v[j] = p[(long long)(h + j) * a.L];
+#pragma unroll
+      for (int j = 0; j < kSumHeads; ++j) acc += v[j];
+    }
+    for (; h < a.Hq; ++h) acc += p[(long long)h * a.L];
     a.sl[b * a.L + t] = acc;
   }
   constexpr int n_words = (int)(sizeof(BudRow) / 4);
   uint32_t* row = (uint32_t*)(a.rows + b);
-  for (int i = t; i < n_words; i += gridDim.x * kThreads) row[i] = 0u;
+  for (int i = t; i < n_words; i += gridDim.x * kSumThreads) row[i] = 0u;
 }
 
 // Walks the 256 bins of one pass upwards (first wavefront): lane l owns bins 4l..4l+3.
@@ -247,7 +260,7 @@ hipError_t launch_budget(const Dims& dm, const float* scores, double tau_cov, in
   a.sl = (float*)((char*)ws + align256((size_t)dm.B * sizeof(BudRow)));
   a.k_keep = k_keep;
   a.Hq = dm.Hq; a.L = dm.L; a.tau = tau_cov;
-  head_sum_kernel<<<dim3((dm.L + kThreads - 1) / kThreads, dm.B), kThreads, 0, st>>>(a);
+  head_sum_kernel<<<dim3((dm.L + kSumThreads - 1) / kSumThreads, dm.B), kSumThreads, 0, st>>>(a);
   const dim3 grid((dm.L + kSlice - 1) / kSlice, dm.B);
   bud_hist_kernel<0><<<grid, kThreads, 0, st>>>(a);
   bud_hist_kernel<1><<<grid, kThreads, 0, st>>>(a);
