@@ -337,11 +337,9 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
-// order_key without its branches: adding +0 turns -0 into +0 and leaves every other value as it is
-__device__ __forceinline__ uint32_t order_key_fast(float f) {
-  const uint32_t u = __float_as_uint(f + 0.0f);
-  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-}
+// The order of order_key on other numbers, [1, 0xffffffff]: a negative value's bits are negated instead of inverted,
+// which maps -0 to +0's key, leaves every other bit pattern a key of its own (NaNs among them) and key 0 to nothing.
+__device__ __forceinline__ uint32_t row_key(uint32_t u) { return (int32_t)u < 0 ? 0u - u : u | 0x80000000u; }
 
 // set bits of a ballot below this lane
 __device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
@@ -385,13 +383,14 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
 #pragma unroll
     for (int e = 0; e < 4; ++e) key[j][e] = __float_as_uint(v[e]);
   }
-  // Ordinary keys lie in [1, 0xfffffffe] (which only NaNs would leave); 0 = beyond the row, 0xffffffff = always
-  // kept: both stay outside the descent.  Few steps of a row hold such a token.
+  // 0 = beyond the row, 0xffffffff = always kept (where there are such tokens, the one NaN with that key takes the key of
+  // the NaN next to it): both stay outside the descent.  Few steps of a row hold such a token.
   const uint32_t n_forced = (uint32_t)(a.ff + a.fl);
+  const uint32_t top = n_forced ? 0xfffffffeu : 0xffffffffu;
 #pragma unroll
   for (int j = 0; j < J; ++j) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) key[j][e] = min(max(order_key_fast(__uint_as_float(key[j][e])), 1u), 0xfffffffeu);
+    for (int e = 0; e < 4; ++e) key[j][e] = min(row_key(key[j][e]), top);
     const int first = wave * 256 * J + 256 * j;
     if (first < a.ff || first + 256 > a.L - a.fl) {        // the same for the whole wavefront
 #pragma unroll

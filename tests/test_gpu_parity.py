@@ -180,6 +180,37 @@ def test_select_row_edges(tsa, L):
         assert np.array_equal(idx, widx) and np.array_equal(inv, winv), (L, k)
 
 
+@pytest.mark.parametrize("L", [100, 5000, 40000, 65536, 65537, 90000])
+def test_select_every_bit_pattern_in_order(tsa, L):
+    """Infinities, NaNs of both signs and every payload at the ends of the range, denormals and both zeros: all lengths
+    of row order them by the same image of their bits (-NaN < -inf < .. < -0 = +0 < .. < +inf < +NaN, NaNs by payload),
+    ties to the lowest token, so a row's set does not depend on which kernel its length takes."""
+    r = _rng(930 + L)
+    edge = np.array([0x7f800000, 0xff800000, 0x7fffffff, 0x7ffffffe, 0x7f800001, 0x7fc00000, 0x7fc00001, 0xffffffff, 0xfffffffe,
+                     0xff800001, 0xffc00000, 0, 0x80000000, 1, 0x80000001, 0x007fffff, 0x807fffff, 0x3f800000, 0xbf800000],
+                    dtype=np.uint32)
+    mixed = r.integers(0, 1 << 32, L, dtype=np.uint64).astype(np.uint32)
+    mixed[r.permutation(L)[: L // 2]] = edge[r.integers(0, len(edge), L // 2)]
+    only = edge[r.integers(0, len(edge), L)]
+    inf = np.where(r.random(L) < 0.4, np.uint32(0xff800000), (r.random(L).astype(np.float32)).view(np.uint32))
+    inf[r.permutation(L)[:5]] = 0x7f800000
+    bits = np.stack([mixed, only, inf]).astype(np.uint32)
+    key = np.where(bits >> 31, ~bits, bits | np.uint32(0x80000000)).astype(np.int64)
+    key[bits == 0x80000000] = 0x80000000
+    for k in sorted({1, L // 50, L // 3, L - L // 50, L - 1, L}):
+        for ff, fl in ((0, 0), (k // 2, min(3, k // 2))):
+            kk, b = key.copy(), bits.copy()
+            if ff + fl:                                    # the topmost NaN is left out beside always-kept tokens
+                b[b == 0x7fffffff] = 0x7ffffffe
+                kk[kk == 0xffffffff] = 0xfffffffe
+                kk[:, :ff] = kk[:, L - fl:] = 1 << 32
+            idx, inv = _run_select(tsa, b.view(np.float32)[None], k, force_first=ff, force_last=fl)
+            for row in range(3):
+                want = np.sort(np.lexsort((np.arange(L), -kk[row]))[:k])
+                assert np.array_equal(idx[0, row], want), (L, k, ff, row)
+                assert np.array_equal(np.flatnonzero(inv[0, row] >= 0), want), (L, k, ff, row)
+
+
 # ------------------------------------------------------------------ compress / decompress
 
 # k = 201 of 777 rows kept: the two-stream scatter kernel (copies driven by idx, zeros by inv);
