@@ -325,6 +325,8 @@ __global__ __launch_bounds__(kThreads) void write_kernel(SelArgs a) {
 // Selection + gather, 32 rows: 901 of 3001 tokens 14.0 -> 10.6 us, 4096 of 8192: 21.9 -> 20.4, 3277 of 32768: 27.4 -> 26.2,
 // 16384 of 32768: 65.3 -> 63.7 (the last one and the second at the rate of HBM).
 constexpr int kBins = 4096;
+constexpr uint32_t kHotLanes = 16;  // keys of a wavefront in one bin from which they are counted by ballots
+constexpr int kCrowd = 2048;        // keys left in a bin from which their range is taken anew
 constexpr int kRank = 256;          // that many keys are ranked against each other instead of binned again
 constexpr int kRowMaxL = 65536;
 constexpr int kCUs = 256;
@@ -467,13 +469,42 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
         break;
       }
       const int shift = bits > 12 ? bits - 12 : 0;
+      // LDS atomics on one address run one after the other (0.85 ns each), and one bin takes most keys of a row where its far
+      // tokens' probabilities underflow to 0 or an outlier stretches the range.  A wavefront looks for such a bin among
+      // the keys of its first step and counts that bin's keys by ballots.  With the new range below, 32 rows of 32768: 60 %
+      // zeros 33 -> 21 us, one value and an outlier 98 -> 20, a cluster and an outlier 51 -> 26, softmax-like scores
+      // 17.6 -> 17.9.  Several crowded bins cost more: two values 65 -> 31, four 44 -> 29 (the sliced kernels: 28 to 31 us
+      // on all of these).
+      uint32_t hot = 0xffffffffu, hot_lanes = kHotLanes - 1;
 #pragma unroll
-      for (int j = 0; j < J; ++j)
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t d = key[0][e] - lo, bin = d >> shift;
+        const uint32_t cand = (uint32_t)__builtin_amdgcn_readlane((int)bin, 16 * e + 5);
+        const uint32_t lanes = (uint32_t)__popcll(__ballot(d <= width && bin == cand));
+        if (lanes > hot_lanes) { hot_lanes = lanes; hot = cand; }
+      }
+      if (hot == 0xffffffffu) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t k = key[j][e];
-          if (k - lo <= width) atomicAdd(&hist[(k - lo) >> shift], 1u);
-        }
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t k = key[j][e] - lo;
+            if (k <= width) atomicAdd(&hist[k >> shift], 1u);
+          }
+      } else {
+        uint32_t n_hot = 0;
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t k = key[j][e] - lo, bin = k >> shift;
+            const bool in = k <= width;
+            n_hot += (uint32_t)__popcll(__ballot(in && bin == hot));
+            asm volatile("" : "+s"(n_hot));                // summed at once: the counts of all steps do not fit the scalar registers
+            if (in && bin != hot) atomicAdd(&hist[bin], 1u);
+          }
+        if (lane == 0) atomicAdd(&hist[hot], n_hot);
+      }
       __syncthreads();
       // bin of the rem-th largest: thread i owns the bins 4095 - 4 i .. 4092 - 4 i
       const u32x4 c = *(const u32x4*)&hist[kBins - 4 - 4 * tid];
@@ -504,6 +535,28 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
       rem = uniform(sh_rem);
       n_in = uniform(sh_cnt);
       bits = shift;
+      if (bits > 0 && n_in > (uint32_t)kCrowd) {
+        // a bin with that many keys often holds one value or a narrow cluster: go on with the range they span
+        const uint32_t w = min((1u << bits) - 1u, kmax - lo);
+        uint32_t hi_k = 0u, lo_k = 0xffffffffu;
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool in = key[j][e] - lo <= w;
+            hi_k = max(hi_k, in ? key[j][e] : 0u);
+            lo_k = min(lo_k, in ? key[j][e] : 0xffffffffu);
+          }
+        hi_k = wave_max(hi_k);
+        lo_k = ~wave_max(~lo_k);
+        if (lane == 0) { wtot[wave] = hi_k; wlo[wave] = lo_k; }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) { hi_k = max(hi_k, wtot[q]); lo_k = min(lo_k, wlo[q]); }
+        kmax = uniform(hi_k);
+        lo = uniform(lo_k);
+        bits = kmax > lo ? 32 - __clz((int)(kmax - lo)) : 0;
+      }
     }
   }
 

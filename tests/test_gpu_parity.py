@@ -211,6 +211,28 @@ def test_select_every_bit_pattern_in_order(tsa, L):
                 assert np.array_equal(np.flatnonzero(inv[0, row] >= 0), want), (L, k, ff, row)
 
 
+@pytest.mark.parametrize("L", [64, 300, 4096, 4099, 12000, 16385, 24577, 32768, 40000, 49152])
+def test_select_crowded_bins(tsa, L):
+    """Rows whose keys crowd into one bin of a histogram pass: most scores zero, one value beside an outlier at either end,
+    a cluster beside an outlier, few distinct values, and rows where only some wavefronts see a crowded bin.  Twelve rows:
+    the one-launch kernel takes them at all these lengths."""
+    r = _rng(960 + L)
+    zeros = np.where(r.random(L) < 0.6, 0.0, r.random(L)).astype(np.float32)
+    one, low = np.full(L, 0.25, np.float32), np.full(L, 0.25, np.float32)
+    one[L // 2], low[L // 3] = 3.0, -7.0
+    cluster = (1.0 + 1e-4 * r.standard_normal(L)).astype(np.float32)
+    cluster[5] = 1e5
+    few = r.integers(0, 3, L).astype(np.float32)
+    part = r.random(L).astype(np.float32)
+    part[L // 4: L // 2] = 0.125
+    s = np.stack([zeros, one, low, cluster, few, part] * 2)[None]
+    for k in sorted({1, L // 3, L - L // 4, L - 1}):
+        ff, fl = (2, 1) if k > 3 and k % 2 else (0, 0)
+        idx, inv = _run_select(tsa, s, k, force_first=ff, force_last=fl)
+        widx, winv = orc.select(s, k, ff, fl)
+        assert np.array_equal(idx, widx) and np.array_equal(inv, winv), (L, k)
+
+
 # ------------------------------------------------------------------ compress / decompress
 
 # k = 201 of 777 rows kept: the two-stream scatter kernel (copies driven by idx, zeros by inv);
