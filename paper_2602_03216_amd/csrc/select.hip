@@ -310,7 +310,7 @@ __global__ __launch_bounds__(kThreads) void write_kernel(SelArgs a) {
 // magnitude (equal 8-bit digits of softmax scores fall into a handful of bins, and LDS atomics on one
 // address run one after the other).  A pass narrows the range by 2^12; as soon as the bin with the k-th key
 // holds at most kRank keys, they are ranked against each other directly.  At most three
-// passes, one or two in practice.  With per-group sets the sum over the g heads happens in the key load.
+// passes, one or two in practice.  With per-group sets the sum over the g heads happens in the key load or before it (kInlineSum).
 // Bound: one CU's share of a row: 4 bytes per token into one CU and the vector instructions per key (at 32768 tokens
 // of 15 us: 3 launch, 4 load, 3 keys and range, 3 histogram and ranking, 3 counting and compaction).
 // Measured on softmax-like scores, 32 rows, against the former kernels (8-bit digits: one workgroup per row with the
@@ -329,6 +329,12 @@ constexpr uint32_t kHotLanes = 16;  // keys of a wavefront in one bin from which
 constexpr int kCrowd = 2048;        // keys left in a bin from which their range is taken anew
 constexpr int kRank = 256;          // that many keys are ranked against each other instead of binned again
 constexpr int kRowMaxL = 65536;
+// A row's workgroup can sum the g heads of its group while it loads them, but one CU then reads g rows, a head at a
+// time (and in the layer every part of the row does).  Beyond that many extra scores the chip-wide sum in a launch of
+// its own is faster, us without / with that launch: (g - 1) L = 24576 (4 x 8192) 9.7 / 11.4, 57344 (8 x 8192) 10.5 / 11.6 (whole layer
+// 67.8 / 67.8), 98304 (4 x 32768) 19.8 / 19.9 (layer 156 / 154), 114688 (8 x 16384) 14.9 / 14.4 (layer 98.4 / 94.5), 229376 23.3 / 20.3,
+// 1015808 (32 x 32768) 58 / 22; 32 heads.
+constexpr long long kInlineSum = 65536;
 constexpr int kCUs = 256;
 
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
@@ -705,20 +711,23 @@ hipError_t launch_select(const Dims& dm, const float* scores, int k_keep, int32_
   a.L = dm.L; a.k = k_keep; a.ff = dm.force_first; a.fl = dm.force_last; a.nslices = n_slices(dm);
   a.k_dev = k_dev; a.k_stride = k_keep; a.rows_per_b = rows / dm.B;
   a.slice = slice_for(dm);
-  if (dm.L <= kRowMaxL) {
+  int g = dm.group_mode ? dm.Hq / dm.Hkv : 1;
+  const bool one_launch = dm.L <= kRowMaxL;
+  if (g > 1 && (!one_launch || (long long)(g - 1) * dm.L > kInlineSum)) {
+    float* gs = (float*)((char*)a.slices + align256((size_t)rows * n_slices(dm) * sizeof(SliceWs)));
+    const long long n = (long long)rows * dm.L;
+    group_sum_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(scores, gs, g, dm.L, n);
+    a.scores = gs;
+    g = 1;
+  }
+  if (one_launch) {
     const bool with_tiles = Vt && 2 * rows <= kCUs;
     a.tiles = v_tiles_of(dm, k_keep, V, with_tiles ? Vt : nullptr);
     a.n_rows = rows;
     a.parts = with_tiles ? min(kCUs / rows, a.tiles.nk_tiles) : 1;
-    run_select_row(a, dm.group_mode ? dm.Hq / dm.Hkv : 1, st);
+    run_select_row(a, g, st);
     if (Vt && !with_tiles) return launch_compress_v_tiles(dm, V, idx, k_keep, Vt, st, k_dev);
     return hipGetLastError();
-  }
-  if (dm.group_mode) {
-    float* gs = (float*)((char*)a.slices + align256((size_t)rows * n_slices(dm) * sizeof(SliceWs)));
-    const long long n = (long long)rows * dm.L;
-    group_sum_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(scores, gs, dm.Hq / dm.Hkv, dm.L, n);
-    a.scores = gs;
   }
   const dim3 grid(a.nslices, rows);
   hist_kernel<0><<<grid, kThreads, 0, st>>>(a);

@@ -233,6 +233,23 @@ def test_select_crowded_bins(tsa, L):
         assert np.array_equal(idx, widx) and np.array_equal(inv, winv), (L, k)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(1, 6, 2, 32768), (1, 6, 2, 32769), (2, 4, 1, 21845), (2, 4, 1, 21846), (1, 16, 2, 9362),
+                                        (1, 16, 2, 9363), (1, 32, 1, 700), (1, 32, 1, 40000), (1, 4, 2, 65536), (1, 28, 4, 65537)])
+def test_select_group_sums(tsa, B, Hq, Hkv, L):
+    """Sets per KV group from the fp32 sum of the heads' scores in head order, on both sides of the line up to which the
+    selection adds the heads while it loads them (65536 extra scores per row): general values, bit for bit."""
+    r = _rng(990 + L)
+    g, k = Hq // Hkv, L // 3
+    s = np.exp(2 * r.standard_normal((B, Hq, L))).astype(np.float32)
+    total = np.zeros((B, Hkv, L), np.float32)
+    for j in range(g):
+        total += s[:, j::g]
+    for ff, fl in ((0, 0), (4, 9)):
+        idx, inv = _run_select(tsa, s, k, Hkv=Hkv, group_mode=1, force_first=ff, force_last=fl)
+        widx, winv = orc.select(total, k, ff, fl)
+        assert np.array_equal(idx, widx) and np.array_equal(inv, winv), (L, ff)
+
+
 # ------------------------------------------------------------------ compress / decompress
 
 # k = 201 of 777 rows kept: the two-stream scatter kernel (copies driven by idx, zeros by inv);
@@ -570,7 +587,7 @@ def test_fused_path_equals_the_separate_calls(tsa, attend_form, B, Hq, Hkv, L, d
 
 @pytest.mark.parametrize("B,Hq,Hkv,L,d,k,group_mode", [
     (1, 1, 1, 70, 64, 64, 0), (1, 1, 1, 5000, 128, 1, 0), (1, 7, 7, 4097, 64, 65, 0), (2, 50, 10, 600, 128, 129, 0),
-    (4, 32, 32, 300, 64, 300, 0), (3, 43, 43, 200, 64, 63, 0), (1, 8, 2, 8193, 128, 1000, 1),
+    (4, 32, 32, 300, 64, 300, 0), (3, 43, 43, 200, 64, 63, 0), (1, 8, 2, 8193, 128, 1000, 1), (1, 16, 1, 5000, 64, 700, 1),
 ])
 def test_selection_with_v_tiles(tsa, B, Hq, Hkv, L, d, k, group_mode):
     """The selection that also gathers V (up to 128 rows: several workgroups per row; above: two launches), against
