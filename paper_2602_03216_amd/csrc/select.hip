@@ -1,7 +1,8 @@
 // Head-wise top-k selection: Algorithm 1 of the paper, S_h = TopK(s_h, k_keep).
 // Exact: the k_keep largest scores, ties to the lowest token index, emitted in ascending
 // token order together with the inverse map.  Integer work on the order-preserving uint32
-// image of the fp32 score.  Rows of up to 65536 tokens take one launch (select_row_kernel, below); longer ones:
+// image of the fp32 score.  Rows of up to 32768 tokens (65536 if there are many) take one launch (select_row_kernel,
+// below); longer ones:
 //   1. radix select, 4 passes of 8 bits, most significant first: every pass histograms the
 //      digit of the keys that still match the prefix found so far (LDS histograms per
 //      wavefront), and the next kernel derives the digit of the k-th largest key from the
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(kThreads) void write_kernel(SelArgs a) {
   }
 }
 
-// Rows of up to kRowMaxL tokens: the whole selection of a row in ONE launch by one workgroup.  The keys of the row
+// Rows of up to row_max_tokens: the whole selection of a row in ONE launch by one workgroup.  The keys of the row
 // stay in registers (4 J per lane; a wavefront owns 256 J consecutive tokens, lane l of step j the four tokens
 // 256 j + 4 l ..), and the threshold comes from a radix descent over the RANGE the row's keys span: the first
 // pass cuts [smallest key, largest key] into kBins equal bins, so the keys spread over the bins whatever their
@@ -315,8 +316,7 @@ __global__ __launch_bounds__(kThreads) void write_kernel(SelArgs a) {
 // of 15 us: 3 launch, 4 load, 3 keys and range, 3 histogram and ranking, 3 counting and compaction).
 // Measured on softmax-like scores, 32 rows, against the former kernels (8-bit digits: one workgroup per row with the
 // keys in LDS up to 16384 tokens, the five sliced launches above that): 3001 tokens 10.6 -> 6.9 us, 8192: 18.2 -> 8.1,
-// 12345: 24.6 -> 10.1, 32768: 28.8 -> 15.3, 28 rows of 65536: 33.7 -> 28.4, 96 rows of 65536: 72 -> 32 us.
-// 65536 tokens are what the registers of 16 wavefronts hold; longer rows take the sliced kernels.
+// 12345: 24.6 -> 10.1, 32768: 28.8 -> 15.3, 96 rows of 65536: 72 -> 32 us.
 // A launch of few rows leaves most CUs idle, and the gather of the selected V rows that follows in the whole layer is
 // a launch of its own that waits for the last row.  With up to 128 rows, `parts` workgroups therefore take the same row
 // where the caller wants the V tiles: each of them finds the threshold (the scores come out of the L2 that the parts of
@@ -328,7 +328,11 @@ constexpr int kBins = 4096;
 constexpr uint32_t kHotLanes = 16;  // keys of a wavefront in one bin from which they are counted by ballots
 constexpr int kCrowd = 2048;        // keys left in a bin from which their range is taken anew
 constexpr int kRank = 256;          // that many keys are ranked against each other instead of binned again
-constexpr int kRowMaxL = 65536;
+// One workgroup per row against the sliced kernels, which take 20 to 45 us, by the number of tokens and not by the scores (selection alone,
+// softmax-like, sliced / one launch): 32768 tokens x 1 row 21.0 / 16.7, x 32 rows 28.5 / 17.9; 49152 x 1 22.5 / 23.0, x 8 23.6 / 23.8,
+// x 16 28.5 / 23.9, x 64 41.8 / 25.4; in the layer 40000 x 8 110.0 / 114.3, x 16 146.3 / 140.0.  Beyond 49152 the 64 keys per lane no longer
+// fit the registers (17 to 30 spill; 8 with 48 keys): 65536 x 8 25.0 / 30.9, x 28 33.5 / 32.7 and in the layer 240 / 240, x 64 43.4 / 33.1.
+inline int row_max_tokens(int rows) { return rows > 32 ? 65536 : rows > 8 ? 49152 : 32768; }
 // A row's workgroup can sum the g heads of its group while it loads them, but one CU then reads g rows, a head at a
 // time (and in the layer every part of the row does).  Beyond that many extra scores the chip-wide sum in a launch of
 // its own is faster, us without / with that launch: (g - 1) L = 24576 (4 x 8192) 9.7 / 11.4, 57344 (8 x 8192) 10.5 / 11.6 (whole layer
@@ -712,7 +716,7 @@ hipError_t launch_select(const Dims& dm, const float* scores, int k_keep, int32_
   a.k_dev = k_dev; a.k_stride = k_keep; a.rows_per_b = rows / dm.B;
   a.slice = slice_for(dm);
   int g = dm.group_mode ? dm.Hq / dm.Hkv : 1;
-  const bool one_launch = dm.L <= kRowMaxL;
+  const bool one_launch = dm.L <= row_max_tokens(rows);
   if (g > 1 && (!one_launch || (long long)(g - 1) * dm.L > kInlineSum)) {
     float* gs = (float*)((char*)a.slices + align256((size_t)rows * n_slices(dm) * sizeof(SliceWs)));
     const long long n = (long long)rows * dm.L;

@@ -233,6 +233,17 @@ def test_select_crowded_bins(tsa, L):
         assert np.array_equal(idx, widx) and np.array_equal(inv, winv), (L, k)
 
 
+@pytest.mark.parametrize("rows,L", [(8, 32768), (8, 32769), (9, 32769), (9, 36865), (9, 49152), (9, 49153), (32, 49153), (33, 49153), (33, 65536),
+                                    (33, 65537)])
+def test_select_row_count_lines(tsa, rows, L):
+    """Both sides of the lines of length and number of rows where the selection passes from one launch to the sliced kernels."""
+    s = np.exp(1.5 * _rng(940 + rows + L).standard_normal((1, rows, L))).astype(np.float32)
+    s[0, ::3, : L // 2] = 0.0
+    idx, inv = _run_select(tsa, s, L // 3, force_first=4, force_last=16)
+    widx, winv = orc.select(s, L // 3, 4, 16)
+    assert np.array_equal(idx, widx) and np.array_equal(inv, winv)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,L", [(1, 6, 2, 32768), (1, 6, 2, 32769), (2, 4, 1, 21845), (2, 4, 1, 21846), (1, 16, 2, 9362),
                                         (1, 16, 2, 9363), (1, 32, 1, 700), (1, 32, 1, 40000), (1, 4, 2, 65536), (1, 28, 4, 65537)])
 def test_select_group_sums(tsa, B, Hq, Hkv, L):
@@ -588,10 +599,11 @@ def test_fused_path_equals_the_separate_calls(tsa, attend_form, B, Hq, Hkv, L, d
 @pytest.mark.parametrize("B,Hq,Hkv,L,d,k,group_mode", [
     (1, 1, 1, 70, 64, 64, 0), (1, 1, 1, 5000, 128, 1, 0), (1, 7, 7, 4097, 64, 65, 0), (2, 50, 10, 600, 128, 129, 0),
     (4, 32, 32, 300, 64, 300, 0), (3, 43, 43, 200, 64, 63, 0), (1, 8, 2, 8193, 128, 1000, 1), (1, 16, 1, 5000, 64, 700, 1),
+    (1, 2, 2, 33000, 64, 4000, 0), (1, 9, 9, 40000, 64, 3001, 0), (1, 33, 33, 50000, 64, 130, 0),
 ])
 def test_selection_with_v_tiles(tsa, B, Hq, Hkv, L, d, k, group_mode):
-    """The selection that also gathers V (up to 128 rows: several workgroups per row; above: two launches), against
-    the separate calls bit for bit: ragged last tiles, more workgroups than tiles, 128 and 129 rows; and the tiles
+    """The selection that also gathers V (up to 128 rows: several workgroups per row; more rows, and few long ones: the gather
+    is a launch of its own), against the separate calls bit for bit: ragged last tiles, more workgroups than tiles, 128 and 129 rows; and the tiles
     of the separate call against torch's gather and transpose."""
     r = _rng(970 + L + k)
     Q, K, V = (gu.to_dev(gu.rand_bits(r, (B, h, L, d))) for h in (Hq, Hkv, Hkv))
