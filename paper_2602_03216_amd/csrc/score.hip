@@ -591,12 +591,15 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
       lse_s[i] = x;
     }
     __syncthreads();
-    // ... of the queries this lane sees as accumulator rows
+    // ... of the queries this lane sees as accumulator rows.  (One address and constant offsets here, and constants in the
+    // comparisons of the masked tiles below: formed per row, the indices lived in 39 registers across the rounds, and 6 to 11
+    // others spilled; 8 KV heads of 16384 tokens, one query head each, whole scoring: 26.4 -> 24.3 us.)
+    const float* my_lse = lse_s + role.hslot * QP + 4 * hi;
     float lse[NQT][16];
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) lse[qt][r] = lse_s[role.hslot * QP + 32 * qt + c_row(r, hi)];
+      for (int r = 0; r < 16; ++r) lse[qt][r] = my_lse[32 * qt + c_row(r, 0)];
     UnitPipe<D, NQT, SPT, false> pp;
     pp.fbase = fbase;
     pp.first_sub = first_sub;
@@ -635,7 +638,7 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
             const int mid = (lo_i + hi_i) >> 1;
             if (qpos_s[mid] < tk) lo_i = mid + 1; else hi_i = mid;
           }
-          n_hidden = lo_i;
+          n_hidden = lo_i - 4 * hi;                        // (accumulator row r of this lane is query c_row(r, 0) + 4 hi)
         }
         float colsum = 0.f;
 #pragma unroll
@@ -646,7 +649,7 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             float p = fast_exp2(sc[r] * a.c - lse[qt][r]);
-            if (32 * qt + c_row(r, hi) < n_hidden) p = 0.f;
+            if (32 * qt + c_row(r, 0) < n_hidden) p = 0.f;
             colsum += p;
           }
         }
