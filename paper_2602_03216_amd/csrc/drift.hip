@@ -12,15 +12,21 @@ namespace {
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 constexpr int kRowsPerBlock = 64;     // rows per workgroup (4 per wavefront), fewer in short calls
-constexpr int kBatch = 4;             // 16-byte pieces per lane and tensor in one request
 
-// What it needs is bytes in flight: 256 CUs reach the HBM rate with about 64 KiB requested per CU.  Sixteen
-// wavefronts per workgroup with two batches of eight loads each (the next batch is requested before the sums of the
-// current one, across row ends) keep at least twice that requested.  A row goes through a buffer descriptor of its own
+// What it needs is bytes in flight: 256 CUs reach the HBM rate with about 64 KiB requested per CU.  Thirty-two
+// wavefronts per CU (two workgroups) with two batches each (the next batch is requested before the sums of the
+// current one, across row ends) keep at least that requested.  A row goes through a buffer descriptor of its own
 // length, so the lanes past its end read zeros and add nothing.
 // Both kernels, 16384 rows x 4096 from HBM: 91.5 us (2.9 TB/s, four wavefronts per CU, one pair of loads in flight
 // each) -> 48.9 us (5.5 TB/s; 4 us of it the last kernel).
-__global__ __launch_bounds__(kThreads) void drift_rows_kernel(const u32x4* __restrict__ hin, const u32x4* __restrict__ hout,
+// kBatch = 16-byte pieces per lane and tensor in one request: 1 for rows of up to 512 values, whose batch is one row,
+// 2 for wider ones.  Narrow rows pay for every piece they do not have (and for the wavefronts that the registers of more pieces keep
+// out), us with 1 / 2 / 4 pieces (4: one workgroup per CU): 65536 x 64 17.2 / 19.7 / 33.6, x 512 24.0 / 24.6 / 35.4, x 1024 43.3 / 42.8 / 47.8,
+// 300000 x 64 61 / 72 / 141, 16384 x 4096 (in the memory-side cache) 40.2 / 40.8 / 40.9, 20000 x 3584 53.6 / 52.5 / 54.1.
+constexpr int kNarrow = 512;
+
+template <int kBatch>
+__global__ __launch_bounds__(kThreads, 8) void drift_rows_kernel(const u32x4* __restrict__ hin, const u32x4* __restrict__ hout,
                                                               long long n_tokens, int rows_per_block, int width, float eps,
                                                               double* partial) {
   __shared__ double wsum[kWaves];
@@ -114,7 +120,8 @@ hipError_t launch_drift(const void* h_in, const void* h_out, long long n_tokens,
   const long long slots = (long long)(drift_ws_bytes(n_tokens) / sizeof(double));
   const int rows = (int)((n_tokens + slots - 1) / slots);
   const int blocks = (int)((n_tokens + rows - 1) / rows);
-  drift_rows_kernel<<<blocks, kThreads, 0, st>>>((const u32x4*)h_in, (const u32x4*)h_out, n_tokens, rows, width, eps, (double*)ws);
+  auto* kernel = width <= kNarrow ? drift_rows_kernel<1> : drift_rows_kernel<2>;
+  kernel<<<blocks, kThreads, 0, st>>>((const u32x4*)h_in, (const u32x4*)h_out, n_tokens, rows, width, eps, (double*)ws);
   drift_final_kernel<<<1, 256, 0, st>>>((const double*)ws, blocks, n_tokens, out);
   return hipGetLastError();
 }

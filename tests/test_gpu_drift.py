@@ -35,7 +35,8 @@ def test_layer_drift(tsa, n_tokens, width, eps):
     assert out.item() == 0.0
 
 
-@pytest.mark.parametrize("n_tokens,width", [(33, 2040), (63, 2048), (2049, 2056), (2100, 24)])
+@pytest.mark.parametrize("n_tokens,width", [(33, 2040), (63, 2048), (2049, 2056), (2100, 24), (2500, 504), (70, 512), (2049, 520),
+                                            (100, 1024), (1, 1032), (65, 8)])
 def test_layer_drift_edges(tsa, n_tokens, width):
     """Rows that end just before, at and after a batch of loads; row counts around the shares of the workgroups (32
     shares at least, 64 rows each at most).  fp32 sums of `width` squares: relative 2e-6 as above."""
