@@ -2,8 +2,8 @@
 // operation on Q^, K^, V^ with cost O(L'^2 d)), also used unchanged as the dense baseline.
 //
 // Flash-style: one workgroup owns 256 query rows (8 wavefronts x 32 rows, two wavefronts per
-// SIMD), streams 64-key tiles through LDS (K in a ring of five half tiles, V in a ring of two tiles, one
-// barrier per tile; with four wavefronts 128 rows), keeps the running max / sum and the output accumulator in registers
+// SIMD; a second form: four wavefronts, 128 rows), streams 64-key tiles through LDS (K in a ring of three tiles, with
+// four wavefronts of five half tiles, V in a ring of two tiles, one barrier per tile), keeps the running max / sum and the output accumulator in registers
 // (online softmax) and never materialises the score matrix.
 //
 // Both products run on v_mfma_f32_32x32x16_bf16 in the TRANSPOSED orientation:
@@ -25,7 +25,7 @@
 // score, in fp32, in place, next to MFMAs that have little other vector work beside them), so the
 // blocks with the exponentials apply exp2 to the half tile as it is; a raise of m in between shifts the
 // waiting half tile by the same amount.
-// Very short compacted sets (up to 2000 tokens at 32 heads) take the 128-row form of attend_split.hip
+// Very short compacted sets (up to 1792 tokens at 32 heads) take the 128-row form of attend_split.hip
 // instead (use_split_form below).
 // The template also holds the layout with 64 rows per wavefront (QS = 2: four wavefronts, one
 // per SIMD, every LDS fragment feeds two MFMAs); it measures slower and is not instantiated
@@ -43,7 +43,7 @@ namespace {
 // the SIMD's issue slots (a lone wavefront issues one vector instruction every ~8 clocks, two
 // together one every ~5) at the price of one LDS fragment per MFMA.  NW = 8: 256 rows, the two wavefronts of a SIMD
 // belong to one workgroup.  NW = 4: 128 rows; the LDS holds two such workgroups (2 x 80384 bytes of 160 KiB, with K
-// in a ring of five half tiles instead of three tiles), three at d = 64 (168 VGPRs: the fused forms spill one to six), which wait
+// in a ring of five half tiles instead of three tiles), three at d = 64 (168 VGPRs: the fused forms spill 8, with lists 13), which wait
 // at their own barriers and start and end one under the other; every K / V tile is staged for half as many rows.
 // Which one runs, and what both measured: use_pair_form below.
 // LISTS: the launch has a block list.  The plain causal form is a kernel of its own: the look-ups of the tile
@@ -615,17 +615,26 @@ double chain_ratio(const AttendArgs& a) {
 // wavefront.  us of the fused launch, split / four wavefronts / 256 rows: 32 heads, d = 128, 901 rows 26.3 / 28 / 35.4
 // (ratio 3.2); 8 heads x 8192 160 / 190 / 208 (1.94); 4 x 16384 285 / 348 / 366 (1.97); 32 x 2048 56.7 / 56.3 / 62.5
 // (1.78); 16 x 5000 142 / 132 / 136 (1.52).  d = 64: 8 x 8000 112 / 125 / 169 (1.94), 32 x 2000 42.5 / 40.5 / 49 (1.78).
+// (Between 1.7 and 1.8 tsa_attend on compacted tensors would gain 2 to 4 % from it, 12 x 6000 134.6 / 137.0, and tsa_forward lose up
+// to 7 %; one rule for both keeps their results the same bit for bit.)
+// Under a block list a window bounds the chains, so that the ratio says little: the form pays only while all of its
+// workgroups, one per CU, run at once, and not with blocks of 64, where a workgroup of four wavefronts walks shorter lists.
+// d = 128, plain, split / four wavefronts / 256 rows: 4 heads x 8192 rows (256 workgroups), blocks of 128 39.6 / 39.8 / 51.6,
+// of 256 54.9 / 58.7 / 70.9, of 64 35.3 / 34.2 / 44.6; 8 x 8192 (512), blocks of 128 74.2 / 61.2 / 63.3, of 256 108.7 / 93.0 / 88.4;
+// 12 x 4096 (384), blocks of 128 63.3 / 47.2 / 49.7, of 256 72.2 / 64.2 / 69.5.
 bool use_split_form(const AttendArgs& a) {
   if (g_attend_form) return g_attend_form == 2;
+  if (a.block_list && (a.block < 128 || (long long)a.BH * ((a.Lc + 127) / 128) > 256)) return false;
   return chain_ratio(a) >= 1.8;
 }
 
 // Four wavefronts per workgroup (two or three workgroups per CU) against 256 rows, us of the fused launch:
 //   d = 64 (three wavefronts per SIMD instead of two): 32 heads x 4096 rows 91.9 / 104.7, x 8192 328 / 372, x 16384
-//     1209 / 1384, sink + window lists 28 x 16384 575 / 662 (blocks of 256), 598 / 714 (128): always.
+//     1209 / 1384, sink + window lists 28 x 16384 575 / 662 (blocks of 256), 598 / 714 (128): always.  (tsa_attend loses 3 to
+//     5 % to a second, nearly empty round just above 768 workgroups: 12 x 9000 169 / 162; tsa_forward there 172 / 189.)
 //   d = 128, block lists with blocks of 64 or 128: a workgroup walks the lists of one or two row blocks instead of the
-//     union of up to four: 28 x 16384 598 / 696 (blocks of 64), 958 / 997 (128), 28 x 4096 89 / 113 (64); not with blocks of 256
-//     (955 / 940).
+//     union of up to four: 28 x 16384 598 / 696 (blocks of 64), 958 / 997 (128), 28 x 4096 89 / 113 (64); with blocks of 256
+//     (955 / 940) only for few heads, by the ratio below (plain 12 x 4096 64.2 / 69.5, 8 x 8192 93.0 / 88.4).
 //   d = 128, plain: a start and an end hidden under the other workgroup are worth more than the second staging of
 //     the tiles as long as the chains are short: 128 heads x 600 rows 45.4 / 56.0, 96 x 1000 50 / 55, 64 x 1500 56 / 59,
 //     32 x 2500 71.5 / 76.2, 96 x 2400 171 / 187, 40 x 3000 112 / 114, 64 x 3300 198 / 200; 32 x 3500 115 / 113,

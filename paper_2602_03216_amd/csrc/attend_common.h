@@ -1,6 +1,6 @@
-// Pieces shared by the two forms of the attention kernel (attend.hip: 256 query rows per workgroup;
-// attend_split.hip: 128 query rows per workgroup with the keys of every tile split over two groups of
-// wavefronts): launch arguments, the tile generator that walks plain causal tiles or a block list,
+// Pieces shared by the three forms of the attention kernel (attend.hip: 256 query rows and eight wavefronts per
+// workgroup, or 128 rows and four; attend_split.hip: 128 query rows per workgroup with the keys of every tile split over
+// two groups of wavefronts): launch arguments, the tile generator that walks plain causal tiles or a block list,
 // the half-tile products on v_mfma_f32_32x32x16_bf16 and the online-softmax steps.
 #pragma once
 

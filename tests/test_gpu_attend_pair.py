@@ -39,3 +39,31 @@ def test_block_lists(tsa, pair, Lc, window, Bs):
     (3, 2, 1, 777, 64, 200, 0, True), (1, 4, 2, 4001, 64, 130, 0, False), (2, 4, 2, 520, 128, 1, 0, False)])
 def test_gather_and_scatter(tsa, pair, B, Hq, Hkv, L, d, k, group_mode, with_blocks):
     par.test_fused_path_equals_the_separate_calls(tsa, pair, B, Hq, Hkv, L, d, k, group_mode, with_blocks)
+
+
+@pytest.mark.parametrize("Hq,Hkv,Lc,d,window,Bs,form", [
+    (4, 4, 8192, 128, 512, 128, 2),      # 256 workgroups of 128 rows: all at once, split keys
+    (4, 2, 8193, 64, 512, 128, 3),       # one more tile of rows per head: two rounds, four wavefronts
+    (12, 4, 4096, 64, 1024, 256, 3),     # 384 workgroups
+    (2, 2, 4096, 128, 512, 64, 3),       # blocks of 64: four wavefronts whatever their number
+    (2, 2, 4096, 64, 512, 256, 2),
+])
+def test_form_taken_under_a_block_list(tsa, Hq, Hkv, Lc, d, window, Bs, form):
+    """Which form a launch with a block list takes, seen in the bits of its output: the split form merges two sums per row at
+    the end and rounds differently (the two others often agree in every bit)."""
+    r = par._rng(1500 + Lc)
+    Q, K, V = (par.gu.to_dev(par.gu.rand_bits(r, (1, h, Lc, d))) for h in (Hq, Hkv, Hkv))
+    bl = par.orc.lambda_block_list(Lc, Bs, window, 1)
+    desc = tsa.make_desc(1, Hq, Hkv, Lc, d, 1)
+    ws = tsa.alloc_attend_workspace(desc, Lc, Hkv, par.gu.DEV)
+    out = {}
+    try:
+        for f in (0, 2, 3):
+            tsa.tsa_bench_set_attend_form(f)
+            out[f] = par.torch.empty_like(Q)
+            tsa.tsa_attend(desc, Q, K, V, Lc, Hkv, out[f], ws, block_list=par.torch.from_numpy(bl).to(par.gu.DEV), block_size=Bs,
+                           max_blocks_per_row=bl.shape[1])
+    finally:
+        tsa.tsa_bench_set_attend_form(0)
+    assert not par.torch.equal(out[2], out[3])
+    assert par.torch.equal(out[0], out[form])
