@@ -1,6 +1,6 @@
-"""The attention kernel with four wavefronts (128 query rows) per workgroup, pinned, on the problems that its other
-forms are checked on: row counts around the edges of a tile, a half tile and a workgroup, running maxima raised inside the
-pipelined loop, block lists of every block size (256: two workgroups share a row block), gather and scatter."""
+"""The attention kernel with four wavefronts (128 query rows) per workgroup, pinned, at the edges of its own tiles: row
+counts around the edges of a tile, a half tile and a workgroup, running maxima raised inside the pipelined loop, block
+lists of every block size (256: two workgroups share a row block), gather and scatter."""
 import pytest
 
 from tests import test_gpu_parity as par

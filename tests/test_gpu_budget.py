@@ -101,11 +101,11 @@ def test_budget_on_scored_workload_then_forward(tsa):
 
 
 def _dynamic_case(tsa, B, Hq, Hkv, L, d, tau_cov, k_max, group_mode, seed, window=0):
-    """Runs _dynamic_case_form with the form of the attention kernel pinned to each of the two (the layer
+    """Runs _dynamic_case_form with the form of the attention kernel pinned to each of the three (the layer
     with a device-side count sizes its launch for k_max, tsa_forward for the count itself, so left alone
     they may pick different forms) and once with the choice left to the library."""
     try:
-        for form in (1, 2, 0):
+        for form in (1, 2, 3, 0):
             tsa.tsa_bench_set_attend_form(form)
             got = _dynamic_case_form(tsa, B, Hq, Hkv, L, d, tau_cov, k_max, group_mode, seed, window, form)
     finally:

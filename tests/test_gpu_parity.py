@@ -19,11 +19,11 @@ def tsa():
     return binding
 
 
-@pytest.fixture(params=[1, 2], ids=["rows256", "rows128_split"])
+@pytest.fixture(params=[1, 2, 3], ids=["rows256", "rows128_split", "rows128"])
 def attend_form(request, tsa):
-    """The attention kernel has two forms (256 query rows per workgroup; 128 rows with the keys of a tile
-    split over two groups of wavefronts) and picks one per launch from the problem size.  Tests that
-    take this fixture run once with each form pinned, so both meet the oracle on every shape."""
+    """The attention kernel has three forms (256 query rows per workgroup; 128 rows with the keys of a tile
+    split over two groups of wavefronts; 128 rows and four wavefronts) and picks one per launch from the problem size.
+    Tests that take this fixture run once with each form pinned, so all meet the oracle on every shape."""
     tsa.tsa_bench_set_attend_form(request.param)
     yield request.param
     tsa.tsa_bench_set_attend_form(0)
