@@ -46,8 +46,8 @@ def _ws(tsa, desc, k):
     (1, 2, 2, 100, 64, 100),      # window = whole sequence
     (1, 2, 1, 33, 128, 1),        # single query
     (1, 2, 2, 5000, 128, 128),    # widest window
-    (1, 8, 2, 2300, 128, 64),     # four heads per KV head (one per wavefront), several tiles per workgroup, ragged tail
-    (1, 7, 1, 1500, 64, 40),      # seven heads per KV head: two rounds over the staged tiles, the second partly idle
+    (1, 8, 2, 2300, 128, 64),     # four heads per KV head, each in workgroups of its own, ragged tail
+    (1, 7, 1, 1500, 64, 40),      # seven heads per KV head
     (1, 4, 1, 700, 128, 128),     # four heads per KV head with the widest window
     (1, 7, 1, 1030, 128, 64),     # last chunk holds only window keys
 ])
@@ -65,11 +65,28 @@ def test_score(tsa, B, Hq, Hkv, L, d, Lq):
 
 @pytest.mark.parametrize("Hq,Hkv,L,d,Lq", [
     (2, 2, 8192, 64, 33), (4, 1, 8193, 64, 64),        # 32 and 33 partials per query: the last folded inside pass 2, the first that is not
-    (4, 1, 4096, 128, 16), (5, 1, 257, 128, 64),       # 16 partials (one batch of the fold); heads dealt over workgroups, the last one's idle
+    (4, 1, 4096, 128, 16), (5, 1, 257, 128, 64),       # 16 partials (one batch of the fold); two chunks, the last one a single key
     (16, 16, 4500, 64, 100),                           # chunks above the smallest, one workgroup per CU
 ])
 def test_score_split_and_fold_edges(tsa, Hq, Hkv, L, d, Lq):
     test_score(tsa, 1, Hq, Hkv, L, d, Lq)
+
+
+# Workgroups that serve several heads: chunks x KV heads must fill half of the CUs.  (Heads at a time, rounds, workgroups that share the rounds):
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,Lq", [
+    (1, 32, 8, 3001, 128, 64),    # (2, 2, 2)
+    (1, 12, 4, 9000, 64, 20),     # (2, 2, 2), the last head's partner idle; one block of 32 queries
+    (1, 6, 2, 17000, 128, 64),    # (2, 2, 2), idle partner; 67 partials, log-sum-exps from the launch of their own
+    (1, 24, 8, 4100, 64, 100),    # (2, 2, 1): both rounds in one workgroup, idle partner in the second
+    (1, 28, 4, 8192, 64, 64),     # (4, 2, 2), one of four idle; 32 partials
+    (1, 10, 2, 17001, 128, 64),   # (4, 2, 2), three of four idle; 67 partials
+    (1, 16, 4, 9000, 128, 20),    # (4, 1, 1), one block of 32 queries
+    (1, 32, 8, 5000, 64, 30),     # (4, 1, 1)
+    (2, 32, 8, 6001, 128, 100),   # (4, 1, 1), widest query block
+    (1, 16, 4, 9001, 64, 128),    # (4, 1, 1)
+])
+def test_score_several_heads_per_workgroup(tsa, B, Hq, Hkv, L, d, Lq):
+    test_score(tsa, B, Hq, Hkv, L, d, Lq)
 
 
 def test_score_custom_scale_and_determinism(tsa):
@@ -135,7 +152,7 @@ def test_select_exact_ties(tsa):
         widx, winv = orc.select(s, k)
         assert np.array_equal(idx, widx) and np.array_equal(inv, winv)
     # rows cut into several slices (of 2048 and of 4096 tokens), ragged last slice, ties across slices
-    for rows, L, k, levels in ((2, 40001, 9000, 3), (16, 70000, 20000, 5)):
+    for rows, L, k, levels in ((2, 40001, 9000, 3), (16, 70000, 20000, 5), (3, 100001, 50000, 2)):
         s = r.integers(0, levels, size=(1, rows, L)).astype(np.float32) * 0.25
         idx, inv = _run_select(tsa, s, k)
         widx, winv = orc.select(s, k)
