@@ -26,6 +26,8 @@ def _rng(seed):
     (2, 2, 2, 1037, 64, 17),
     (1, 8, 2, 5000, 128, 128),
     (1, 2, 1, 300, 128, 1),
+    (1, 12, 4, 9000, 128, 20),     # two heads per workgroup, one slot idle
+    (1, 28, 4, 8192, 64, 64),      # four heads per workgroup, one slot idle
 ])
 def test_random_query_scoring(tsa, B, Hq, Hkv, L, d, n):
     r = _rng(2000 + L)

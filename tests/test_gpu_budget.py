@@ -163,6 +163,8 @@ def _dynamic_case_form(tsa, B, Hq, Hkv, L, d, tau_cov, k_max, group_mode, seed, 
     (2, 4, 2, 2048, 128, 0.3, 600, 0),         # the budget asks for more than k_max: clamped
     (1, 2, 2, 700, 128, 0.0, 700, 0),          # tau_cov = 0: nothing is dropped
     (1, 2, 1, 900, 64, 1.0, 900, 0),           # tau_cov = 1: a single token is kept
+    (2, 2, 1, 66001, 64, 0.3, 30000, 0),       # the sliced selection kernels with two counts of their own
+    (2, 4, 2, 40001, 64, 0.4, 9000, 1),        # ... with group sums, clamped
 ])
 def test_forward_dynamic_equals_budget_then_forward(tsa, B, Hq, Hkv, L, d, tau_cov, k_max, group_mode):
     window = -group_mode if group_mode < 0 else 0

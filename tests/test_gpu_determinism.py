@@ -81,8 +81,10 @@ def _ws(nbytes, fill):
 CASES = [
     # B, Hq, Hkv, L, d, Lq, k, group_mode, pool_w
     (2, 4, 2, 3000, 128, 64, 700, 0, 1),
-    (1, 6, 2, 20011, 128, 64, 5000, 1, 3),      # rows longer than 16384: the sliced selection kernels; pooled scores
+    (1, 6, 2, 20011, 128, 64, 5000, 1, 3),      # selection in one launch that sums the three heads of a group; pooled scores
     (3, 2, 2, 777, 64, 17, 777, 0, 1),
+    (1, 6, 2, 70011, 64, 64, 3001, 1, 1),       # the sliced selection kernels and the group sums in the workspace
+    (2, 2, 2, 40003, 64, 33, 2000, 0, 1),       # the sliced kernels, two batch entries with counts of their own
 ]
 
 

@@ -42,7 +42,7 @@ def _both(tsa, s_np, k, **kw):
 
 def test_static_scratch_selection_equals_the_workspace_form_on_two_calls_in_a_row(tsa):
     r = np.random.Generator(np.random.PCG64(77))
-    # first call: long rows (the sliced kernels), many ties; second call, smaller: short rows (one launch per row)
+    # rows of at most 49152 tokens, as many as here, are selected in one launch and leave the scratch alone; many ties
     s1 = (r.integers(0, 50, size=(2, 6, 40001)) / 64.0).astype(np.float32)
     idx, inv = _both(tsa, s1, 9000)
     widx, winv = orc.select(s1.astype(np.float64), 9000)
@@ -51,12 +51,29 @@ def test_static_scratch_selection_equals_the_workspace_form_on_two_calls_in_a_ro
     idx, inv = _both(tsa, s2, 400, force_first=2, force_last=3)
     widx, winv = orc.select(s2.astype(np.float64), 400, 2, 3)
     assert np.array_equal(idx, widx) and np.array_equal(inv, winv)
-    # group mode (the group sums live in the scratch too), then a long row again after the short ones
+    # group mode with the sums of the heads inside the launch, then long rows again after the short ones
     s3 = (np.floor(r.random((1, 8, 20000)) * 4096) / 4096).astype(np.float32)
     idx, inv = _both(tsa, s3, 700, Hkv=2, group_mode=1)
     widx, winv = orc.select(orc.group_scores(s3.astype(np.float64), 4), 700)
     assert np.array_equal(idx, widx) and np.array_equal(inv, winv)
     _both(tsa, s1[:1, :2, :17000].copy(), 17000)
+
+
+def test_static_scratch_is_shared_by_calls_in_a_row(tsa):
+    """Calls that use the scratch (the sliced kernels: few rows of more than 32768 tokens, any of more than 65536; group sums),
+    each smaller than the one before it, so that what the larger one left is all around the smaller one's part."""
+    r = np.random.Generator(np.random.PCG64(78))
+    s1 = (r.integers(0, 50, size=(2, 6, 90001)) / 64.0).astype(np.float32)
+    s2 = (np.floor(r.random((1, 8, 70001)) * 4096) / 4096).astype(np.float32)
+    s3 = r.random((1, 2, 40001)).astype(np.float32)
+    s4 = (np.floor(r.random((1, 32, 3000)) * 4096) / 4096).astype(np.float32)      # 31 x 3000 further scores: summed into the scratch
+    for rep in range(2):
+        for s, k, kw in ((s1, 30000, {}), (s2, 700, dict(Hkv=2, group_mode=1)), (s3, 39000, dict(force_first=2, force_last=3)),
+                         (s4, 100, dict(Hkv=1, group_mode=1))):
+            idx, inv = _both(tsa, s, k, **kw)
+            sel = orc.group_scores(s.astype(np.float64), s.shape[1] // kw["Hkv"]) if "Hkv" in kw else s.astype(np.float64)
+            widx, winv = orc.select(sel, k, kw.get("force_first", 0), kw.get("force_last", 0))
+            assert np.array_equal(idx, widx) and np.array_equal(inv, winv), (rep, s.shape)
 
 
 def test_static_scratch_selection_rejects_what_does_not_fit(tsa):
