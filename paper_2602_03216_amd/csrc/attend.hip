@@ -30,6 +30,8 @@
 // The template also holds the layout with 64 rows per wavefront (QS = 2: four wavefronts, one
 // per SIMD, every LDS fragment feeds two MFMAs); it measures slower and is not instantiated
 // by default.
+#include <algorithm>
+
 #include "attend_common.h"
 
 namespace tsa {
@@ -610,13 +612,15 @@ double chain_ratio(const AttendArgs& a) {
   return 512.0 / (double)(a.BH * (nq + 1));
 }
 
-// The split form pays for very short compacted sets, where the longest chain and not the chip's throughput is the
-// launch: it halves that chain, and stages every K / V tile for half as many rows and half as many keys per
-// wavefront.  us of the fused launch, split / four wavefronts / 256 rows: 32 heads, d = 128, 901 rows 26.3 / 28 / 35.4
-// (ratio 3.2); 8 heads x 8192 160 / 190 / 208 (1.94); 4 x 16384 285 / 348 / 366 (1.97); 32 x 2048 56.7 / 56.3 / 62.5
-// (1.78); 16 x 5000 142 / 132 / 136 (1.52).  d = 64: 8 x 8000 112 / 125 / 169 (1.94), 32 x 2000 42.5 / 40.5 / 49 (1.78).
-// (Between 1.7 and 1.8 tsa_attend on compacted tensors would gain 2 to 4 % from it, 12 x 6000 134.6 / 137.0, and tsa_forward lose up
-// to 7 %; one rule for both keeps their results the same bit for bit.)
+// The split form pays where the longest chain and not the chip's throughput is the launch: it halves that chain, and stages
+// every K / V tile for half as many rows and half as many keys per wavefront.  The ratio from which it does rises with
+// the number of heads: the more heads, the fewer rows at the same ratio, and the more the start and the merge of its
+// workgroups weigh.  us of the launch, fused, d = 128, split / four wavefronts / 256 rows: 4 heads x 18894 rows (ratio 1.71) 413 / 434 / 446,
+// x 20942 (1.54) 505 / 505 / 515; 8 x 9422 (1.68) 221 / 223 / 232, x 9934 (1.60) 243 / 241 / 249; 16 x 4046 (1.88) 87 / 98 / 105, x 4302 (1.78)
+// 108 / 106 / 112; 20 x 3278 (1.83) 87.7 / 81.5 / 87.8; 32 x 901 (3.2) 26.3 / 28 / 35.4, x 1742 (2.0) 48.4 / 47.2 / 53.5 (at d = 64
+// 37.2 / 38.4 / 44.3, plain x 1792 31.7 / 33.6: hence 2.0 up to 32 heads); 40 x 1250 (2.13)
+// 40.2 / 36.4 / 42.1; 64 x 738 (2.0) 33.0 / 26.9 / 31.7.  tsa_attend on compacted tensors crosses at the same ratios, at d = 64 0.1 to 0.15 lower
+// and the fused launch as much higher; one rule for all keeps tsa_forward and the separate calls the same bit for bit.
 // Under a block list a window bounds the chains, so that the ratio says little: the form pays only while all of its
 // workgroups, one per CU, run at once, and not with blocks of 64, where a workgroup of four wavefronts walks shorter lists.
 // d = 128, plain, split / four wavefronts / 256 rows: 4 heads x 8192 rows (256 workgroups), blocks of 128 39.6 / 39.8 / 51.6,
@@ -624,8 +628,9 @@ double chain_ratio(const AttendArgs& a) {
 // 12 x 4096 (384), blocks of 128 63.3 / 47.2 / 49.7, of 256 72.2 / 64.2 / 69.5.
 bool use_split_form(const AttendArgs& a) {
   if (g_attend_form) return g_attend_form == 2;
-  if (a.block_list && (a.block < 128 || (long long)a.BH * ((a.Lc + 127) / 128) > 256)) return false;
-  return chain_ratio(a) >= 1.8;
+  if (a.block_list) return a.block >= 128 && (long long)a.BH * ((a.Lc + 127) / 128) <= 256 && chain_ratio(a) >= 1.8;
+  const double line = 1.5 + 0.0175 * a.BH;
+  return chain_ratio(a) >= (a.BH <= 32 ? std::min(line, 2.0) : line);
 }
 
 // Four wavefronts per workgroup (two or three workgroups per CU) against 256 rows, us of the fused launch:

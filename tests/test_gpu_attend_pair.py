@@ -67,3 +67,29 @@ def test_form_taken_under_a_block_list(tsa, Hq, Hkv, Lc, d, window, Bs, form):
         tsa.tsa_bench_set_attend_form(0)
     assert not par.torch.equal(out[2], out[3])
     assert par.torch.equal(out[0], out[form])
+
+
+@pytest.mark.parametrize("Hq,Hkv,Lc,d,form", [(4, 4, 18900, 128, 2), (4, 2, 22600, 64, 3), (16, 2, 4090, 64, 2), (16, 2, 4300, 64, 3), (40, 8, 1300, 128, 3),
+                                              (40, 8, 1000, 64, 2), (32, 8, 1792, 64, 2), (32, 8, 1793, 64, 3)])
+def test_form_taken_without_a_list(tsa, Hq, Hkv, Lc, d, form):
+    """Both sides of the line between the split form and four wavefronts, which rises with the number of heads; tsa_forward's
+    launch takes the same side."""
+    r = par._rng(1600 + Lc)
+    torch = par.torch
+    Q, K, V = (torch.from_numpy(r.standard_normal((1, h, Lc, d), dtype="float32")).to(par.gu.DEV).bfloat16() for h in (Hq, Hkv, Hkv))
+    desc = tsa.make_desc(1, Hq, Hkv, Lc, d, 1)
+    ws = tsa.alloc_attend_workspace(desc, Lc, Hkv, par.gu.DEV)
+    idx = torch.arange(Lc, dtype=torch.int32, device=par.gu.DEV).repeat(1, Hq, 1)
+    Vt = tsa.alloc_attend_workspace(desc, Lc, Hq, par.gu.DEV)
+    tsa.tsa_compress_v_tiles(desc, V, idx, Lc, Vt)
+    out, fused = {}, {}
+    try:
+        for f in (0, 2, 3):
+            tsa.tsa_bench_set_attend_form(f)
+            out[f], fused[f] = torch.empty_like(Q), torch.empty_like(Q)
+            tsa.tsa_attend(desc, Q, K, V, Lc, Hkv, out[f], ws)
+            tsa.tsa_attend_fused(desc, Q, K, Vt, idx, idx, Lc, O=fused[f])
+    finally:
+        tsa.tsa_bench_set_attend_form(0)
+    assert not torch.equal(out[2], out[3])
+    assert torch.equal(out[0], out[form]) and torch.equal(fused[0], out[0])
