@@ -647,6 +647,29 @@ def test_selection_with_v_tiles(tsa, B, Hq, Hkv, L, d, k, group_mode):
     assert torch.equal(idx2, idx) and torch.equal(O2, O1)
 
 
+@pytest.mark.parametrize("Hq,Hkv,L,d,k,group_mode", [(4, 2, 5000, 64, 1300, 0), (6, 2, 20000, 64, 4000, 1), (2, 1, 3000, 128, 2950, 0), (12, 12, 40000, 64, 900, 0)])
+def test_selection_with_v_tiles_on_equal_scores(tsa, Hq, Hkv, L, d, k, group_mode):
+    """Zero queries: every token that all scoring queries see has the same score, so the sets are the first tokens, and every
+    workgroup that shares a row has to resolve the ties alike; the V tiles against the separate calls bit for bit."""
+    r = _rng(995 + L)
+    K, V = (gu.to_dev(gu.rand_bits(r, (1, Hkv, L, d))) for _ in range(2))
+    Q = torch.zeros((1, Hq, L, d), dtype=torch.bfloat16, device=gu.DEV)
+    desc = tsa.make_desc(1, Hq, Hkv, L, d, 32, group_mode=group_mode, force_last=5)
+    Hs = Hkv if group_mode else Hq
+    ws = _ws(tsa, desc, k)
+    O1 = torch.full((1, Hq, L, d), 5.0, dtype=torch.bfloat16, device=gu.DEV)
+    O2, idx = torch.full_like(O1, 7.0), torch.zeros((1, Hs, k), dtype=torch.int32, device=gu.DEV)
+    tsa.tsa_forward(desc, Q, K, V, k, O1, ws, idx_out=idx)
+    want = torch.cat([torch.arange(k - 5), torch.arange(L - 5, L)]).int().to(gu.DEV).expand(1, Hs, k)
+    assert torch.equal(idx, want)
+    inv = torch.full((1, Hs, L), -1, dtype=torch.int32, device=gu.DEV)
+    inv.scatter_(2, want.long(), torch.arange(k, dtype=torch.int32, device=gu.DEV).expand(1, Hs, k).contiguous())
+    Vt = tsa.alloc_attend_workspace(desc, k, Hs, gu.DEV)
+    tsa.tsa_compress_v_tiles(desc, V, idx, k, Vt)
+    tsa.tsa_attend_fused(desc, Q, K, Vt, idx, inv, k, O=O2)
+    assert torch.equal(O1, O2)
+
+
 @pytest.mark.parametrize("Hq,Hk,Lc,d,Bs", [(4, 2, 1000, 128, 128), (3, 3, 1500, 64, 128), (2, 1, 2600, 128, 128),
                                            (4, 2, 1100, 128, 64), (2, 2, 1900, 64, 256)])
 def test_attend_per_head_block_lists(tsa, attend_form, Hq, Hk, Lc, d, Bs):
