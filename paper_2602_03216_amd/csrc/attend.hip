@@ -174,7 +174,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
       const int qb = q0 / a.block + j;
       if (j < gen.n_lists && qb < nqb) {
         gen.list[j] = bl + (long long)qb * a.max_blocks;
-        gen.cnt[j] = count_valid(gen.list[j], a.max_blocks, qb);
+        gen.cnt[j] = count_valid(gen.list[j], a.max_blocks, qb, lane);
         if (gen.cnt[j] > 0) gen.cur[j] = gen.list[j][0];
         gen.full |= 1 << j;
         longest_list = max(longest_list, gen.cnt[j]);
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   }
 
   // ---- fused form: the zero rows the tile loop did not get to
-  if (zfill) {
+  auto flush_zero_rows = [&]() {
     // Latency-bound: a batch of look-ups is a memory round trip.  Sixteen rows per thread and batch, the
     // look-ups of the next batch requested before the stores of the current one (so that waiting for them
     // never includes waiting for those stores to be acknowledged).
@@ -560,39 +560,23 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
       for (int j = 0; j < kBatch; ++j) r[j] = rn[j];
       t0 = t1;
     }
-  }
+  };
 
-  // ---- epilogue: normalise, round to bf16, store O[query][d] (a lane holds 4 consecutive d per register quad)
+  // ---- epilogue: normalise, round to bf16, store the rows (RowOut).  The LDS is free: every wavefront is past the
+  // barrier behind the last read of a tile.
+  using Out = RowOut<D, ND, FUSED>;
+  static_assert(NW * Out::kLds <= (KRING * KHALF + 2 * VTILE) * 2, "the rows of all wavefronts fit the tile rings");
+  char* const lds_out = (char*)smem + wave * Out::kLds;
 #pragma unroll
   for (int qs = 0; qs < QS; ++qs) {
-    const int qrow = wrow0 + 32 * qs + lo;
+    const int row0 = wrow0 + 32 * qs;
     const float lt = l[qs] + __shfl_xor(l[qs], 32);
     const float inv_l = lt > 0.f ? 1.0f / lt : 0.f;
-    if (qrow < Lc) {
-      __bf16* orow = a.O ? a.O + (bh * a.Lc + qrow) * D : nullptr;
-      __bf16* frow = nullptr;                       // fused: the token's row of the full-length output
-      __bf16* xrow = nullptr;                       // fused: the token's slice of the residual stream
-      if (FUSED && a.Of) frow = a.Of + a.os.head(b, h) + idx_row[qrow] * a.os.l;
-      if (FUSED && a.X) xrow = a.X + (((long long)b * a.L + idx_row[qrow]) * a.Hq + h) * D;
-#pragma unroll
-      for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          u32x2 w;
-          w[0] = pack_bf16(o[qs][dt][4 * q4 + 0] * inv_l, o[qs][dt][4 * q4 + 1] * inv_l);
-          w[1] = pack_bf16(o[qs][dt][4 * q4 + 2] * inv_l, o[qs][dt][4 * q4 + 3] * inv_l);
-          if (orow) *(u32x2*)(orow + 32 * dt + 8 * q4 + 4 * hi) = w;
-          if (FUSED && frow) *(u32x2*)(frow + 32 * dt + 8 * q4 + 4 * hi) = w;
-          if (FUSED && xrow) {
-            u32x2* px = (u32x2*)(xrow + 32 * dt + 8 * q4 + 4 * hi);
-            u32x2 x = *px;
-            x[0] = add_bf16_pairs(x[0], w[0]);
-            x[1] = add_bf16_pairs(x[1], w[1]);
-            *px = x;
-          }
-        }
-      if (a.lse && hi == 0) a.lse[bh * a.Lc + qrow] = (m[qs] + log2f(lt)) * kLn2;
-    }
+    Out out;
+    out.look_up(idx_row, row0, Lc, lane);
+    out.put(o[qs], inv_l, lds_out, lane);
+    out.store(a, b, h, row0, Lc, 0, lds_out, lane, [&]() { if (zfill && qs == 0) flush_zero_rows(); });
+    if (a.lse && hi == 0 && row0 + lo < Lc) a.lse[bh * a.Lc + row0 + lo] = (m[qs] + log2f(lt)) * kLn2;
   }
 }
 

@@ -21,6 +21,8 @@
 // what an iteration prefetches across its closing barrier was written an iteration earlier.
 #include "attend_common.h"
 
+#include <type_traits>
+
 namespace tsa {
 
 using namespace attend_detail;
@@ -34,7 +36,8 @@ struct Step {
   Tile a, b;                            // the two 64-key tiles of a step; b.k0 < 0: the step has one tile
 };
 
-template <int D, bool FUSED>
+// LISTS: the launch has a block list (a kernel of its own, see attend.hip)
+template <int D, bool FUSED, bool LISTS>
 __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a) {
   constexpr int QS = 1;
   constexpr int kThreads = kThreadsS;
@@ -79,7 +82,7 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   const int koff = 32 * kg;                              // this wavefront's keys inside a 64-key tile
   const int q0 = qt * BMS;
   const int wrow0 = q0 + RW * rg;
-  const int half_bit = (a.block_list && a.block < BMS) ? 1 << ((RW * rg) / a.block) : 1;
+  const int half_bit = (LISTS && a.block < BMS) ? 1 << ((RW * rg) / a.block) : 1;
   const float c = a.c;
   const float c_ = c;
   const float inv_c = 1.0f / c;
@@ -112,25 +115,9 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
     zr = zt < z_hi ? inv_row[zt] : 0;
   };
 
-  // Q^T operand fragments of the wavefront's 32 rows (both key groups hold the same rows)
-  bf16x8 qf[QS][NS];
-  {
-    int qrow_off = (wrow0 + lo) * ROWB;
-    if (FUSED) {
-      const int qr = wrow0 + lo;
-      qrow_off = qr < Lc ? (int)__umul24(idx_row[qr], q_pitch) : a.L * q_pitch;
-    }
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(Qr, qrow_off + 16 * hi + 32 * s, 0, 0);
-      qf[0][s] = __builtin_bit_cast(bf16x8, v);
-    }
-  }
-  __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0), see attend.hip
-
   // ---- key tiles, two per step
   TileGen gen;
-  gen.plain = a.block_list == nullptr;
+  gen.plain = !LISTS;
   gen.plain_i = 0;
   gen.plain_n = (min(q0 + BMS, Lc) + BN - 1) / BN;
   gen.sub = gen.kb = gen.use = 0;
@@ -153,7 +140,7 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
       const int qb = q0 / a.block + j;
       if (j < gen.n_lists && qb < nqb) {
         gen.list[j] = bl + (long long)qb * a.max_blocks;
-        gen.cnt[j] = count_valid(gen.list[j], a.max_blocks, qb);
+        gen.cnt[j] = count_valid(gen.list[j], a.max_blocks, qb, lane);
         if (gen.cnt[j] > 0) gen.cur[j] = gen.list[j][0];
         gen.full |= 1 << j;
         longest_list = max(longest_list, gen.cnt[j]);
@@ -182,32 +169,32 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   u32x4 kreg[2][CH], vreg[2][CH];
   auto row_off = [&](int tok) -> int { return FUSED ? (int)__umul24(tok, k_pitch) : tok * ROWB; };
   // tiles that do not exist are replaced by tile 0 in the look-ups and loads: loaded, never used
-  auto fetch_tok = [&](int j, int k0) {
+  auto fetch_tok = [&](int (&tok)[CH], int k0) {
     k0 = max(k0, 0);
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
-      if (FUSED) ktok[j][i] = __builtin_amdgcn_raw_buffer_load_b32(Ir, (st_row + i * kRowsPerPass) * 4, k0 * 4, 0);
-      else ktok[j][i] = k0 + st_row + i * kRowsPerPass;
+      if (FUSED) tok[i] = __builtin_amdgcn_raw_buffer_load_b32(Ir, (st_row + i * kRowsPerPass) * 4, k0 * 4, 0);
+      else tok[i] = k0 + st_row + i * kRowsPerPass;
     }
   };
-  auto load_k = [&](int j) {
+  auto load_k = [&](const int (&tok)[CH], u32x4 (&reg)[CH]) {
 #pragma unroll
     for (int i = 0; i < CH; ++i)
-      kreg[j][i] = __builtin_amdgcn_raw_buffer_load_b128(Kr, row_off(ktok[j][i]) + 16 * st_col, 0, 0);
+      reg[i] = __builtin_amdgcn_raw_buffer_load_b128(Kr, row_off(tok[i]) + 16 * st_col, 0, 0);
   };
-  auto load_v = [&](int j, int k0) {
+  auto load_v = [&](u32x4 (&reg)[CH], int k0) {
     k0 = max(k0, 0);
 #pragma unroll
     for (int i = 0; i < CH; ++i)
-      vreg[j][i] = __builtin_amdgcn_raw_buffer_load_b128(Vr, gv_off + i * kThreads * 16, k0 * ROWB, 0);
+      reg[i] = __builtin_amdgcn_raw_buffer_load_b128(Vr, gv_off + i * kThreads * 16, k0 * ROWB, 0);
   };
-  auto store_k = [&](__bf16* dst, int j) {
+  auto store_k = [&](__bf16* dst, const u32x4 (&reg)[CH]) {
 #pragma unroll
-    for (int i = 0; i < CH; ++i) *(u32x4*)(&dst[lk_off + i * kRowsPerPass * KS]) = kreg[j][i];
+    for (int i = 0; i < CH; ++i) *(u32x4*)(&dst[lk_off + i * kRowsPerPass * KS]) = reg[i];
   };
-  auto store_v = [&](__bf16* dst, int j) {
+  auto store_v = [&](__bf16* dst, const u32x4 (&reg)[CH]) {
 #pragma unroll
-    for (int i = 0; i < CH; ++i) *(u32x4*)(&dst[lv_off + i * kVRowsPerPass * VS]) = vreg[j][i];
+    for (int i = 0; i < CH; ++i) *(u32x4*)(&dst[lv_off + i * kVRowsPerPass * VS]) = reg[i];
   };
 
   // LDS read bases: the wavefront's 32 keys are rows koff.. of a K tile and columns koff.. of a V^T tile
@@ -246,38 +233,54 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   uint32_t pA[QS][8], pB[QS][8];
   // half tile h of step S: first key and whether this wavefront takes part in it
   auto act = [&](const Tile& t) -> bool { return t.k0 >= 0 && (t.use & half_bit) && t.k0 + koff <= wrow0 + RW - 1; };
-  if (S0.a.k0 >= 0) {
-    fetch_tok(0, S0.a.k0);
-    fetch_tok(1, S0.b.k0);
-    load_k(0);
-    load_k(1);
-    load_v(0, S0.a.k0);
-    load_v(1, S0.b.k0);
-    store_k(kwa, 0);                 // a_0 only serves the first S^T below; the slot is free again after the second barrier
-    store_k(kb0, 1);
-    store_v(va0, 0);
-    store_v(vb0, 1);
-    if (S1.a.k0 >= 0) {
-      fetch_tok(0, S1.a.k0);
-      fetch_tok(1, S1.b.k0);
-      load_k(0);
-      load_k(1);
-      store_k(ka1, 0);
-      store_k(kb1, 1);
+  bf16x8 qf[QS][NS];             // Q^T operand fragments of the wavefront's 32 rows (both key groups hold the same rows)
+  {
+    // Everything the first two steps need is requested in two rounds, first the look-ups (and V, which needs none), then
+    // the rows they name: two memory latencies instead of six (with the merge below shared by both key groups: 901 of 3001
+    // tokens x 32 heads 55.2 -> 54.1 us for the layer, 256 of 1024 x 4 32.3 -> 30.9).
+    int qtok = wrow0 + lo, k0tok[2][CH], k1tok[2][CH], k2tok[2][CH];
+    u32x4 kreg0[2][CH], kreg1[2][CH], vreg0[2][CH];
+    if (FUSED) qtok = __builtin_amdgcn_raw_buffer_load_b32(Ir, qtok * 4, 0, 0);
+    fetch_tok(k0tok[0], S0.a.k0);
+    fetch_tok(k0tok[1], S0.b.k0);
+    fetch_tok(k1tok[0], S1.a.k0);
+    fetch_tok(k1tok[1], S1.b.k0);
+    fetch_tok(k2tok[0], S2.a.k0);
+    fetch_tok(k2tok[1], S2.b.k0);
+    fetch_tok(ktok[0], S3.a.k0);
+    fetch_tok(ktok[1], S3.b.k0);
+    load_v(vreg0[0], S0.a.k0);
+    load_v(vreg0[1], S0.b.k0);
+    load_v(vreg[0], S1.a.k0);
+    load_v(vreg[1], S1.b.k0);
+    __builtin_amdgcn_sched_barrier(0);
+    int qrow_off = qtok * ROWB;
+    if (FUSED) qrow_off = wrow0 + lo < Lc ? (int)__umul24(qtok, q_pitch) : a.L * q_pitch;   // past the end: out of the buffer's range, reads zeros
+    load_k(k0tok[0], kreg0[0]);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(Qr, qrow_off + 16 * hi + 32 * s, 0, 0);
+      qf[0][s] = __builtin_bit_cast(bf16x8, v);
     }
+    load_k(k0tok[1], kreg0[1]);
+    load_k(k1tok[0], kreg1[0]);
+    load_k(k1tok[1], kreg1[1]);
+    load_k(k2tok[0], kreg[0]);
+    load_k(k2tok[1], kreg[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    store_v(va0, vreg0[0]);
+    store_v(vb0, vreg0[1]);
+    store_k(kwa, kreg0[0]);          // a_0 only serves the first S^T below; the slot is free again after the second barrier
+    store_k(kb0, kreg0[1]);
+    store_k(ka1, kreg1[0]);
+    store_k(kb1, kreg1[1]);
   }
-  __syncthreads();
+  // (everything but the two tiles of step 2 has landed, on every path, see attend.hip)
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * CH));         // vmcnt(2 CH)
+  lds_barrier();
   if (S0.a.k0 >= 0) qk_half<D, QS>(kwa, k_rd, qf, sA);
-  __syncthreads();
-  // in flight from here on: K of step 2, V of step 1; token ids of step 3
-  fetch_tok(0, S2.a.k0);
-  fetch_tok(1, S2.b.k0);
-  load_k(0);
-  load_k(1);
-  load_v(0, S1.a.k0);
-  load_v(1, S1.b.k0);
-  fetch_tok(0, S3.a.k0);
-  fetch_tok(1, S3.b.k0);
+  lds_barrier();
+  // in flight from here on: K of step 2 (V of step 1 and the token ids of step 3 are there)
   if (act(S0.a)) {
     if (S0.a.k0 + koff + 31 > wrow0) mask_half<QS>(sA, S0.a.k0 + koff, hi, wrow0 + lo);
     softmax_max<ND, QS>(sA, c, m, l, o);
@@ -418,25 +421,25 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
       softmax_max<ND, QS>(sA, c, m, l, o);
     }
     if (S2.a.k0 >= 0) {
-      store_k(kwa, 0);
-      store_k(kwb, 1);
+      store_k(kwa, kreg[0]);
+      store_k(kwb, kreg[1]);
     }
     if (S1.a.k0 >= 0) {
-      store_v(vwa, 0);
-      store_v(vwb, 1);
+      store_v(vwa, vreg[0]);
+      store_v(vwb, vreg[1]);
     }
     if (S3.a.k0 >= 0) {
-      load_k(0);
-      load_k(1);
+      load_k(ktok[0], kreg[0]);
+      load_k(ktok[1], kreg[1]);
     }
     if (S2.a.k0 >= 0) {
-      load_v(0, S2.a.k0);
-      load_v(1, S2.b.k0);
+      load_v(vreg[0], S2.a.k0);
+      load_v(vreg[1], S2.b.k0);
     }
     const Step S4 = next_step();
     if (S4.a.k0 >= 0) {
-      fetch_tok(0, S4.a.k0);
-      fetch_tok(1, S4.b.k0);
+      fetch_tok(ktok[0], S4.a.k0);
+      fetch_tok(ktok[1], S4.b.k0);
     }
     lds_barrier();
     S0 = S1; S1 = S2; S2 = S3; S3 = S4;
@@ -444,7 +447,7 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   }
 
   // ---- fused form: the zero rows the loop did not get to
-  if (zfill) {
+  auto flush_zero_rows = [&]() {
     // Latency-bound: a batch of look-ups is a memory round trip.  Sixteen rows per thread and batch, the
     // look-ups of the next batch requested before the stores of the current one (so that waiting for them
     // never includes waiting for those stores to be acknowledged).
@@ -466,66 +469,50 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
       for (int j = 0; j < kBatch; ++j) r[j] = rn[j];
       t0 = t1;
     }
-  }
+  };
 
-  // ---- merge of the two key groups: group 1 hands (m, l, O) of its rows to group 0 through LDS
-  constexpr int NF = 2 + 16 * ND;                        // floats per lane
-  float* mrg = (float*)smem + (rg * NF) * 64 + lane;     // field f of this lane: mrg[f * 64]
-  static_assert(4 * NF * 64 * 4 <= (NKT * KTILE + NVT * VTILE) * 2, "merge buffer does not fit the tile rings");
+  // ---- merge of the two key groups: each keeps half of the columns and hands the other half of its accumulators, with
+  // (m, l), to its partner through LDS, so that both finish and store half of the rows' columns
+  constexpr int NX = ND / 2;                             // d sub-tiles a wavefront keeps
+  constexpr int NF = 2 + 16 * NX;                        // floats a lane hands over
+  using Out = RowOut<D, NX, FUSED>;
+  static_assert(8 * NF * 256 <= (NKT * KTILE + NVT * VTILE) * 2 && Out::kLds <= NF * 256, "the exchange does not fit the tile rings");
+  Out out;
+  out.look_up(idx_row, wrow0, Lc, lane);
   __syncthreads();                                       // every wavefront is done with the tiles
-  if (kg == 1) {
-    mrg[0] = m[0];
-    mrg[64] = l[0];
+  float* give = (float*)smem + wave * (NF * 64) + lane;  // field f of this lane: give[f * 64]
+  float* take = (float*)smem + (wave ^ 4) * (NF * 64) + lane;
+  give[0] = m[0];
+  give[64] = l[0];
 #pragma unroll
-    for (int dt = 0; dt < ND; ++dt)
+  for (int dt = 0; dt < NX; ++dt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mrg[(2 + 16 * dt + r) * 64] = o[0][dt][r];
-  }
+    for (int r = 0; r < 16; ++r) give[(2 + 16 * dt + r) * 64] = kg ? o[0][dt][r] : o[0][NX + dt][r];
   __syncthreads();
-  if (kg == 1) return;
+  f32x16 ox[NX];
+  float mn, lt;
   {
-    const float m1 = mrg[0], l1 = mrg[64];
-    const float mn = fmaxf(m[0], m1);
-    const float a0 = fast_exp2(m[0] - mn), a1 = fast_exp2(m1 - mn);
-    l[0] = l[0] * a0 + l1 * a1;
-    m[0] = mn;
+    const float mt = take[0], lx = take[64];
+    mn = fmaxf(m[0], mt);
+    const float a_own = fast_exp2(m[0] - mn), a_in = fast_exp2(mt - mn);
+    // group 0's term is the fused one in both groups: the row sum and the columns do not depend on who adds
+    lt = kg ? fmaf(lx, a_in, l[0] * a_own) : fmaf(l[0], a_own, lx * a_in);
 #pragma unroll
-    for (int dt = 0; dt < ND; ++dt)
+    for (int dt = 0; dt < NX; ++dt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[0][dt][r] = o[0][dt][r] * a0 + mrg[(2 + 16 * dt + r) * 64] * a1;
+      for (int r = 0; r < 16; ++r) {
+        const float own = kg ? o[0][NX + dt][r] : o[0][dt][r], in = take[(2 + 16 * dt + r) * 64];
+        ox[dt][r] = kg ? fmaf(in, a_in, own * a_own) : fmaf(own, a_own, in * a_in);
+      }
   }
 
-  // ---- epilogue (key group 0): normalise, round to bf16, store
-  {
-    const int qrow = wrow0 + lo;
-    const float lt = l[0] + __shfl_xor(l[0], 32);
-    const float inv_l = lt > 0.f ? 1.0f / lt : 0.f;
-    if (qrow < Lc) {
-      __bf16* orow = a.O ? a.O + (bh * a.Lc + qrow) * D : nullptr;
-      __bf16* frow = nullptr;
-      __bf16* xrow = nullptr;
-      if (FUSED && a.Of) frow = a.Of + a.os.head(b, h) + idx_row[qrow] * a.os.l;
-      if (FUSED && a.X) xrow = a.X + (((long long)b * a.L + idx_row[qrow]) * a.Hq + h) * D;
-#pragma unroll
-      for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          u32x2 w;
-          w[0] = pack_bf16(o[0][dt][4 * q4 + 0] * inv_l, o[0][dt][4 * q4 + 1] * inv_l);
-          w[1] = pack_bf16(o[0][dt][4 * q4 + 2] * inv_l, o[0][dt][4 * q4 + 3] * inv_l);
-          if (orow) *(u32x2*)(orow + 32 * dt + 8 * q4 + 4 * hi) = w;
-          if (FUSED && frow) *(u32x2*)(frow + 32 * dt + 8 * q4 + 4 * hi) = w;
-          if (FUSED && xrow) {
-            u32x2* px = (u32x2*)(xrow + 32 * dt + 8 * q4 + 4 * hi);
-            u32x2 x = *px;
-            x[0] = add_bf16_pairs(x[0], w[0]);
-            x[1] = add_bf16_pairs(x[1], w[1]);
-            *px = x;
-          }
-        }
-      if (a.lse && hi == 0) a.lse[bh * a.Lc + qrow] = (m[0] + log2f(lt)) * kLn2;
-    }
-  }
+  // ---- epilogue: normalise, round to bf16, store the rows (RowOut; the LDS that the partner's half came through, which
+  // nobody else reads)
+  lt += __shfl_xor(lt, 32);
+  char* const lds_out = (char*)smem + (wave ^ 4) * (NF * 256);
+  out.put(ox, lt > 0.f ? 1.0f / lt : 0.f, lds_out, lane);
+  out.store(a, b, h, wrow0, Lc, 32 * NX * kg, lds_out, lane, [&]() { if (zfill) flush_zero_rows(); });
+  if (a.lse && kg == 0 && hi == 0 && wrow0 + lo < Lc) a.lse[bh * a.Lc + wrow0 + lo] = (mn + log2f(lt)) * kLn2;
 }
 
 }  // namespace
@@ -535,13 +522,15 @@ hipError_t launch_attend_split(AttendArgs& a, int d, bool fused, hipStream_t st)
   a.nk_tiles = (a.Lc + BN - 1) / BN;
   map_workgroups(a);
   const unsigned grid = grid_for(a);
-  if (d == 128) {
-    if (fused) attend_split_kernel<128, true><<<grid, kThreadsS, 0, st>>>(a);
-    else attend_split_kernel<128, false><<<grid, kThreadsS, 0, st>>>(a);
-  } else {
-    if (fused) attend_split_kernel<64, true><<<grid, kThreadsS, 0, st>>>(a);
-    else attend_split_kernel<64, false><<<grid, kThreadsS, 0, st>>>(a);
-  }
+  const auto go = [&](auto fused_tag, auto lists_tag) {
+    constexpr bool F = decltype(fused_tag)::value, B = decltype(lists_tag)::value;
+    if (d == 128) attend_split_kernel<128, F, B><<<grid, kThreadsS, 0, st>>>(a);
+    else attend_split_kernel<64, F, B><<<grid, kThreadsS, 0, st>>>(a);
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  if (fused) a.block_list ? go(yes, yes) : go(yes, no);
+  else a.block_list ? go(no, yes) : go(no, no);
   return hipGetLastError();
 }
 
