@@ -15,7 +15,10 @@
 // as the integer sum of the 24-bit significands (shifted by the lowest exponent bit), accumulated with
 // integer atomics, and becomes a double only when the bins are walked, in a fixed order.  Two runs on
 // the same scores give the same count bit for bit.
+// Rows of up to kRowTokens take all of that in one launch (bud_row_kernel, below); longer ones the chain of small kernels.
 #include "tsa_internal.h"
+
+#include <climits>
 
 namespace tsa {
 
@@ -41,7 +44,7 @@ struct BudRow {
 struct BudArgs {
   const float* scores;   // [B,Hq,L]
   float* sl;             // [B,L]
-  BudRow* rows;          // [B]
+  BudRow* rows;          // [B]; NULL: the row kernel follows, no histograms to clear
   int32_t* k_keep;       // [B]
   int Hq, L;
   double tau;
@@ -101,6 +104,7 @@ __global__ __launch_bounds__(kSumThreads) void head_sum_kernel(BudArgs a) {
     for (; h < a.Hq; ++h) acc += p[(long long)h * a.L];
     a.sl[b * a.L + t] = acc;
   }
+  if (!a.rows) return;
   constexpr int n_words = (int)(sizeof(BudRow) / 4);
   uint32_t* row = (uint32_t*)(a.rows + b);
   for (int i = t; i < n_words; i += gridDim.x * kSumThreads) row[i] = 0u;
@@ -212,6 +216,28 @@ __global__ __launch_bounds__(kThreads) void bud_hist_kernel(BudArgs a) {
   }
 }
 
+// The count from the value v at which the ascending mass crosses the target: n_eq tokens have it, count_below tokens
+// with mass_below lie under it; of the n_eq, as many are dropped as are needed to reach the target.
+__device__ __forceinline__ int32_t keep_of(const BudArgs& a, float value, uint32_t n_eq, uint32_t count_below, double mass_below,
+                                           double target) {
+  long long k_sparse = 0;
+  if (a.tau > 0.0) {
+    const double v = (double)value;
+    long long j = n_eq;
+    if (v > 0.0) {
+      const double need = (target - mass_below) / v;
+      j = (long long)ceil(need);
+      if (j < 1) j = 1;
+      if (j > (long long)n_eq) j = n_eq;
+    }
+    k_sparse = (long long)count_below + j;
+  }
+  long long keep = (long long)a.L - k_sparse;
+  if (keep < a.k_min) keep = a.k_min;
+  if (keep > a.k_max) keep = a.k_max;
+  return (int32_t)keep;
+}
+
 __global__ void bud_final_kernel(BudArgs a) {
   const long long b = blockIdx.x;
   BudRow* rw = a.rows + b;
@@ -220,26 +246,205 @@ __global__ void bud_final_kernel(BudArgs a) {
   const BudState st = next_state(rw, 3, rw->state[3], a.tau, nullptr, 0, lane);
   if (lane == 0) {
     rw->state[4] = st;
-    long long k_sparse = 0;
-    if (a.tau > 0.0) {
-      // all tokens of the final bin have the value v: take as many as are needed to reach the target
-      const uint32_t bin = st.prefix & 255u;
-      const uint32_t n_eq = rw->count[3][bin];
-      const double v = (double)key_value(st.prefix);
-      long long j = n_eq;
-      if (v > 0.0) {
-        const double need = (target - st.mass_below) / v;
-        j = (long long)ceil(need);
-        if (j < 1) j = 1;
-        if (j > (long long)n_eq) j = n_eq;
-      }
-      k_sparse = (long long)st.count_below + j;
-    }
-    long long keep = (long long)a.L - k_sparse;
-    if (keep < a.k_min) keep = a.k_min;
-    if (keep > a.k_max) keep = a.k_max;
-    a.k_keep[b] = (int32_t)keep;
+    a.k_keep[b] = keep_of(a, key_value(st.prefix), rw->count[3][st.prefix & 255u], st.count_below, st.mass_below, target);
   }
+}
+
+// ---- rows of up to kRowTokens: the descent in one launch, one workgroup per row.
+// The chain above is five launches of a few us each whose work is a few hundred ns: what they cost is the launches.  Here the
+// row's keys stay in registers (J per thread), and the bins are cut from the RANGE the keys span (as the selection cuts
+// them) instead of from the digits: 2048 bins of at most 2^21 consecutive keys, and the keys of a bin still differ by
+// at most one step of the binary exponent, so that the bin's mass stays an exact integer sum.  Count and mass share one
+// 64-bit LDS atomic per key: count in the upper 20 bits, the signed sum of the (at most 25-bit) shifted significands
+// of up to 2^14 keys in the lower 44.  As soon as the bin that crosses the target holds at most 64 keys, one wavefront ranks
+// them against each other (integer sums again, so the order in which they were collected does not matter): one
+// pass in practice, three at most (2^32 -> 2^21 -> 2^10 -> 1).
+// Bound by the chain of its steps on one CU: load, range, a pass (clear, count, scan), ranking.
+constexpr int kRowBins = 2 * kThreads;
+// 16 keys per thread; beyond, one CU's share of the row (0.6 us per 1000 tokens) outweighs the launches.  Whole budget with 32 heads,
+// one launch / five: 4096 tokens 10.6 / 23.2 us, 8192 13.8 / 22.9, 12345 15.7 / 22.6, 16384 16.7 / 22.9, 20000 20.4 / 23.7, 32768 26.1 / 23.8.
+constexpr int kRowTokens = 16 * kThreads;
+constexpr int kCountShift = 44;
+constexpr int kHot = 16;                      // keys of a wavefront in one bin from which they are added up first
+constexpr int kRank = 64;
+
+__device__ __forceinline__ int key_exponent(uint32_t key) {
+  const uint32_t u = (key & 0x80000000u) ? key : ~key;
+  const int e = (int)((u >> 23) & 255u);
+  return e < 1 ? 1 : e;
+}
+// smallest exponent field among the keys lo .. lo + last (see bin_exponent)
+__device__ __forceinline__ int range_exponent(uint32_t lo, uint32_t last) {
+  const uint32_t hi = lo > 0xffffffffu - last ? 0xffffffffu : lo + last;
+  return min(key_exponent(lo), key_exponent(hi));
+}
+// a key's score as an integer, in units of 2^(base - 150)
+__device__ __forceinline__ long long key_units(uint32_t key, int base) {
+  uint32_t sig;
+  int e;
+  split_float(key_value(key), sig, e);
+  const long long u = (long long)((unsigned long long)sig << ((e - base) & 1));   // e - base is 0 or 1
+  return (key & 0x80000000u) ? u : -u;
+}
+__device__ __forceinline__ int lane_value(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+
+template <int J>
+__global__ __launch_bounds__(kThreads) void bud_row_kernel(BudArgs a) {
+  __shared__ unsigned long long bins[kRowBins];
+  __shared__ double wmass[kWaves];
+  __shared__ uint32_t wcount[kWaves], wmin[kWaves], wmax[kWaves];
+  __shared__ uint32_t cand[kRank];
+  __shared__ int sh_first, sh_last, n_cand;
+  __shared__ double sh_mass;
+  __shared__ uint32_t sh_below, sh_in;
+  const long long b = blockIdx.x;
+  const float* s = a.sl + b * a.L;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  uint32_t key[J];
+  uint32_t kmin = 0xffffffffu, kmax = 0u;
+  float v[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) v[j] = s[min(tid + j * kThreads, a.L - 1)];
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    key[j] = order_key(v[j]);                                // (past the end: the last key again)
+    kmin = min(kmin, key[j]);
+    kmax = max(kmax, key[j]);
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, d));
+    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, d));
+  }
+  if (lane == 0) { wmin[wave] = kmin; wmax[wave] = kmax; }
+  bins[tid] = 0ull;
+  bins[tid + kThreads] = 0ull;
+  if (tid == 0) { sh_first = INT_MAX; sh_last = -1; n_cand = 0; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) { kmin = min(kmin, wmin[w]); kmax = max(kmax, wmax[w]); }
+
+  int n_mine = (a.L - tid + kThreads - 1) / kThreads;      // keys of this thread
+  uint32_t lo = kmin, last = kmax - kmin;     // the keys still in question: [lo, lo + last]
+  uint32_t count_below = 0, n_in = 0;
+  double mass_below = 0.0, target = 0.0;
+  for (bool first_pass = true;; first_pass = false) {
+    const int shift = max(0, 32 - __clz((int)(last | 1u)) - 11);                   // last >> shift < kRowBins
+    const uint32_t bin_last = (1u << shift) - 1u;
+    asm volatile("" : "+v"(n_mine));            // (J comparisons per pass, not J lane masks kept across the passes)
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      asm volatile("" : "+v"(key[j]));                      // (nothing derived from a key lives across the passes: registers)
+      const uint32_t off = key[j] - lo;                                            // keys below lo wrap beyond `last`
+      const bool in = j < n_mine && off <= last;
+      const unsigned long long act = __ballot(in);
+      if (act == 0ull) continue;
+      const uint32_t bin = in ? off >> shift : 0u;
+      const unsigned long long add = (1ull << kCountShift) + (unsigned long long)key_units(key[j], range_exponent(lo + (bin << shift), bin_last));
+      // additions to one address run one after the other: a wavefront whose keys crowd into one bin adds them up first
+      const int leader = __ffsll((long long)act) - 1;
+      const bool same = in && bin == (uint32_t)lane_value((int)bin, leader);
+      const unsigned long long hot = __ballot(same);
+      if (__popcll(hot) >= kHot) {
+        unsigned long long sum = same ? add : 0ull;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
+        if (lane == leader) atomicAdd(&bins[bin], sum);
+        if (in && !same) atomicAdd(&bins[bin], add);
+      } else if (in) {
+        atomicAdd(&bins[bin], add);
+      }
+    }
+    __syncthreads();
+    // thread t owns bins 2 t and 2 t + 1; masses below them by a scan in a fixed order
+    double ms[2] = {0.0, 0.0};
+    uint32_t cn[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const unsigned long long w = bins[2 * tid + j];
+      const long long sum = (long long)(w << (64 - kCountShift)) >> (64 - kCountShift);
+      cn[j] = (uint32_t)((w - (unsigned long long)sum) >> kCountShift);
+      if (cn[j]) ms[j] = ldexp((double)sum, range_exponent(lo + ((uint32_t)(2 * tid + j) << shift), bin_last) - 150);
+    }
+    const double mine = ms[0] + ms[1];
+    const uint32_t minec = cn[0] + cn[1];
+    double incl = mine;
+    uint32_t inclc = minec;
+    if (__ballot(minec != 0u)) {
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const double up = __shfl_up(incl, d);
+        const uint32_t upc = __shfl_up(inclc, d);
+        if (lane >= d) { incl += up; inclc += upc; }
+      }
+    }
+    if (lane == 63) { wmass[wave] = incl; wcount[wave] = inclc; }
+    __syncthreads();
+    double base = 0.0, all = 0.0;
+    uint32_t basec = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      if (w < wave) { base += wmass[w]; basec += wcount[w]; }
+      all += wmass[w];
+    }
+    if (first_pass) target = a.tau * all;                                          // the first pass's bins hold every token
+    // the first bin whose keys reach the target; if none does (tau >= 1 up to rounding), the last bin with any token
+    const double mb0 = mass_below + base + (incl - mine), mb1 = mb0 + ms[0];
+    const uint32_t cb0 = count_below + basec + (inclc - minec), cb1 = cb0 + cn[0];
+    const bool hit0 = cn[0] && mb0 + ms[0] >= target, hit1 = cn[1] && mb1 + ms[1] >= target;
+    const unsigned long long reach = __ballot(hit0 || hit1), some = __ballot(minec != 0u);
+    if (reach && lane == __ffsll((long long)reach) - 1) atomicMin(&sh_first, 2 * tid + (hit0 ? 0 : 1));
+    if (some && lane == 63 - __clzll((long long)some)) atomicMax(&sh_last, 2 * tid + (cn[1] ? 1 : 0));
+    __syncthreads();
+    const int bin = sh_first != INT_MAX ? sh_first : sh_last;
+    if (bin == 2 * tid) { sh_mass = mb0; sh_below = cb0; sh_in = cn[0]; }
+    if (bin == 2 * tid + 1) { sh_mass = mb1; sh_below = cb1; sh_in = cn[1]; }
+    bins[tid] = 0ull;                                      // for the next pass
+    bins[tid + kThreads] = 0ull;
+    __syncthreads();
+    if (tid == 0) { sh_first = INT_MAX; sh_last = -1; }
+    mass_below = sh_mass;
+    count_below = sh_below;
+    n_in = sh_in;
+    lo += (uint32_t)bin << shift;
+    last = bin_last;
+    if (n_in <= kRank || shift == 0) break;
+    __syncthreads();
+  }
+  if (last == 0) {                                         // a single value (as many keys as there may be)
+    if (tid == 0) a.k_keep[b] = keep_of(a, key_value(lo), n_in, count_below, mass_below, target);
+    return;
+  }
+  asm volatile("" : "+v"(n_mine));
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+    if (j < n_mine && key[j] - lo <= last) cand[atomicAdd(&n_cand, 1)] = key[j];     // n_in of them
+  __syncthreads();
+  if (wave) return;
+  // lane i: the keys below candidate i, and those equal to it
+  const int base = range_exponent(lo, last);
+  const uint32_t mine = cand[min(lane, (int)n_in - 1)];
+  const long long units = key_units(mine, base);
+  long long below = 0;
+  uint32_t n_less = 0, n_eq = 0;
+  for (int i = 0; i < (int)n_in; ++i) {
+    const uint32_t other = (uint32_t)lane_value((int)mine, i);
+    const long long u = ((long long)lane_value((int)(units >> 32), i) << 32) | (uint32_t)lane_value((int)units, i);
+    if (other < mine) { below += u; ++n_less; }
+    n_eq += other == mine;
+  }
+  const double mb = mass_below + ldexp((double)below, base - 150);
+  const bool reach = mb + ldexp((double)(units * (long long)n_eq), base - 150) >= target;
+  // the smallest candidate that reaches the target, else the largest
+  uint32_t pick = reach ? mine : 0xffffffffu, top = mine;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    pick = min(pick, (uint32_t)__shfl_xor((int)pick, d));
+    top = max(top, (uint32_t)__shfl_xor((int)top, d));
+  }
+  if (!__ballot(reach)) pick = top;
+  if (lane == __ffsll((long long)__ballot(mine == pick)) - 1)
+    a.k_keep[b] = keep_of(a, key_value(mine), n_eq, count_below + n_less, mb, target);
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -260,7 +465,14 @@ hipError_t launch_budget(const Dims& dm, const float* scores, double tau_cov, in
   a.sl = (float*)((char*)ws + align256((size_t)dm.B * sizeof(BudRow)));
   a.k_keep = k_keep;
   a.Hq = dm.Hq; a.L = dm.L; a.tau = tau_cov;
+  if (dm.L <= kRowTokens) a.rows = nullptr;
   head_sum_kernel<<<dim3((dm.L + kSumThreads - 1) / kSumThreads, dm.B), kSumThreads, 0, st>>>(a);
+  if (!a.rows) {
+    const int per_thread = (dm.L + kThreads - 1) / kThreads;
+    if (per_thread <= 4) bud_row_kernel<4><<<dm.B, kThreads, 0, st>>>(a);
+    else bud_row_kernel<16><<<dm.B, kThreads, 0, st>>>(a);
+    return hipGetLastError();
+  }
   const dim3 grid((dm.L + kSlice - 1) / kSlice, dm.B);
   bud_hist_kernel<0><<<grid, kThreads, 0, st>>>(a);
   bud_hist_kernel<1><<<grid, kThreads, 0, st>>>(a);
