@@ -56,17 +56,15 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   constexpr int kThreads = 64 * NW;
   constexpr int RW = 32 * QS;                     // query rows per wavefront
   constexpr int BM = RW * NW;                     // query rows per workgroup
-  // LDS row stride of a K tile in elements.  K rows are read 16 bytes per lane by 16 lanes of
-  // different keys: a 16-byte pad walks them over all 64 banks.
-  constexpr int KS = D + 8;
-  constexpr int KTILE = BN * KS, VTILE = D * VS;  // elements of one staged tile (K: [key][d], V: [d][key])
-  constexpr int CH = BN * (D / 8) / kThreads;     // 16-byte chunks per thread per tile
+  using KRows = LdsRows<2 * D>;                   // K tile: [key][d]
+  using VRows = LdsRows<2 * BN>;                  // V^T tile: [d][key]
+  constexpr int KHALF = 32 / KRows::RPB * kBlock, VTILE = D / VRows::RPB * kBlock;   // bytes of half a K tile, of a V^T tile
+  constexpr int CH = BN * D / (512 * NW);         // blocks (of 512 elements) of a tile that a wavefront loads
   constexpr int NS = D / 16;                      // MFMA k-steps of the QK product
   constexpr int ND = D / 32;                      // d sub-tiles of the output
   constexpr int ROWB = D * 2;                     // bytes of one row in global memory
-  constexpr int KHALF = KTILE / 2;
   constexpr int KRING = NW == 8 ? 6 : 5;          // half tiles of the K ring
-  __shared__ __attribute__((aligned(16))) __bf16 smem[KRING * KHALF + 2 * VTILE];   // K ring, V ring [2 tiles]
+  __shared__ __attribute__((aligned(1024))) char smem[KRING * KHALF + 2 * VTILE];   // K ring, V ring [2 tiles]
 
   // ---- workgroup -> (head, query tile).  Consecutive workgroup ids go to different XCDs, so
   // id % 8 picks the XCD; all tiles of a head (and all heads of a KV group) stay on one XCD to
@@ -97,9 +95,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   const __bf16* k_head = FUSED ? a.K + a.ks.head(b, h / g_grp) : a.K + bkv * Lc * D;
   const int n_rows = FUSED ? a.L : Lc;
   const __amdgpu_buffer_rsrc_t Qr = head_rsrc(q_head, (long long)n_rows * q_pitch);
-  const __amdgpu_buffer_rsrc_t Kr = head_rsrc(k_head, (long long)n_rows * k_pitch);
+  const u32x4 Kr = rsrc_words(k_head, (long long)n_rows * k_pitch);
   const long long vt_bytes = (long long)a.nk_tiles * BN * ROWB;
-  const __amdgpu_buffer_rsrc_t Vr = head_rsrc(a.Vt + bkv * (vt_bytes / 2), vt_bytes);
+  const u32x4 Vr = rsrc_words(a.Vt + bkv * (vt_bytes / 2), vt_bytes);
   const int32_t* idx_row = FUSED ? a.idx + bkv * a.Lc : nullptr;
   // index loads past the end of the set return 0 (token 0): such rows are only ever read as keys
   // beyond every query of the workgroup, which causality masks
@@ -188,18 +186,19 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
     z_every = max(1, n_pipelined / max(1, z_passes));
   }
 
-  // ---- staging: global -> registers -> LDS in 16-byte chunks.  A K tile is 64 rows of the
-  // row-major tensor: thread chunk i covers row st_row + i * kRowsPerPass, columns 8*st_col.. .
-  // A V tile is one contiguous [d][64] block of the tiled V^T tensor (64 keys = 64 * ROWB bytes as
-  // well): thread chunk i is 16-byte piece tid + i * kThreads, i.e. d-row piece / 8, keys
-  // 8 * (piece % 8).. .  The tile's first key goes into the scalar offset of the buffer load.
-  const int st_row = CH * (tid / (D / 8)), st_col = tid % (D / 8);   // K rows st_row .. st_row + CH - 1 of the tile
-  const bool st_half = __builtin_amdgcn_readfirstlane(st_row) >= 32; // (a wavefront's rows lie in one half tile)
-  const int lk_off = k_row_perm(NW == 8 ? st_row : st_row & 31) * KS + 8 * st_col;   // elements, LDS side (K): permuted row order (which leaves
-                                                                  // the CH <= 4 rows of a thread next to each other)
-  const int gv_off = 16 * tid;                                    // bytes, global side (V^T)
-  const int lv_off = (tid >> 3) * VS + 8 * (tid & 7);             // elements, LDS side (V^T)
-  constexpr int kVRowsPerPass = kThreads / 8;
+  // ---- staging: global memory -> LDS, in blocks of 1 KiB (LdsRows); wavefront w takes blocks CH w .. CH w + CH - 1 of
+  // either tile.  Row R of the K tile in LDS need not be key R: what a lane loads is chosen so that its CH rows are
+  // CH consecutive keys (one look-up in idx for all of them), and the fragment reads undo that together with k_row_perm.
+  // A V^T tile is one contiguous [d][64] block of the tiled tensor.  Offsets that all lanes share go into the scalar
+  // offset of the load.
+  const int uwave = __builtin_amdgcn_readfirstlane(wave);
+  const int st_row = CH * (tid / KRows::LPR), st_col = 16 * KRows::piece(lane);      // keys st_row .. st_row + CH - 1 of the tile, byte in the row
+  constexpr int kHalfBlocks = 32 / KRows::RPB;
+  const bool st_half = uwave * CH >= kHalfBlocks;                                    // (a wavefront's blocks lie in one half tile)
+  const int st_lds = (uwave * CH % kHalfBlocks) * kBlock;
+  const int gv_off = (lane / VRows::LPR) * 2 * BN + 16 * VRows::piece(lane);
+  const int gv_block = uwave * CH * 1024, lv_block = uwave * CH * kBlock;
+  const int lds0 = (int)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
   // Rows of the next K tile to be loaded: ktok[i] = row of thread chunk i (fused: the token the
   // compacted row stands for, fetched from idx one tile ahead of the K load that uses it).
   int ktok[CH];
@@ -222,36 +221,34 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
       for (int i = 0; i < CH; ++i) ktok[i] = k0 + st_row + i;
     }
   };
-  auto load_k = [&](const int (&ktok)[CH], u32x4 (&reg)[CH]) {
-#pragma unroll
-    for (int i = 0; i < CH; ++i)
-      reg[i] = __builtin_amdgcn_raw_buffer_load_b128(Kr, row_off(ktok[i]) + 16 * st_col, 0, 0);
+  // block i of this wavefront's share (half0, half1, dst: slots of the rings, bytes)
+  auto load_k = [&](const int (&ktok)[CH], int half0, int half1, int i) {
+    load_to_lds(Kr, row_off(ktok[i]) + st_col, 0, lds0 + (st_half ? half1 : half0) + st_lds + i * kBlock);
   };
-  auto load_v = [&](int k0, u32x4 (&reg)[CH]) {
-#pragma unroll
-    for (int i = 0; i < CH; ++i)
-      reg[i] = __builtin_amdgcn_raw_buffer_load_b128(Vr, gv_off + i * kThreads * 16, k0 * ROWB, 0);
-  };
-  // thread chunk i of a K tile goes to the first or the second half tile (half0, half1: slots of the ring; with eight
-  // wavefronts half1 follows half0)
-  auto store_k_chunk = [&](__bf16* half0, __bf16* half1, int i, const u32x4& v) {
-    *(u32x4*)(&(NW == 4 && st_half ? half1 : half0)[lk_off + i * KS]) = v;
-  };
-  auto store_k = [&](__bf16* half0, __bf16* half1, const u32x4 (&reg)[CH]) {
-#pragma unroll
-    for (int i = 0; i < CH; ++i) store_k_chunk(half0, half1, i, reg[i]);
-  };
-  auto store_v = [&](__bf16* dst, const u32x4 (&reg)[CH]) {
-#pragma unroll
-    for (int i = 0; i < CH; ++i) *(u32x4*)(&dst[lv_off + i * kVRowsPerPass * VS]) = reg[i];
-  };
+  auto load_v = [&](int k0, int dst, int i) { load_to_lds(Vr, gv_off, k0 * ROWB + gv_block + i * 1024, lds0 + dst + lv_block + i * kBlock); };
 
-  // LDS read bases.  K operand (A of S^T): MFMA row lo = LDS row lo = key k_row_perm(lo) of the
-  // half tile, 8 d-values at 8*hi.  (The permutation is applied when the tile is written: eight
-  // adjacent lanes must read eight adjacent LDS rows to stay free of bank conflicts.)
-  const int k_rd = lo * KS + 8 * hi;
+  // LDS read bases.  K operand (A of S^T): MFMA row lo = key k_row_perm(lo) of the half tile, 8 d-values at 8*hi.
+  const int k_key = k_row_perm(lo);
+  constexpr int GR = KRows::RPB * CH;             // keys that a wavefront loads
+  const int k_ldsrow = (k_key & ~(GR - 1)) | ((k_key & (CH - 1)) * KRows::RPB) | ((k_key & (GR - 1)) / CH);
+  const int kb0 = KRows::read_base(k_ldsrow, hi);
   // V^T operand (A of O^T): row = d (lo within the 32-row d sub-tile), 8 keys at 8*hi.
-  const int v_rd = lo * VS + 8 * hi;
+  const int vb0 = VRows::read_base(lo, hi);
+  const int k_rd[2] = {kb0, kb0 ^ 32}, v_rd[2] = {vb0, vb0 ^ 32};
+  constexpr int VSUB = 32 / VRows::RPB * kBlock;  // bytes between d sub-tiles
+  auto k_frag = [&](int half, int i) -> bf16x8 { return *(const bf16x8*)(smem + half + KRows::read_off(k_rd, i)); };
+  // 16 keys from 16 hf on, d sub-tile dt (hf 0 .. 3 over the tile's 64 keys)
+  auto v_frag = [&](int tile, int hf, int dt) -> bf16x8 { return *(const bf16x8*)(smem + tile + VRows::read_off(v_rd, hf) + dt * VSUB); };
+  auto qk = [&](int half, const bf16x8 (&qf)[QS][NS], f32x16 (&s)[QS]) {
+#pragma unroll
+    for (int qs = 0; qs < QS; ++qs) s[qs] = f32x16{0};
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+      const bf16x8 kf = k_frag(half, st);
+#pragma unroll
+      for (int qs = 0; qs < QS; ++qs) s[qs] = mfma32(kf, qf[qs][st], s[qs]);
+    }
+  };
 
   f32x16 o[QS][ND];
   float m[QS], l[QS];
@@ -263,35 +260,33 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
     for (int dt = 0; dt < ND; ++dt) o[qs][dt] = f32x16{0};
   }
 
-  // Ring slots.  K half tiles: kh(0) = K(t) half 1, kh(1) and kh(2) = K(t+1), K(t+2) goes to kh(3) and kh(4)
+  // Ring slots (byte offsets).  K half tiles: kh(0) = K(t) half 1, kh(1) and kh(2) = K(t+1), K(t+2) goes to kh(3) and kh(4)
   // (whose last readers were in iteration t - 1); V tiles: V(t) in vc, V(t+1) goes to vn.  With eight wavefronts the
-  // LDS has room for three whole tiles, whose halves are one address register and an offset (0.4 % of a long launch).
-  __bf16* kr[5];
+  // LDS has room for three whole tiles, whose halves are one offset apart (0.4 % of a long launch).
+  int kr[5];
 #pragma unroll
-  for (int j = 0; j < 5; ++j) kr[j] = smem + (NW == 8 ? 2 * j : j) * KHALF;   // (eight wavefronts: tiles t, t + 1, t + 2)
-  auto kh = [&](int j) -> __bf16* { return NW == 8 ? kr[(j + 1) >> 1] + ((j + 1) & 1) * KHALF : kr[j]; };
-  auto k_first = [&]() -> __bf16* { return NW == 8 ? kr[0] : kr[3]; };         // K(0) half 0, read by the prologue alone
-  __bf16* vc = smem + KRING * KHALF;
-  __bf16* vn = smem + KRING * KHALF + VTILE;
+  for (int j = 0; j < 5; ++j) kr[j] = (NW == 8 ? 2 * j : j) * KHALF;   // (eight wavefronts: tiles t, t + 1, t + 2)
+  auto kh = [&](int j) -> int { return NW == 8 ? kr[(j + 1) >> 1] + ((j + 1) & 1) * KHALF : kr[j]; };
+  auto k_first = [&]() -> int { return NW == 8 ? kr[0] : kr[3]; };         // K(0) half 0, read by the prologue alone
+  int vc = KRING * KHALF;
+  int vn = KRING * KHALF + VTILE;
   auto rotate = [&]() {
-    __bf16 *t0 = kr[0], *t1 = kr[1];
+    int t0 = kr[0], t1 = kr[1];
     if (NW == 8) { kr[0] = kr[1]; kr[1] = kr[2]; kr[2] = t0; }
     else { kr[0] = kr[2]; kr[1] = kr[3]; kr[2] = kr[4]; kr[3] = t0; kr[4] = t1; }
     t0 = vc; vc = vn; vn = t0;
   };
 
   // ---- prologue
-  Tile T0 = gen.next(), T1 = gen.next(), T2 = gen.next(), T3 = gen.next();
-  u32x4 kreg[CH], vreg[CH];
+  Tile T0 = gen.next(), T1 = gen.next(), T2 = gen.next();
   f32x16 sA[QS], sB[QS];
   uint32_t pA[QS][8], pB[QS][8];
   bf16x8 qf[QS][NS];             // Q^T operand fragments, in registers for the whole kernel
   {
-    // Everything the first iterations need is requested in two rounds, first the look-ups (and V, which needs
-    // none), then the rows they name: two memory latencies instead of six (0.5 to 1 % of a launch up to 32 x 16384 rows).  Tiles that do not exist are
+    // Everything the first iteration needs is requested in two rounds, first the look-ups, then the
+    // rows they name and V: two memory latencies instead of six (0.5 to 1 % of a launch up to 32 x 16384 rows).  Tiles that do not exist are
     // replaced by tile 0: loaded, never used.
-    int qtok[QS], k0tok[CH], k1tok[CH], k2tok[CH];
-    u32x4 kreg0[CH], kreg1[CH], vreg0[CH];
+    int qtok[QS], k0tok[CH], k1tok[CH];
 #pragma unroll
     for (int qs = 0; qs < QS; ++qs) {
       const int qr = wrow0 + 32 * qs + lo;
@@ -299,10 +294,10 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
     }
     fetch_tok(max(T0.k0, 0), k0tok);
     fetch_tok(max(T1.k0, 0), k1tok);
-    fetch_tok(max(T2.k0, 0), k2tok);
-    fetch_tok(max(T3.k0, 0), ktok);
-    load_v(max(T0.k0, 0), vreg0);
-    load_v(max(T1.k0, 0), vreg);
+    fetch_tok(max(T2.k0, 0), ktok);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) load_k(k0tok, k_first(), kh(0), i);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int qs = 0; qs < QS; ++qs) {
@@ -315,21 +310,29 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
         qf[qs][s] = __builtin_bit_cast(bf16x8, v);
       }
     }
-    load_k(k0tok, kreg0);
-    load_k(k1tok, kreg1);
-    load_k(k2tok, kreg);
     __builtin_amdgcn_sched_barrier(0);
-    store_v(vc, vreg0);
-    store_k(k_first(), kh(0), kreg0);
-    store_k(kh(1), kh(2), kreg1);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) load_k(k1tok, kh(1), kh(2), i);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) load_v(max(T0.k0, 0), vc, i);
   }
-  // (the stores have waited for everything but the last tile of K, on every path: otherwise the compiler would
-  // carry the Q fragments as "possibly pending" into the loop, and every MFMA that reads one would wait for
-  // the oldest K / V prefetch in flight)
-  __builtin_amdgcn_s_waitcnt(0x0F70 | CH);               // vmcnt(CH)
+  // Everything has landed (the next wait for loads is at the end of the first iteration; and the compiler must know that the
+  // Q fragments and look-ups have, or it would carry them as "possibly pending" into the loop).
+  wait_loads();
   lds_barrier();
-  if (T0.k0 >= 0) qk_half<D, QS>(k_first(), k_rd, qf, sA);
+  if (T0.k0 >= 0) qk(k_first(), qf, sA);
   if (NW != 8) lds_barrier();                            // that slot is written in the first iteration
+  // O^T += V^T P^T for half `half` of a tile (two MFMA k-steps of 16 keys)
+  auto pv = [&](int tile, int half, const uint32_t (&pb)[QS][8]) {
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int dt = 0; dt < ND; ++dt) {
+        const bf16x8 vf = v_frag(tile, 2 * half + hf, dt);
+#pragma unroll
+        for (int qs = 0; qs < QS; ++qs) o[qs][dt] = mfma32(vf, p_operand(pb[qs], hf), o[qs][dt]);
+      }
+  };
   auto wave_active = [&](const Tile& t) -> bool { return t.k0 >= 0 && (t.use & half_bit) && t.k0 <= wrow0 + RW - 1; };
   if (wave_active(T0)) {
     if (T0.k0 + 31 > wrow0) mask_half<QS>(sA, T0.k0, hi, wrow0 + lo);
@@ -338,7 +341,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
 
   // Invariant at the top of an iteration: sA = S^T of the first half of tile T0, already masked
   // and already covered by the running max m (if this wavefront takes part in T0); K(T0)'s second half in
-  // kh(0), K(T1) in kh(1) and kh(2), V(T0) in vc; kreg = K(T2) and vreg = V(T1) are in flight; ktok = rows of T3.
+  // kh(0), K(T1) in kh(1) and kh(2), V(T0) in vc, nothing in flight; ktok = rows of T2.  The iteration requests K(T2) and V(T1)
+  // at its start (the slots' last readers are behind the barrier) and waits for them at its end.
   //
   // Order inside an iteration: every block of 16 MFMAs is issued next to vector work that does
   // not depend on it, so the matrix pipe and the VALU overlap within the wavefront:
@@ -371,25 +375,20 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   // must all belong to block 0 (K of the next tile, complete since the previous barrier), not to
   // the V tile that this iteration is still writing
   static_assert(kChunks % kRing == 0 && kRing > kPF && kPF <= CPB, "fragment ring does not fit the chunk stream");
-  constexpr int kZChunk = 2 * CH < CPB ? 2 * CH : CPB - 1;
   bf16x8 kfr[kRing];
   // fragment fetch for chunk c of the iteration whose half tiles of K and tile of V sit in (k1_, k2_, vc_)
-  auto fetch = [&](int c, const __bf16* k1_, const __bf16* k2_, const __bf16* vc_) {
+  auto fetch = [&](int c, int k1_, int k2_, int vc_) {
     const int blk = c / CPB, i = c % CPB, slot = c % kRing;
-    if (blk == 0) kfr[slot] = *(const bf16x8*)(&k1_[k_rd + 16 * i]);
-    else if (blk == 2) kfr[slot] = *(const bf16x8*)(&k2_[k_rd + 16 * i]);
-    else {
-      const int hf = i / ND, dt = i % ND;
-      kfr[slot] = *(const bf16x8*)(&vc_[v_rd + (32 * dt) * VS + (blk == 3 ? 32 : 0) + 16 * hf]);
-    }
+    if (blk == 0) kfr[slot] = k_frag(k1_, i);
+    else if (blk == 2) kfr[slot] = k_frag(k2_, i);
+    else kfr[slot] = v_frag(vc_, (blk == 3 ? 2 : 0) + i / ND, i % ND);
   };
   auto prime_ring = [&]() {
 #pragma unroll
     for (int c = 0; c < kPF; ++c) fetch(c, kh(0), kh(1), vc);
   };
-  // vload: byte offset of the V tile to prefetch (tile T2), tokload: first compacted row of the
-  // K tile whose rows are looked up (tile T4)
-  auto fast_iter = [&](const int vload, const int tokload) {
+  // v1: first key of the V tile to load (tile T1); tok3: first compacted row of the K tile whose rows are looked up (tile T3)
+  auto fast_iter = [&](const int v1, const int tok3) {
     float mxc[QS], mx[QS], ps0[QS], ps1[QS];
     f32x16 acc[QS];
 #pragma unroll
@@ -405,6 +404,10 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
       // prefetch kPF chunks ahead; the first chunks of the next iteration read the rotated slots
       if (c + kPF < kChunks) fetch(c + kPF, kh(0), kh(1), vc);
       else fetch(c + kPF - kChunks, kh(2), kh(3), vn);
+      // K(t+2) -> kh(3), kh(4), V(t+1) -> vn, then the look-ups of the K tile after that
+      if (c < CH) load_k(ktok, kh(3), kh(4), c);
+      else if (c < 2 * CH) load_v(v1, vn, c - CH);
+      else if (c == 2 * CH) fetch_tok(tok3, ktok);
       if (blk == 0 || blk == 2) {
         const f32x16 (&s_in)[QS] = blk == 0 ? sA : sB;
         uint32_t (&p_out)[QS][8] = blk == 0 ? pA : pB;
@@ -455,20 +458,6 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
           }
           if (qs + 1 < QS) __builtin_amdgcn_sched_barrier(0);
         }
-        // K(t+2) -> kh(3), kh(4), V(t+1) -> vn, then refill the registers
-        if (blk == 3 && i < CH) {
-          store_k_chunk(kh(3), kh(4), i, kreg[i]);
-          kreg[i] = __builtin_amdgcn_raw_buffer_load_b128(Kr, row_off(ktok[i]) + 16 * st_col, 0, 0);
-          if (i == CH - 1) fetch_tok(tokload, ktok);
-        }
-        if (blk == 3 && i >= CH && i < 2 * CH) {
-          *(u32x4*)(&vn[lv_off + (i - CH) * kVRowsPerPass * VS]) = vreg[i - CH];
-          vreg[i - CH] = __builtin_amdgcn_raw_buffer_load_b128(Vr, gv_off + (i - CH) * kThreads * 16, vload, 0);
-        }
-        if (FUSED && blk == 3 && i == kZChunk && zfill && --z_count <= 0) {
-          zero_step();
-          z_count = z_every;
-        }
         if (i == CPB - 1) {
 #pragma unroll
           for (int qs = 0; qs < QS; ++qs) mxc[qs] = fmaxf(mx[qs], __shfl_xor(mx[qs], 32));
@@ -479,10 +468,16 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
         raise_max_rel<ND, QS>(mxc, m, l, o, sB);
       }
     }
+    wait_loads();
+    // (behind the wait: the next one comes an iteration later, when the stores have long been acknowledged)
+    if (FUSED && zfill && --z_count <= 0) {
+      zero_step();
+      z_count = z_every;
+    }
     lds_barrier();
     raise_max_rel<ND, QS>(mxc, m, l, o, sA);
     rotate();
-    };
+  };
 
   // ---- tile loop.  A tile takes the pipelined iteration when it and the tile after it lie below
   // the workgroup's first row and are used by both halves of the workgroup (plain causal: every
@@ -499,10 +494,10 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
         for (int r = 0; r < 16; ++r) sA[qs][r] = fmaf(sA[qs][r], c_, -m[qs]);
       prime_ring();
       do {
-        const Tile T4 = gen.next();
+        const Tile T3 = gen.next();
         // tiles that do not exist are replaced by tile 0 in the prefetches: loaded, never used
-        fast_iter(max(T2.k0, 0) * ROWB, max(T4.k0, 0));
-        T0 = T1; T1 = T2; T2 = T3; T3 = T4;
+        fast_iter(max(T1.k0, 0), max(T3.k0, 0));
+        T0 = T1; T1 = T2; T2 = T3;
       } while (pipelined(T0) && pipelined(T1));
       if (T0.k0 < 0) break;
 #pragma unroll
@@ -510,28 +505,30 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
 #pragma unroll
         for (int r = 0; r < 16; ++r) sA[qs][r] = (sA[qs][r] + m[qs]) * inv_c;
     }
-    qk_half<D, QS>(kh(0), k_rd, qf, sB);
+    const Tile T3 = gen.next();
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      if (T2.k0 >= 0) load_k(ktok, kh(3), kh(4), i);
+      if (T1.k0 >= 0) load_v(T1.k0, vn, i);
+    }
+    if (T3.k0 >= 0) fetch_tok(T3.k0, ktok);
+    qk(kh(0), qf, sB);
     if (wave_active(T0)) {
       if (T0.k0 + BN - 1 > wrow0) mask_half<QS>(sB, T0.k0 + 32, hi, wrow0 + lo);
       softmax_exp<QS>(sA, c, m, l, pA);
-      pv_half<D, QS>(vc, v_rd, pA, o);
+      pv(vc, 0, pA);
       softmax_max<ND, QS>(sB, c, m, l, o);
       softmax_exp<QS>(sB, c, m, l, pB);
-      pv_half<D, QS>(vc + 32, v_rd, pB, o);
+      pv(vc, 1, pB);
     }
-    if (T1.k0 >= 0) qk_half<D, QS>(kh(1), k_rd, qf, sA);
+    if (T1.k0 >= 0) qk(kh(1), qf, sA);
     if (wave_active(T1)) {
       if (T1.k0 + 31 > wrow0) mask_half<QS>(sA, T1.k0, hi, wrow0 + lo);
       softmax_max<ND, QS>(sA, c, m, l, o);
     }
-    if (T2.k0 >= 0) store_k(kh(3), kh(4), kreg);
-    if (T1.k0 >= 0) store_v(vn, vreg);
-    if (T3.k0 >= 0) load_k(ktok, kreg);
-    if (T2.k0 >= 0) load_v(T2.k0, vreg);
-    const Tile T4 = gen.next();
-    if (T4.k0 >= 0) fetch_tok(T4.k0, ktok);
+    wait_loads();
     lds_barrier();
-    T0 = T1; T1 = T2; T2 = T3; T3 = T4;
+    T0 = T1; T1 = T2; T2 = T3;
     rotate();
   }
 
@@ -565,8 +562,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   // ---- epilogue: normalise, round to bf16, store the rows (RowOut).  The LDS is free: every wavefront is past the
   // barrier behind the last read of a tile.
   using Out = RowOut<D, ND, FUSED>;
-  static_assert(NW * Out::kLds <= (KRING * KHALF + 2 * VTILE) * 2, "the rows of all wavefronts fit the tile rings");
-  char* const lds_out = (char*)smem + wave * Out::kLds;
+  static_assert(NW * Out::kLds <= KRING * KHALF + 2 * VTILE, "the rows of all wavefronts fit the tile rings");
+  char* const lds_out = smem + wave * Out::kLds;
 #pragma unroll
   for (int qs = 0; qs < QS; ++qs) {
     const int row0 = wrow0 + 32 * qs;

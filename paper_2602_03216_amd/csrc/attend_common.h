@@ -101,6 +101,50 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// ---- tiles in LDS.  K and V^T tiles go from global memory straight into LDS: no staging registers, no LDS store
+// instructions.  Such a load writes the 64 lanes' 16-byte pieces to 1 KiB of consecutive addresses (a block: 8 or 4 rows of
+// 128 or 256 bytes), so rows cannot be padded; instead the pieces of a row are stored in an order that depends on the row
+// (piece p of row r at position p ^ swizzle, chosen on the global side of the load), and the blocks are kBlock
+// bytes apart.  With both, 16 consecutive rows put any one piece into 16 different positions of the 256 bytes that the banks
+// cover: row bits 0, 1 (256-byte rows) or 1, 2 (128-byte rows, whose bit 0 selects the half of the 256 bytes) go into
+// the low two bits of the position by the exclusive or, the next two (one) through the 64 bytes between blocks.
+// A fragment read of k-step i takes piece hi + 2 i: only bit 0 of i meets the swizzle, so two lane offsets and immediates
+// reach all of them.
+constexpr int kBlock = 1024 + 64;
+template <int RB>                                   // bytes of a row: 128 or 256
+struct LdsRows {
+  static constexpr int LPR = RB / 16, RPB = 64 / LPR;                        // pieces of a row, rows of a block
+  __device__ static __forceinline__ int swizzle(int row) { return RB == 256 ? row & 3 : (row >> 1) & 3; }
+  // global side: the piece of its row (row lane / LPR of the block) that lane `lane` of a load fetches
+  __device__ static __forceinline__ int piece(int lane) { return (lane % LPR) ^ swizzle(lane / LPR); }
+  // byte offset of piece hi (+ 2 i: read_off) of row `row`
+  __device__ static __forceinline__ int read_base(int row, int hi) { return (row / RPB) * kBlock + (row % RPB) * RB + ((hi ^ swizzle(row)) << 4); }
+  __device__ static __forceinline__ int read_off(const int (&base)[2], int i) { return base[i & 1] + 64 * (i >> 1); }
+};
+
+// One block: lane l's 16 bytes at (buffer + voff + soff) to LDS byte `lds` + 16 l.  Counted by vmcnt, by nothing the compiler
+// tracks: whoever reads the block waits (s_waitcnt vmcnt, then the workgroup barrier) himself.  In assembly because the
+// compiler, which cannot tell the slots of a ring apart, would wait for these loads before every fragment read; there is no
+// output register that it could reuse while the load is in flight.
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, int voff, int soff, int lds) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+#endif
+}
+// The descriptor of head_rsrc (below) as plain words.
+__device__ __forceinline__ u32x4 rsrc_words(const __bf16* base, long long bytes) {
+  const unsigned long long p = (unsigned long long)base;
+  return u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, (uint32_t)bytes, 0x00020000u};
+}
+
+// Every load of this wavefront has landed, in registers or in LDS.  The builtin is what the compiler sees; the scheduling
+// barriers keep it where it stands.
+__device__ __forceinline__ void wait_loads() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0)
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // Row stride (elements) of a V^T tile in LDS: [d][64 keys + pad].  A fragment read takes 16 bytes
 // per lane from 16 consecutive d-rows: 144-byte rows walk those lanes over all 64 banks.
 constexpr int VS = BN + 8;
