@@ -69,10 +69,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   // ---- workgroup -> (head, query tile).  Consecutive workgroup ids go to different XCDs, so
   // id % 8 picks the XCD; all tiles of a head (and all heads of a KV group) stay on one XCD to
   // share its L2, and the longest (last) query tiles are scheduled first.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int vhead = xcd * a.vheads_per_xcd + slot % a.vheads_per_xcd;
-  const int hp = vhead / a.head_split, part = vhead % a.head_split;
-  const int b = hp / a.Hq, h = hp % a.Hq;
+  int b, h, from_last;
+  workgroup_of(a, blockIdx.x, b, h, from_last);
   // Rows of this batch entry's compacted set: the launch's count, or (fused form with a coverage
   // budget decided on the device) the count read from k_dev; a.Lc stays the capacity, i.e. the row
   // stride of idx and of the tile arrays, and the grid is sized for it.
@@ -81,18 +79,16 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
     Lc = a.k_dev[b];
     nq_tiles = (Lc + BM - 1) / BM;
   }
-  const int qt = nq_tiles - 1 - ((slot / a.vheads_per_xcd) * a.head_split + part);
+  const int qt = nq_tiles - 1 - from_last;
   if (qt < 0) return;
-  const int g = a.Hq / a.kvh;
-  const int n_grp = FUSED ? a.Hkv : a.kvh, g_grp = a.Hq / n_grp;
   const long long bh = (long long)b * a.Hq + h;
-  const long long bkv = (long long)b * a.kvh + h / g;    // head of K^ / V^ (fused: of the index set and the V tiles)
+  const long long bkv = (long long)b * a.kvh + a.by_g.div(h);    // head of K^ / V^ (fused: of the index set and the V tiles)
   // rows of Q and K: the compacted tensors, or (fused) the original ones addressed through idx
   // (fused: row pitch and head offsets come from the caller's layout; byte offsets of a row fit 32 bits
   // and both factors of token * pitch fit 24 bits, checked on the host)
   const int q_pitch = FUSED ? (int)a.qs.l * 2 : ROWB, k_pitch = FUSED ? (int)a.ks.l * 2 : ROWB;
   const __bf16* q_head = FUSED ? a.Q + a.qs.head(b, h) : a.Q + bh * Lc * D;
-  const __bf16* k_head = FUSED ? a.K + a.ks.head(b, h / g_grp) : a.K + bkv * Lc * D;
+  const __bf16* k_head = FUSED ? a.K + a.ks.head(b, a.by_g_kv.div(h)) : a.K + bkv * Lc * D;
   const int n_rows = FUSED ? a.L : Lc;
   const __amdgpu_buffer_rsrc_t Qr = head_rsrc(q_head, (long long)n_rows * q_pitch);
   const u32x4 Kr = rsrc_words(k_head, (long long)n_rows * k_pitch);
@@ -124,21 +120,21 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   const int32_t* inv_row = nullptr;
   u32x4* zrow = nullptr;
   int z_hi = 0, zt = 0, zr[ZR] = {};                     // end of the range, next rows of this thread, their inv entries
-  int z_every = 1, z_count = 1, z_passes = 1;
-  if (zfill) {
+  int z_every = 1, z_count = 1;
+  auto start_zero_rows = [&](int n_pipelined) {
     inv_row = a.inv + bkv * a.L;
     // Token range of this workgroup.  Any partition of [0, L) over the query tiles of a head works (a row is
     // cleared iff inv marks it unselected, whoever looks).  The shares grow linearly with the query tile,
     // as the number of tile iterations does, so that every workgroup can clear its share inside its loop.
-    const long long nq = nq_tiles, wt = nq * (nq + 1) / 2;
-    const int tok_lo = (int)((long long)a.L * ((long long)qt * (qt + 1) / 2) / wt);
-    z_hi = (int)((long long)a.L * ((long long)(qt + 1) * (qt + 2) / 2) / wt);
+    const int tok_lo = zero_bound(a.L, nq_tiles, qt);
+    z_hi = zero_bound(a.L, nq_tiles, qt + 1);
     zrow = (u32x4*)(a.Of + a.os.head(b, h)) + (tid % LPR);
     zt = tok_lo + tid / LPR;
 #pragma unroll
     for (int j = 0; j < ZR; ++j) zr[j] = zt + j * RPT < z_hi ? inv_row[zt + j * RPT] : 0;
-    z_passes = (z_hi - tok_lo + RPP - 1) / RPP;
-  }
+    // as evenly over the pipelined iterations as their number allows (RPP is a power of two)
+    z_every = max(1, (int)((float)n_pipelined / (float)max(1, (z_hi - tok_lo + RPP - 1) / RPP)));
+  };
   auto zero_step = [&]() {
 #pragma unroll
     for (int j = 0; j < ZR; ++j)
@@ -178,12 +174,6 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
         longest_list = max(longest_list, gen.cnt[j]);
       }
     }
-  }
-
-  // zero rows: as evenly over the pipelined iterations as their number allows
-  if (zfill) {
-    const int n_pipelined = gen.plain ? q0 / BN - 1 : gen.tiles_per_block * longest_list - 6;
-    z_every = max(1, n_pipelined / max(1, z_passes));
   }
 
   // ---- staging: global memory -> LDS, in blocks of 1 KiB (LdsRows); wavefront w takes blocks CH w .. CH w + CH - 1 of
@@ -316,6 +306,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
 #pragma unroll
     for (int i = 0; i < CH; ++i) load_v(max(T0.k0, 0), vc, i);
   }
+  // (the zero rows' first look-ups while those are under way)
+  if (zfill) start_zero_rows(gen.plain ? q0 / BN - 1 : gen.tiles_per_block * longest_list - 6);
   // Everything has landed (the next wait for loads is at the end of the first iteration; and the compiler must know that the
   // Q fragments and look-ups have, or it would carry them as "possibly pending" into the loop).
   wait_loads();

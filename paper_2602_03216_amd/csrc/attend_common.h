@@ -39,7 +39,9 @@ struct AttendArgs {
   int max_blocks;
   int block;                   // block size of the list: 64, 128 or 256 tokens
   int BH, Hq, kvh, Lc, nq_tiles, nk_tiles;
-  int head_split, vheads_per_xcd;   // workgroup -> (head, query tile) map, see map_workgroups()
+  int split_log2, vheads_per_xcd;   // workgroup -> (head, query tile) map, see map_workgroups()
+  FastDiv by_vheads, by_Hq;    // ... its divisions
+  FastDiv by_g, by_g_kv;       // query heads per head of V^ (and index set), per head of K
   const int32_t* k_dev;        // fused form: compacted rows per batch entry, decided on the device (NULL: Lc)
   Strides qs, ks, os;          // fused form: layouts of the original Q, K and of the full-length output (elements)
   float c;                     // scale * log2(e)
@@ -63,18 +65,41 @@ struct AttendArgs {
 // A head's query tiles stay on one XCD (they stream the same K / V through its L2), consecutive heads (the
 // heads of a KV group) share an XCD, and the longest (last) query tiles are scheduled first.  When the number
 // of heads is no multiple of 8, whole heads per XCD would leave some XCDs with one head more than others (28
-// heads: four against three, a launch 14 % longer than its work); every head is then cut into `head_split`
-// parts (query tiles qt with (nq - 1 - qt) % head_split == part), so that the B * Hq * head_split parts
+// heads: four against three, a launch 14 % longer than its work); every head is then cut into
+// 1 << split_log2 parts (query tiles qt with (nq - 1 - qt) % parts == part; 2, 4 or 8 of them), so that all the parts
 // divide evenly: XCD x takes parts [x * vheads_per_xcd, (x + 1) * vheads_per_xcd), i.e. whole heads and at
 // most two partial ones.
 inline void map_workgroups(AttendArgs& a) {
-  int g = 8;
-  while (a.BH % g) g >>= 1;                       // gcd(BH, 8)
-  a.head_split = 8 / g;
+  int g = 8, log2 = 0;
+  while (a.BH % g) { g >>= 1; ++log2; }           // gcd(BH, 8)
+  a.split_log2 = log2;
   a.vheads_per_xcd = a.BH / g;
+  const uint64_t heads = (uint64_t)a.BH;
+  a.by_vheads = FastDiv(a.vheads_per_xcd, (uint64_t)a.vheads_per_xcd * (a.nq_tiles + 1));
+  a.by_Hq = FastDiv(a.Hq, heads);
+  a.by_g = FastDiv(a.Hq / a.kvh, a.Hq);
+  a.by_g_kv = FastDiv(a.Hq / a.Hkv, a.Hq);
 }
 inline unsigned grid_for(const AttendArgs& a) {
-  return 8u * (unsigned)a.vheads_per_xcd * (unsigned)((a.nq_tiles + a.head_split - 1) / a.head_split);
+  return 8u * (unsigned)a.vheads_per_xcd * (unsigned)((a.nq_tiles + (1 << a.split_log2) - 1) >> a.split_log2);
+}
+
+// The map on the device: head b, h and the number of the query tile counted from the last one.
+__device__ __forceinline__ void workgroup_of(const AttendArgs& a, unsigned id, int& b, int& h, int& from_last) {
+  const unsigned xcd = id & 7u, slot = id >> 3;
+  const unsigned rank = a.by_vheads.div(slot), vhead = xcd * a.vheads_per_xcd + (slot - rank * a.vheads_per_xcd);
+  const unsigned hp = vhead >> a.split_log2, part = vhead & ((1u << a.split_log2) - 1u);
+  const unsigned b_ = a.by_Hq.div(hp);
+  b = (int)b_;
+  h = (int)(hp - b_ * a.Hq);
+  from_last = (int)((rank << a.split_log2) + part);
+}
+// First token of query tile t's share of the zero rows, of nq tiles (see attend.hip): one function of the tile for both
+// neighbours, monotone in float arithmetic too.
+__device__ __forceinline__ int zero_bound(int L, int nq, int t) {
+  if (t >= nq) return L;
+  const float per = (float)L / ((float)nq * (float)(nq + 1));
+  return min((int)((float)t * (float)(t + 1) * per), L);
 }
 
 // two bf16 in one dword: widen to fp32 (exact), add, round each sum to bf16 (nearest even)

@@ -51,24 +51,20 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   constexpr int NKT = 5, NVT = 4;                 // ring slots
   __shared__ __attribute__((aligned(16))) __bf16 smem[NKT * KTILE + NVT * VTILE];
 
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int vhead = xcd * a.vheads_per_xcd + slot % a.vheads_per_xcd;
-  const int hp = vhead / a.head_split, part = vhead % a.head_split;
-  const int b = hp / a.Hq, h = hp % a.Hq;
+  int b, h, from_last;
+  workgroup_of(a, blockIdx.x, b, h, from_last);
   int Lc = a.Lc, nq_tiles = a.nq_tiles;
   if (FUSED && a.k_dev) {
     Lc = a.k_dev[b];
     nq_tiles = (Lc + BMS - 1) / BMS;
   }
-  const int qt = nq_tiles - 1 - ((slot / a.vheads_per_xcd) * a.head_split + part);
+  const int qt = nq_tiles - 1 - from_last;
   if (qt < 0) return;
-  const int g = a.Hq / a.kvh;
-  const int n_grp = FUSED ? a.Hkv : a.kvh, g_grp = a.Hq / n_grp;
   const long long bh = (long long)b * a.Hq + h;
-  const long long bkv = (long long)b * a.kvh + h / g;
+  const long long bkv = (long long)b * a.kvh + a.by_g.div(h);
   const int q_pitch = FUSED ? (int)a.qs.l * 2 : ROWB, k_pitch = FUSED ? (int)a.ks.l * 2 : ROWB;
   const __bf16* q_head = FUSED ? a.Q + a.qs.head(b, h) : a.Q + bh * Lc * D;
-  const __bf16* k_head = FUSED ? a.K + a.ks.head(b, h / g_grp) : a.K + bkv * Lc * D;
+  const __bf16* k_head = FUSED ? a.K + a.ks.head(b, a.by_g_kv.div(h)) : a.K + bkv * Lc * D;
   const int n_rows = FUSED ? a.L : Lc;
   const __amdgpu_buffer_rsrc_t Qr = head_rsrc(q_head, (long long)n_rows * q_pitch);
   const __amdgpu_buffer_rsrc_t Kr = head_rsrc(k_head, (long long)n_rows * k_pitch);
@@ -95,20 +91,16 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   const int32_t* inv_row = nullptr;
   u32x4* zrow = nullptr;
   int z_hi = 0, zt = 0, zr = 0;
-  int z_every = 1, z_count = 1, z_passes = 1;
-  if (zfill) {
+  int z_every = 1, z_count = 1;
+  auto start_zero_rows = [&](int n_pipelined) {
     inv_row = a.inv + bkv * a.L;
-    // Token range of this workgroup.  Any partition of [0, L) over the query tiles of a head works (a row is
-    // cleared iff inv marks it unselected, whoever looks).  The shares grow linearly with the query tile,
-    // as the number of tile iterations does, so that every workgroup can clear its share inside its loop.
-    const long long nq = nq_tiles, wt = nq * (nq + 1) / 2;
-    const int tok_lo = (int)((long long)a.L * ((long long)qt * (qt + 1) / 2) / wt);
-    z_hi = (int)((long long)a.L * ((long long)(qt + 1) * (qt + 2) / 2) / wt);
+    const int tok_lo = zero_bound(a.L, nq_tiles, qt);
+    z_hi = zero_bound(a.L, nq_tiles, qt + 1);
     zrow = (u32x4*)(a.Of + a.os.head(b, h)) + (tid % LPR);
     zt = tok_lo + tid / LPR;
     zr = zt < z_hi ? inv_row[zt] : 0;
-    z_passes = (z_hi - tok_lo + RPP - 1) / RPP;
-  }
+    z_every = max(1, (int)((float)n_pipelined / (float)max(1, (z_hi - tok_lo + RPP - 1) / RPP)));
+  };
   auto zero_step = [&]() {
     if (zr < 0) __builtin_nontemporal_store(u32x4{0u, 0u, 0u, 0u}, zrow + (long long)zt * o_pitch16);
     zt += RPP;
@@ -153,10 +145,6 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
     s.b = s.a.k0 >= 0 ? gen.next() : Tile{-1, 0};
     return s;
   };
-  if (zfill) {
-    const int n_pipelined = gen.plain ? q0 / (2 * BN) - 1 : gen.tiles_per_block * longest_list / 2 - 3;
-    z_every = max(1, n_pipelined / max(1, z_passes));
-  }
 
   // ---- staging: global -> registers -> LDS in 16-byte chunks, two K tiles and two V tiles per step
   constexpr int kRowsPerPass = kThreads / (D / 8);
@@ -267,6 +255,9 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
     load_k(k1tok[1], kreg1[1]);
     load_k(k2tok[0], kreg[0]);
     load_k(k2tok[1], kreg[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    // (the zero rows' first look-ups while those are under way)
+    if (zfill) start_zero_rows(gen.plain ? q0 / (2 * BN) - 1 : gen.tiles_per_block * longest_list / 2 - 3);
     __builtin_amdgcn_sched_barrier(0);
     store_v(va0, vreg0[0]);
     store_v(vb0, vreg0[1]);

@@ -187,8 +187,8 @@ __global__ __launch_bounds__(kThreads) void residual_kernel(
 __global__ __launch_bounds__(64) void v_tile_kernel(VTiles a, const int32_t* idx, int k, const int32_t* k_dev) {
   __shared__ __attribute__((aligned(16))) char lds[kVtLds];
   const long long row = blockIdx.y;
-  const int tile = blockIdx.x / a.halves, half = blockIdx.x % a.halves;
-  const int n = k_dev ? k_dev[(int)row / a.rows_per_b] : k;
+  const int tile = blockIdx.x >> (a.halves - 1), half = blockIdx.x & (a.halves - 1);
+  const int n = k_dev ? k_dev[a.by_b.div((uint32_t)row)] : k;
   if (tile * kKeyTile >= n) return;          // past this batch entry's count
   v_half_tile(a, row, tile, half, idx ? idx + row * k : nullptr, n, threadIdx.x, lds);
 }
@@ -215,7 +215,9 @@ hipError_t launch_v_tiles(int B, int kv_heads, int Lc, int d, const void* V, voi
   VTiles a;
   a.V = (const __bf16*)V; a.Vt = (__bf16*)Vt;
   a.vs = Strides{(long long)kv_heads * Lc * d, (long long)Lc * d, (long long)d};
-  a.rows_per_b = kv_heads; a.rows_per_kv = 1;
+  a.rows_per_b = kv_heads;
+  a.by_b = FastDiv(kv_heads, (uint64_t)B * kv_heads);
+  a.by_kv = FastDiv(1, kv_heads);
   a.nk_tiles = (Lc + kKeyTile - 1) / kKeyTile;
   a.halves = d / 64;
   const dim3 grid((unsigned)(a.nk_tiles * a.halves), (unsigned)(B * kv_heads));

@@ -59,6 +59,8 @@ struct ScoreArgs {
   float2* part;       // [B*Hq][nchunks][QP] (max, sum) in the log2 domain
   float* lse2;        // [B*Hq][QP]
   int Hq, Hkv, L, Lq, nchunks, chunk;      // chunk = keys per workgroup
+  int g;              // query heads per KV head
+  FastDiv by_Hkv;
   int pool_w;
   float* pooled;      // final output when pool_w > 1 (scores then points at a raw buffer)
   float c;            // scale * log2(e)
@@ -383,8 +385,8 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass1(ScoreA
   __shared__ float2 red[kWaves][QP];
   const int chunk = blockIdx.x;
   const int bkv = blockIdx.y;                            // (batch entry, KV head): 32-bit index arithmetic, no 64-bit division
-  const int kv = bkv % a.Hkv, b = bkv / a.Hkv;
-  const int g = a.Hq / a.Hkv;
+  const int b = (int)a.by_Hkv.div(bkv), kv = bkv - b * a.Hkv;
+  const int g = a.g;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
   const WaveRole role = wave_role<HPW>(wave);
   const int c_begin = chunk * a.chunk, c_end = min(c_begin + a.chunk, a.L);
@@ -559,8 +561,8 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
   // (268 MB at 128K tokens x 8 KV heads) does not fit it.
   const int chunk = (int)(gridDim.x - 1 - blockIdx.x);
   const int bkv = (int)(gridDim.y - 1 - blockIdx.y);
-  const int kv = bkv % a.Hkv, b = bkv / a.Hkv;
-  const int g = a.Hq / a.Hkv;
+  const int b = (int)a.by_Hkv.div(bkv), kv = bkv - b * a.Hkv;
+  const int g = a.g;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
   const WaveRole role = wave_role<HPW>(wave);
   const int c_begin = chunk * a.chunk, c_end = min(c_begin + a.chunk, a.L);
@@ -748,6 +750,8 @@ hipError_t launch_common(const Dims& dm, ScoreArgs& a, const void* K, float* sco
   a.K = (const __bf16*)K; a.scores = scores;
   a.ks = dm.kv;
   a.Hq = dm.Hq; a.Hkv = dm.Hkv; a.L = dm.L; a.Lq = dm.last_q;
+  a.g = dm.Hq / dm.Hkv;
+  a.by_Hkv = FastDiv(dm.Hkv, (uint64_t)dm.B * dm.Hkv);
   a.chunk = chunk_for(dm);
   a.nchunks = (dm.L + a.chunk - 1) / a.chunk;
   a.c = dm.scale * kLog2e;

@@ -18,6 +18,8 @@
 // threads each), sized so that a launch has about 512 workgroups: each of the five small kernels
 // is a chain of dependent steps per thread, so it pays to spread it over the whole chip, but not
 // to go below a few tokens per thread.
+#include <algorithm>
+
 #include "v_tiles.h"
 
 namespace tsa {
@@ -60,12 +62,14 @@ struct SelArgs {
   // Count decided on the device (dynamic coverage budget): k_dev[b] replaces k for the rows of batch
   // entry b (NULL: every row takes k); a row of idx is k_stride entries long either way.
   const int32_t* k_dev;
-  int k_stride, rows_per_b;
+  int k_stride;
+  FastDiv by_b;               // batch entry of a row
   // select_row_kernel only: `parts` workgroups share a row; with tiles.Vt they also gather the row's V tiles
   int parts, n_rows;
+  FastDiv by_parts;
   VTiles tiles;
   __device__ __forceinline__ uint32_t k_of(long long row) const {
-    return (uint32_t)(k_dev ? k_dev[row / rows_per_b] : k);
+    return (uint32_t)(k_dev ? k_dev[by_b.div((uint32_t)row)] : k);
   }
 };
 
@@ -370,8 +374,9 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
   // workgroups of a row share an L2
   const unsigned at = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   if (at >= (unsigned)(a.n_rows * a.parts)) return;
-  const long long row = at / (unsigned)a.parts;
-  const int part = at % (unsigned)a.parts;
+  const unsigned row_ = a.by_parts.div(at);
+  const long long row = row_;
+  const int part = (int)(at - row_ * a.parts);
   const float* s = a.scores + row * g * a.L;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int t0 = wave * 256 * J + 4 * lane;
@@ -599,7 +604,7 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
   int32_t* out_inv = a.inv ? a.inv + row * a.L : nullptr;
   // this workgroup's share of the row: whole tiles of idx, every parts-th step of inv
   const uint32_t n_tiles = (k_row + kKeyTile - 1) / kKeyTile;
-  const uint32_t tile_lo = n_tiles * part / a.parts, tile_hi = n_tiles * (part + 1) / a.parts;
+  const uint32_t tile_lo = a.by_parts.div(n_tiles * part), tile_hi = a.by_parts.div(n_tiles * (part + 1));
   const uint32_t pos_lo = tile_lo * kKeyTile, pos_n = (tile_hi - tile_lo) * kKeyTile;
   asm volatile("" : "+s"(T));                              // the comparisons below are made afresh: 8 J masks do not fit the scalar registers
 #pragma unroll
@@ -643,7 +648,8 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
         ++pos;
       }
     }
-    if (out_inv && (wave * J + j) % a.parts == part) {
+    const uint32_t step = wave * J + j;
+    if (out_inv && step - a.by_parts.div(step) * a.parts == (uint32_t)part) {
       if (t + 3 < a.L) *(u32x4_a4*)(out_inv + t) = iv;
       else {
 #pragma unroll
@@ -658,7 +664,7 @@ __global__ __launch_bounds__(kThreads) void select_row_kernel(SelArgs a, int g) 
   __syncthreads();                                         // the share of idx is written: all of this workgroup's wavefronts read it
   const uint32_t halves = (tile_hi - tile_lo) * a.tiles.halves;
   for (uint32_t i = wave; i < halves; i += kWaves)
-    v_half_tile(a.tiles, row, tile_lo + i / a.tiles.halves, i % a.tiles.halves, out_idx, (int)k_row, lane, vt_lds + wave * kVtLds);
+    v_half_tile(a.tiles, row, tile_lo + (i >> (a.tiles.halves - 1)), i & (a.tiles.halves - 1), out_idx, (int)k_row, lane, vt_lds + wave * kVtLds);
 }
 
 // J with 4096 J >= L, from the built ones
@@ -713,7 +719,8 @@ hipError_t launch_select(const Dims& dm, const float* scores, int k_keep, int32_
   a.scores = scores;
   a.idx = idx; a.inv = inv;
   a.L = dm.L; a.k = k_keep; a.ff = dm.force_first; a.fl = dm.force_last; a.nslices = n_slices(dm);
-  a.k_dev = k_dev; a.k_stride = k_keep; a.rows_per_b = rows / dm.B;
+  a.k_dev = k_dev; a.k_stride = k_keep;
+  a.by_b = FastDiv(rows / dm.B, rows);
   a.slice = slice_for(dm);
   int g = dm.group_mode ? dm.Hq / dm.Hkv : 1;
   const bool one_launch = dm.L <= row_max_tokens(rows);
@@ -729,6 +736,7 @@ hipError_t launch_select(const Dims& dm, const float* scores, int k_keep, int32_
     a.tiles = v_tiles_of(dm, k_keep, V, with_tiles ? Vt : nullptr);
     a.n_rows = rows;
     a.parts = with_tiles ? min(kCUs / rows, a.tiles.nk_tiles) : 1;
+    a.by_parts = FastDiv(a.parts, (uint64_t)std::max(rows + 8, a.tiles.nk_tiles + 64) * a.parts);
     run_select_row(a, g, st);
     if (Vt && !with_tiles) return launch_compress_v_tiles(dm, V, idx, k_keep, Vt, st, k_dev);
     return hipGetLastError();

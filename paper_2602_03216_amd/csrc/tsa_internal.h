@@ -44,6 +44,19 @@ struct Dims {
   Strides q, kv, o;            // Q; K and V; O
 };
 
+// Division by a number the host knows, one multiplication on the device (an integer division is some thirty dependent
+// instructions, and a workgroup has several of them in front of its first load; with the attention's zero-row set-up behind
+// its first requests, layer of 256 of 1024 tokens x 4 heads 30.9 -> 29.6 us, 901 of 3001 x 32 54.1 -> 52.9).  m = ceil(2^32 / d): exact for n d < 2^32;
+// beyond that, and for d = 1, m = 0 and the device divides.
+struct FastDiv {
+  uint32_t d, m;
+  FastDiv() = default;
+  FastDiv(uint32_t d_, uint64_t n_max) : d(d_), m(d_ > 1 && n_max * d_ < (1ull << 32) ? (uint32_t)(((1ull << 32) + d_ - 1) / d_) : 0u) {}
+#if defined(__HIPCC__)
+  __device__ __forceinline__ uint32_t div(uint32_t n) const { return m ? __umulhi(n, m) : d == 1u ? n : n / d; }
+#endif
+};
+
 // ---- launchers (each returns hipGetLastError() after queuing its kernels) ----
 
 // score.hip

@@ -12,8 +12,9 @@ struct VTiles {
   const __bf16* V;
   __bf16* Vt;                 // [rows][nk_tiles][D][kKeyTile]; NULL: no tiles wanted
   Strides vs;                 // layout of V, in elements
-  int rows_per_b, rows_per_kv;   // tile rows (index sets, or heads) per batch entry and per KV head
-  int nk_tiles, halves;       // tiles per row; halves = D / 64
+  int rows_per_b;             // tile rows (index sets, or heads) per batch entry
+  FastDiv by_b, by_kv;        // batch entry of a tile row; KV head of a tile row of its batch entry
+  int nk_tiles, halves;       // tiles per row; halves = D / 64 (1 or 2)
 };
 
 // Tiles of the rows that an index set selects: one tile row per set.
@@ -21,7 +22,8 @@ inline VTiles v_tiles_of(const Dims& dm, int k_keep, const void* V, void* Vt) {
   VTiles t;
   t.V = (const __bf16*)V; t.Vt = (__bf16*)Vt; t.vs = dm.kv;
   t.rows_per_b = dm.group_mode ? dm.Hkv : dm.Hq;
-  t.rows_per_kv = dm.group_mode ? 1 : dm.Hq / dm.Hkv;
+  t.by_b = FastDiv(t.rows_per_b, (uint64_t)dm.B * t.rows_per_b);
+  t.by_kv = FastDiv(dm.group_mode ? 1 : dm.Hq / dm.Hkv, t.rows_per_b);
   t.nk_tiles = (k_keep + kKeyTile - 1) / kKeyTile;
   t.halves = dm.d / 64;
   return t;
@@ -37,7 +39,7 @@ constexpr int kVtLds = 8192;   // bytes of LDS a wavefront uses in v_half_tile
 __device__ __forceinline__ void v_half_tile(const VTiles& a, long long row, int tile, int half, const int32_t* idx, int n, int lane,
                                             char* lds) {
   const int col = lane & 7, oct = lane >> 3, r0 = tile * kKeyTile + 8 * oct;
-  const int b = (int)row / a.rows_per_b, kv = ((int)row % a.rows_per_b) / a.rows_per_kv;
+  const int b = (int)a.by_b.div((uint32_t)row), kv = (int)a.by_kv.div((uint32_t)row - b * a.rows_per_b);
   const __bf16* head = a.V + a.vs.head(b, kv) + 64 * half + 8 * col;
   const bool whole = tile * kKeyTile + kKeyTile <= n;      // the same for the whole wavefront
   int tok[8];
