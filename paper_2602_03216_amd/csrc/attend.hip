@@ -56,10 +56,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   constexpr int kThreads = 64 * NW;
   constexpr int RW = 32 * QS;                     // query rows per wavefront
   constexpr int BM = RW * NW;                     // query rows per workgroup
-  using KRows = LdsRows<2 * D>;                   // K tile: [key][d]
-  using VRows = LdsRows<2 * BN>;                  // V^T tile: [d][key]
-  constexpr int KHALF = 32 / KRows::RPB * kBlock, VTILE = D / VRows::RPB * kBlock;   // bytes of half a K tile, of a V^T tile
-  constexpr int CH = BN * D / (512 * NW);         // blocks (of 512 elements) of a tile that a wavefront loads
+  using Stg = Stage<D, NW>;
+  constexpr int KHALF = Stg::KHALF, VTILE = Stg::VTILE, CH = Stg::CH;
   constexpr int NS = D / 16;                      // MFMA k-steps of the QK product
   constexpr int ND = D / 32;                      // d sub-tiles of the output
   constexpr int ROWB = D * 2;                     // bytes of one row in global memory
@@ -176,69 +174,16 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
     }
   }
 
-  // ---- staging: global memory -> LDS, in blocks of 1 KiB (LdsRows); wavefront w takes blocks CH w .. CH w + CH - 1 of
-  // either tile.  Row R of the K tile in LDS need not be key R: what a lane loads is chosen so that its CH rows are
-  // CH consecutive keys (one look-up in idx for all of them), and the fragment reads undo that together with k_row_perm.
-  // A V^T tile is one contiguous [d][64] block of the tiled tensor.  Offsets that all lanes share go into the scalar
-  // offset of the load.
-  const int uwave = __builtin_amdgcn_readfirstlane(wave);
-  const int st_row = CH * (tid / KRows::LPR), st_col = 16 * KRows::piece(lane);      // keys st_row .. st_row + CH - 1 of the tile, byte in the row
-  constexpr int kHalfBlocks = 32 / KRows::RPB;
-  const bool st_half = uwave * CH >= kHalfBlocks;                                    // (a wavefront's blocks lie in one half tile)
-  const int st_lds = (uwave * CH % kHalfBlocks) * kBlock;
-  const int gv_off = (lane / VRows::LPR) * 2 * BN + 16 * VRows::piece(lane);
-  const int gv_block = uwave * CH * 1024, lv_block = uwave * CH * kBlock;
-  const int lds0 = (int)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  // ---- staging: global memory -> LDS
+  Stg stg;
+  stg.init(smem, tid);
   // Rows of the next K tile to be loaded: ktok[i] = row of thread chunk i (fused: the token the
   // compacted row stands for, fetched from idx one tile ahead of the K load that uses it).
   int ktok[CH];
   auto row_off = [&](int tok) -> int { return FUSED ? (int)__umul24(tok, k_pitch) : tok * ROWB; };
-  auto fetch_tok = [&](int k0, int (&ktok)[CH]) {
-    if (FUSED) {
-      if (CH == 4) {
-        const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(Ir, st_row * 4, k0 * 4, 0);
-#pragma unroll
-        for (int i = 0; i < CH; ++i) ktok[i] = t[i & 3];
-      } else if (CH == 2) {
-        const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(Ir, st_row * 4, k0 * 4, 0);
-#pragma unroll
-        for (int i = 0; i < CH; ++i) ktok[i] = t[i & 1];
-      } else {
-        ktok[0] = __builtin_amdgcn_raw_buffer_load_b32(Ir, st_row * 4, k0 * 4, 0);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < CH; ++i) ktok[i] = k0 + st_row + i;
-    }
-  };
-  // block i of this wavefront's share (half0, half1, dst: slots of the rings, bytes)
-  auto load_k = [&](const int (&ktok)[CH], int half0, int half1, int i) {
-    load_to_lds(Kr, row_off(ktok[i]) + st_col, 0, lds0 + (st_half ? half1 : half0) + st_lds + i * kBlock);
-  };
-  auto load_v = [&](int k0, int dst, int i) { load_to_lds(Vr, gv_off, k0 * ROWB + gv_block + i * 1024, lds0 + dst + lv_block + i * kBlock); };
-
-  // LDS read bases.  K operand (A of S^T): MFMA row lo = key k_row_perm(lo) of the half tile, 8 d-values at 8*hi.
-  const int k_key = k_row_perm(lo);
-  constexpr int GR = KRows::RPB * CH;             // keys that a wavefront loads
-  const int k_ldsrow = (k_key & ~(GR - 1)) | ((k_key & (CH - 1)) * KRows::RPB) | ((k_key & (GR - 1)) / CH);
-  const int kb0 = KRows::read_base(k_ldsrow, hi);
-  // V^T operand (A of O^T): row = d (lo within the 32-row d sub-tile), 8 keys at 8*hi.
-  const int vb0 = VRows::read_base(lo, hi);
-  const int k_rd[2] = {kb0, kb0 ^ 32}, v_rd[2] = {vb0, vb0 ^ 32};
-  constexpr int VSUB = 32 / VRows::RPB * kBlock;  // bytes between d sub-tiles
-  auto k_frag = [&](int half, int i) -> bf16x8 { return *(const bf16x8*)(smem + half + KRows::read_off(k_rd, i)); };
-  // 16 keys from 16 hf on, d sub-tile dt (hf 0 .. 3 over the tile's 64 keys)
-  auto v_frag = [&](int tile, int hf, int dt) -> bf16x8 { return *(const bf16x8*)(smem + tile + VRows::read_off(v_rd, hf) + dt * VSUB); };
-  auto qk = [&](int half, const bf16x8 (&qf)[QS][NS], f32x16 (&s)[QS]) {
-#pragma unroll
-    for (int qs = 0; qs < QS; ++qs) s[qs] = f32x16{0};
-#pragma unroll
-    for (int st = 0; st < NS; ++st) {
-      const bf16x8 kf = k_frag(half, st);
-#pragma unroll
-      for (int qs = 0; qs < QS; ++qs) s[qs] = mfma32(kf, qf[qs][st], s[qs]);
-    }
-  };
+  auto fetch_tok = [&](int k0, int (&tok)[CH]) { stg.template look_up<FUSED>(Ir, k0, tok); };
+  auto load_k = [&](const int (&tok)[CH], int half0, int half1, int i) { stg.load_k(Kr, row_off(tok[i]), half0, half1, i); };
+  auto load_v = [&](int k0, int tile, int i) { stg.load_v(Vr, k0, tile, i); };
 
   f32x16 o[QS][ND];
   float m[QS], l[QS];
@@ -312,19 +257,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   // Q fragments and look-ups have, or it would carry them as "possibly pending" into the loop).
   wait_loads();
   lds_barrier();
-  if (T0.k0 >= 0) qk(k_first(), qf, sA);
+  if (T0.k0 >= 0) stg.template qk<QS>(k_first(), qf, sA);
   if (NW != 8) lds_barrier();                            // that slot is written in the first iteration
-  // O^T += V^T P^T for half `half` of a tile (two MFMA k-steps of 16 keys)
-  auto pv = [&](int tile, int half, const uint32_t (&pb)[QS][8]) {
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-      for (int dt = 0; dt < ND; ++dt) {
-        const bf16x8 vf = v_frag(tile, 2 * half + hf, dt);
-#pragma unroll
-        for (int qs = 0; qs < QS; ++qs) o[qs][dt] = mfma32(vf, p_operand(pb[qs], hf), o[qs][dt]);
-      }
-  };
   auto wave_active = [&](const Tile& t) -> bool { return t.k0 >= 0 && (t.use & half_bit) && t.k0 <= wrow0 + RW - 1; };
   if (wave_active(T0)) {
     if (T0.k0 + 31 > wrow0) mask_half<QS>(sA, T0.k0, hi, wrow0 + lo);
@@ -371,9 +305,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   // fragment fetch for chunk c of the iteration whose half tiles of K and tile of V sit in (k1_, k2_, vc_)
   auto fetch = [&](int c, int k1_, int k2_, int vc_) {
     const int blk = c / CPB, i = c % CPB, slot = c % kRing;
-    if (blk == 0) kfr[slot] = k_frag(k1_, i);
-    else if (blk == 2) kfr[slot] = k_frag(k2_, i);
-    else kfr[slot] = v_frag(vc_, (blk == 3 ? 2 : 0) + i / ND, i % ND);
+    if (blk == 0) kfr[slot] = stg.k_frag(k1_, i);
+    else if (blk == 2) kfr[slot] = stg.k_frag(k2_, i);
+    else kfr[slot] = stg.v_frag(vc_, (blk == 3 ? 2 : 0) + i / ND, i % ND);
   };
   auto prime_ring = [&]() {
 #pragma unroll
@@ -504,16 +438,16 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
       if (T1.k0 >= 0) load_v(T1.k0, vn, i);
     }
     if (T3.k0 >= 0) fetch_tok(T3.k0, ktok);
-    qk(kh(0), qf, sB);
+    stg.template qk<QS>(kh(0), qf, sB);
     if (wave_active(T0)) {
       if (T0.k0 + BN - 1 > wrow0) mask_half<QS>(sB, T0.k0 + 32, hi, wrow0 + lo);
       softmax_exp<QS>(sA, c, m, l, pA);
-      pv(vc, 0, pA);
+      stg.template pv<QS>(vc, 0, pA, o);
       softmax_max<ND, QS>(sB, c, m, l, o);
       softmax_exp<QS>(sB, c, m, l, pB);
-      pv(vc, 1, pB);
+      stg.template pv<QS>(vc, 1, pB, o);
     }
-    if (T1.k0 >= 0) qk(kh(1), qf, sA);
+    if (T1.k0 >= 0) stg.template qk<QS>(kh(1), qf, sA);
     if (wave_active(T1)) {
       if (T1.k0 + 31 > wrow0) mask_half<QS>(sA, T1.k0, hi, wrow0 + lo);
       softmax_max<ND, QS>(sA, c, m, l, o);

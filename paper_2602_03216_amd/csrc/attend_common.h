@@ -153,13 +153,16 @@ struct LdsRows {
 // output register that it could reuse while the load is in flight.
 __device__ __forceinline__ void load_to_lds(u32x4 rsrc, int voff, int soff, int lds) {
 #if defined(__HIP_DEVICE_COMPILE__)
+  soff = __builtin_amdgcn_readfirstlane(soff);           // (the same in all lanes already; nothing where the compiler knows)
+  lds = __builtin_amdgcn_readfirstlane(lds);
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 #endif
 }
 // The descriptor of head_rsrc (below) as plain words.
 __device__ __forceinline__ u32x4 rsrc_words(const __bf16* base, long long bytes) {
   const unsigned long long p = (unsigned long long)base;
-  return u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, (uint32_t)bytes, 0x00020000u};
+  const auto scalar = [](uint32_t x) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+  return u32x4{scalar((uint32_t)p), scalar((uint32_t)(p >> 32) & 0xffffu), scalar((uint32_t)bytes), 0x00020000u};
 }
 
 // Every load of this wavefront has landed, in registers or in LDS.  The builtin is what the compiler sees; the scheduling
@@ -169,10 +172,6 @@ __device__ __forceinline__ void wait_loads() {
   __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0)
   __builtin_amdgcn_sched_barrier(0);
 }
-
-// Row stride (elements) of a V^T tile in LDS: [d][64 keys + pad].  A fragment read takes 16 bytes
-// per lane from 16 consecutive d-rows: 144-byte rows walk those lanes over all 64 banks.
-constexpr int VS = BN + 8;
 
 // Keys sit in the LDS tile in a permuted row order (bits 2 and 3 of the row swapped), so
 // that accumulator register r of lane half hi holds key 16*(r/8) + 8*hi + r%8 of its 32-key
@@ -238,38 +237,104 @@ __device__ __forceinline__ int count_valid(const int32_t* row, int max_blocks, i
   return max_blocks;
 }
 
-// One 32-key half tile of S^T for the wavefront's two query sub-tiles: s[qs] (16 fp32 each).
-template <int D, int QS>
-__device__ __forceinline__ void qk_half(const __bf16* Kt_half, int k_rd, const bf16x8 (&qf)[QS][D / 16], f32x16 (&s)[QS]) {
-#pragma unroll
-  for (int qs = 0; qs < QS; ++qs) s[qs] = f32x16{0};
-#pragma unroll
-  for (int st = 0; st < D / 16; ++st) {
-    const bf16x8 kf = *(const bf16x8*)(&Kt_half[k_rd + 16 * st]);
-#pragma unroll
-    for (int qs = 0; qs < QS; ++qs) s[qs] = mfma32(kf, qf[qs][st], s[qs]);
-  }
-}
-
-// O^T += V^T P^T for one 32-key half tile (two MFMA k-steps of 16 keys), both query sub-tiles.
-// Vt_half points at the half's first key inside a [d][VS] tile.
+// P^T operand of MFMA k-step hf (16 keys) of a half tile, from the packed probabilities.
 __device__ __forceinline__ bf16x8 p_operand(const uint32_t (&pb)[8], int hf) {
   const u32x4 pw = {pb[4 * hf + 0], pb[4 * hf + 1], pb[4 * hf + 2], pb[4 * hf + 3]};
   return __builtin_bit_cast(bf16x8, pw);
 }
 
-template <int D, int QS>
-__device__ __forceinline__ void pv_half(const __bf16* Vt_half, int v_rd, const uint32_t (&pb)[QS][8], f32x16 (&o)[QS][D / 32]) {
+// Staging of 64-key tiles by NW wavefronts and the reads of their fragments.  Wavefront w loads blocks CH w .. CH w + CH - 1 of
+// either tile.  Row R of the K tile in LDS need not be key R: what a lane loads is chosen so that its CH rows are CH
+// consecutive keys (one look-up in idx for all of them), and the fragment reads undo that together with k_row_perm.  A
+// V^T tile is one contiguous [d][64] block of the tiled tensor.  Offsets that all lanes share go into the scalar offset of
+// the load.  Slots of the rings are byte offsets into `smem`.
+template <int D, int NW>
+struct Stage {
+  using KRows = LdsRows<2 * D>;                   // K tile: [key][d]
+  using VRows = LdsRows<2 * BN>;                  // V^T tile: [d][key]
+  static constexpr int KHALF = 32 / KRows::RPB * kBlock, VTILE = D / VRows::RPB * kBlock;   // bytes of half a K tile, of a V^T tile
+  static constexpr int CH = BN * D / (512 * NW);  // blocks (of 512 elements) of a tile that a wavefront loads
+  static constexpr int NS = D / 16, ND = D / 32;  // MFMA k-steps of the QK product, d sub-tiles of the output
+  static constexpr int kHalfBlocks = 32 / KRows::RPB, VSUB = 32 / VRows::RPB * kBlock;      // VSUB: bytes between d sub-tiles
+  char* smem;
+  int row, col;                // keys row .. row + CH - 1 of a K tile, byte in the row
+  bool half;                   // (a wavefront's blocks lie in one half tile)
+  int lds0, k_lds, v_lds, v_off, v_block;
+  int k_rd[2], v_rd[2];
+  __device__ __forceinline__ void init(char* smem_, int tid) {
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lo = lane & 31, hi = lane >> 5;
+    smem = smem_;
+    lds0 = (int)(uintptr_t)(__attribute__((address_space(3))) char*)smem_;
+    row = CH * (tid / KRows::LPR);
+    col = 16 * KRows::piece(lane);
+    half = wave * CH >= kHalfBlocks;
+    k_lds = (wave * CH % kHalfBlocks) * kBlock;
+    v_lds = wave * CH * kBlock;
+    v_off = (lane / VRows::LPR) * 2 * BN + 16 * VRows::piece(lane);
+    v_block = wave * CH * 1024;
+    // K operand (A of S^T): MFMA row lo = key k_row_perm(lo) of the half tile, 8 d-values at 8 hi
+    constexpr int GR = KRows::RPB * CH;           // keys that a wavefront loads
+    const int key = k_row_perm(lo);
+    const int at = (key & ~(GR - 1)) | ((key & (CH - 1)) * KRows::RPB) | ((key & (GR - 1)) / CH);
+    k_rd[0] = KRows::read_base(at, hi);
+    k_rd[1] = k_rd[0] ^ 32;
+    // V^T operand (A of O^T): row = d (lo within the 32-row d sub-tile), 8 keys at 8 hi
+    v_rd[0] = VRows::read_base(lo, hi);
+    v_rd[1] = v_rd[0] ^ 32;
+  }
+  // row numbers of the K tile at row k0: idx's entries (FUSED) or the rows themselves
+  template <bool FUSED>
+  __device__ __forceinline__ void look_up(__amdgpu_buffer_rsrc_t idx, int k0, int (&tok)[CH]) const {
+    if constexpr (!FUSED) {
 #pragma unroll
-  for (int hf = 0; hf < 2; ++hf) {
+      for (int i = 0; i < CH; ++i) tok[i] = k0 + row + i;
+    } else if constexpr (CH == 4) {
+      const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(idx, row * 4, k0 * 4, 0);
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) {
-      const bf16x8 vf = *(const bf16x8*)(&Vt_half[v_rd + (32 * dt) * VS + 16 * hf]);
+      for (int i = 0; i < CH; ++i) tok[i] = t[i];
+    } else if constexpr (CH == 2) {
+      const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(idx, row * 4, k0 * 4, 0);
 #pragma unroll
-      for (int qs = 0; qs < QS; ++qs) o[qs][dt] = mfma32(vf, p_operand(pb[qs], hf), o[qs][dt]);
+      for (int i = 0; i < CH; ++i) tok[i] = t[i];
+    } else {
+      tok[0] = __builtin_amdgcn_raw_buffer_load_b32(idx, row * 4, k0 * 4, 0);
     }
   }
-}
+  // block i of this wavefront's share; row_off: byte offset of the row of K; half0, half1, tile: slots
+  __device__ __forceinline__ void load_k(u32x4 K, int row_off, int half0, int half1, int i) const {
+    load_to_lds(K, row_off + col, 0, lds0 + (half ? half1 : half0) + k_lds + i * kBlock);
+  }
+  __device__ __forceinline__ void load_v(u32x4 Vt, int k0, int tile, int i) const {
+    load_to_lds(Vt, v_off, k0 * 2 * D + v_block + i * 1024, lds0 + tile + v_lds + i * kBlock);
+  }
+  __device__ __forceinline__ bf16x8 k_frag(int half_slot, int i) const { return *(const bf16x8*)(smem + half_slot + KRows::read_off(k_rd, i)); }
+  // 16 keys from 16 hf on (hf 0 .. 3 over the tile's 64 keys), d sub-tile dt
+  __device__ __forceinline__ bf16x8 v_frag(int tile, int hf, int dt) const { return *(const bf16x8*)(smem + tile + VRows::read_off(v_rd, hf) + dt * VSUB); }
+  // S^T of a half tile
+  template <int QS>
+  __device__ __forceinline__ void qk(int half_slot, const bf16x8 (&qf)[QS][NS], f32x16 (&s)[QS]) const {
+#pragma unroll
+    for (int qs = 0; qs < QS; ++qs) s[qs] = f32x16{0};
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+      const bf16x8 kf = k_frag(half_slot, st);
+#pragma unroll
+      for (int qs = 0; qs < QS; ++qs) s[qs] = mfma32(kf, qf[qs][st], s[qs]);
+    }
+  }
+  // O^T += V^T P^T for half `h` of a tile (two MFMA k-steps of 16 keys)
+  template <int QS>
+  __device__ __forceinline__ void pv(int tile, int h, const uint32_t (&pb)[QS][8], f32x16 (&o)[QS][ND]) const {
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int dt = 0; dt < ND; ++dt) {
+        const bf16x8 vf = v_frag(tile, 2 * h + hf, dt);
+#pragma unroll
+        for (int qs = 0; qs < QS; ++qs) o[qs][dt] = mfma32(vf, p_operand(pb[qs], hf), o[qs][dt]);
+      }
+  }
+};
 
 // Row max of one half tile (per query sub-tile), in scaled log2 units.
 template <int QS>

@@ -42,14 +42,13 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   constexpr int QS = 1;
   constexpr int kThreads = kThreadsS;
   constexpr int RW = 32;
-  constexpr int KS = D + 8;
-  constexpr int KTILE = BN * KS, VTILE = D * VS;
-  constexpr int CH = BN * (D / 8) / kThreads;     // 16-byte chunks per thread per tile
+  using Stg = Stage<D, kThreads / 64>;
+  constexpr int KHALF = Stg::KHALF, KTILE = 2 * KHALF, VTILE = Stg::VTILE, CH = Stg::CH;
   constexpr int NS = D / 16;
   constexpr int ND = D / 32;
   constexpr int ROWB = D * 2;
   constexpr int NKT = 5, NVT = 4;                 // ring slots
-  __shared__ __attribute__((aligned(16))) __bf16 smem[NKT * KTILE + NVT * VTILE];
+  __shared__ __attribute__((aligned(1024))) char smem[NKT * KTILE + NVT * VTILE];
 
   int b, h, from_last;
   workgroup_of(a, blockIdx.x, b, h, from_last);
@@ -67,9 +66,9 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   const __bf16* k_head = FUSED ? a.K + a.ks.head(b, a.by_g_kv.div(h)) : a.K + bkv * Lc * D;
   const int n_rows = FUSED ? a.L : Lc;
   const __amdgpu_buffer_rsrc_t Qr = head_rsrc(q_head, (long long)n_rows * q_pitch);
-  const __amdgpu_buffer_rsrc_t Kr = head_rsrc(k_head, (long long)n_rows * k_pitch);
+  const u32x4 Kr = rsrc_words(k_head, (long long)n_rows * k_pitch);
   const long long vt_bytes = (long long)a.nk_tiles * BN * ROWB;
-  const __amdgpu_buffer_rsrc_t Vr = head_rsrc(a.Vt + bkv * (vt_bytes / 2), vt_bytes);
+  const u32x4 Vr = rsrc_words(a.Vt + bkv * (vt_bytes / 2), vt_bytes);
   const int32_t* idx_row = FUSED ? a.idx + bkv * a.Lc : nullptr;
   const __amdgpu_buffer_rsrc_t Ir = __builtin_amdgcn_make_buffer_rsrc((void*)idx_row, 0, FUSED ? Lc * 4 : 0, 0x00020000);
 
@@ -146,48 +145,16 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
     return s;
   };
 
-  // ---- staging: global -> registers -> LDS in 16-byte chunks, two K tiles and two V tiles per step
-  constexpr int kRowsPerPass = kThreads / (D / 8);
-  const int st_row = tid / (D / 8), st_col = tid % (D / 8);
-  const int lk_off = k_row_perm(st_row) * KS + 8 * st_col;
-  const int gv_off = 16 * tid;
-  const int lv_off = (tid >> 3) * VS + 8 * (tid & 7);
-  constexpr int kVRowsPerPass = kThreads / 8;
+  // ---- staging: global memory -> LDS, two K tiles and two V tiles per step; tiles that do not exist are replaced by
+  // tile 0 in the look-ups and loads: loaded, never used
+  Stg stg;
+  stg.init(smem, tid);
   int ktok[2][CH];
-  u32x4 kreg[2][CH], vreg[2][CH];
   auto row_off = [&](int tok) -> int { return FUSED ? (int)__umul24(tok, k_pitch) : tok * ROWB; };
-  // tiles that do not exist are replaced by tile 0 in the look-ups and loads: loaded, never used
-  auto fetch_tok = [&](int (&tok)[CH], int k0) {
-    k0 = max(k0, 0);
-#pragma unroll
-    for (int i = 0; i < CH; ++i) {
-      if (FUSED) tok[i] = __builtin_amdgcn_raw_buffer_load_b32(Ir, (st_row + i * kRowsPerPass) * 4, k0 * 4, 0);
-      else tok[i] = k0 + st_row + i * kRowsPerPass;
-    }
-  };
-  auto load_k = [&](const int (&tok)[CH], u32x4 (&reg)[CH]) {
-#pragma unroll
-    for (int i = 0; i < CH; ++i)
-      reg[i] = __builtin_amdgcn_raw_buffer_load_b128(Kr, row_off(tok[i]) + 16 * st_col, 0, 0);
-  };
-  auto load_v = [&](u32x4 (&reg)[CH], int k0) {
-    k0 = max(k0, 0);
-#pragma unroll
-    for (int i = 0; i < CH; ++i)
-      reg[i] = __builtin_amdgcn_raw_buffer_load_b128(Vr, gv_off + i * kThreads * 16, k0 * ROWB, 0);
-  };
-  auto store_k = [&](__bf16* dst, const u32x4 (&reg)[CH]) {
-#pragma unroll
-    for (int i = 0; i < CH; ++i) *(u32x4*)(&dst[lk_off + i * kRowsPerPass * KS]) = reg[i];
-  };
-  auto store_v = [&](__bf16* dst, const u32x4 (&reg)[CH]) {
-#pragma unroll
-    for (int i = 0; i < CH; ++i) *(u32x4*)(&dst[lv_off + i * kVRowsPerPass * VS]) = reg[i];
-  };
-
-  // LDS read bases: the wavefront's 32 keys are rows koff.. of a K tile and columns koff.. of a V^T tile
-  const int k_rd = (koff + lo) * KS + 8 * hi;
-  const int v_rd = lo * VS + 8 * hi + koff;
+  auto fetch_tok = [&](int (&tok)[CH], int k0) { stg.template look_up<FUSED>(Ir, max(k0, 0), tok); };
+  auto load_k = [&](const int (&tok)[CH], int tile, int i) { stg.load_k(Kr, row_off(tok[i]), tile, tile + KHALF, i); };
+  auto load_v = [&](int k0, int tile, int i) { stg.load_v(Vr, max(k0, 0), tile, i); };
+  const int khalf = __builtin_amdgcn_readfirstlane(kg) * KHALF;   // this wavefront's keys: half kg of a K tile, 64 bytes of a V^T row
 
   f32x16 o[QS][ND];
   float m[QS], l[QS];
@@ -199,79 +166,61 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   // Ring roles at the top of the iteration of step j:
   //   K: kb0 = b_j, ka1 = a_(j+1), kb1 = b_(j+1) readable; kwa, kwb receive a_(j+2), b_(j+2) during the iteration
   //   V: va0 = a_j, vb0 = b_j readable; vwa, vwb receive a_(j+1), b_(j+1)
-  __bf16* kb0 = smem;
-  __bf16* ka1 = smem + KTILE;
-  __bf16* kb1 = smem + 2 * KTILE;
-  __bf16* kwa = smem + 3 * KTILE;
-  __bf16* kwb = smem + 4 * KTILE;
-  __bf16* va0 = smem + NKT * KTILE;
-  __bf16* vb0 = va0 + VTILE;
-  __bf16* vwa = va0 + 2 * VTILE;
-  __bf16* vwb = va0 + 3 * VTILE;
+  int kb0 = 0, ka1 = KTILE, kb1 = 2 * KTILE, kwa = 3 * KTILE, kwb = 4 * KTILE;
+  int va0 = NKT * KTILE, vb0 = va0 + VTILE, vwa = va0 + 2 * VTILE, vwb = va0 + 3 * VTILE;
   auto rotate = [&]() {
-    __bf16* r0 = kb0; __bf16* r1 = ka1;
+    const int r0 = kb0, r1 = ka1;
     kb0 = kb1; ka1 = kwa; kb1 = kwb; kwa = r0; kwb = r1;
-    __bf16* t = va0; va0 = vwa; vwa = t;
+    int t = va0; va0 = vwa; vwa = t;
     t = vb0; vb0 = vwb; vwb = t;
   };
 
   // ---- prologue: K of steps 0 and 1 and V of step 0 into LDS, S^T of the first half
-  Step S0 = next_step(), S1 = next_step(), S2 = next_step(), S3 = next_step();
+  Step S0 = next_step(), S1 = next_step(), S2 = next_step();
   f32x16 sA[QS], sB[QS];
   uint32_t pA[QS][8], pB[QS][8];
   // half tile h of step S: first key and whether this wavefront takes part in it
   auto act = [&](const Tile& t) -> bool { return t.k0 >= 0 && (t.use & half_bit) && t.k0 + koff <= wrow0 + RW - 1; };
   bf16x8 qf[QS][NS];             // Q^T operand fragments of the wavefront's 32 rows (both key groups hold the same rows)
   {
-    // Everything the first two steps need is requested in two rounds, first the look-ups (and V, which needs none), then
-    // the rows they name: two memory latencies instead of six (with the merge below shared by both key groups: 901 of 3001
+    // Everything the first two steps need is requested in two rounds, first the look-ups, then the rows they name and V: two
+    // memory latencies instead of six (with the merge below shared by both key groups: 901 of 3001
     // tokens x 32 heads 55.2 -> 54.1 us for the layer, 256 of 1024 x 4 32.3 -> 30.9).
-    int qtok = wrow0 + lo, k0tok[2][CH], k1tok[2][CH], k2tok[2][CH];
-    u32x4 kreg0[2][CH], kreg1[2][CH], vreg0[2][CH];
+    int qtok = wrow0 + lo, k0tok[2][CH], k1tok[2][CH];
     if (FUSED) qtok = __builtin_amdgcn_raw_buffer_load_b32(Ir, qtok * 4, 0, 0);
     fetch_tok(k0tok[0], S0.a.k0);
     fetch_tok(k0tok[1], S0.b.k0);
     fetch_tok(k1tok[0], S1.a.k0);
     fetch_tok(k1tok[1], S1.b.k0);
-    fetch_tok(k2tok[0], S2.a.k0);
-    fetch_tok(k2tok[1], S2.b.k0);
-    fetch_tok(ktok[0], S3.a.k0);
-    fetch_tok(ktok[1], S3.b.k0);
-    load_v(vreg0[0], S0.a.k0);
-    load_v(vreg0[1], S0.b.k0);
-    load_v(vreg[0], S1.a.k0);
-    load_v(vreg[1], S1.b.k0);
+    fetch_tok(ktok[0], S2.a.k0);
+    fetch_tok(ktok[1], S2.b.k0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) load_k(k0tok[0], kwa, i);   // a_0 only serves the first S^T below; the slot is free again after the second barrier
     __builtin_amdgcn_sched_barrier(0);
     int qrow_off = qtok * ROWB;
     if (FUSED) qrow_off = wrow0 + lo < Lc ? (int)__umul24(qtok, q_pitch) : a.L * q_pitch;   // past the end: out of the buffer's range, reads zeros
-    load_k(k0tok[0], kreg0[0]);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(Qr, qrow_off + 16 * hi + 32 * s, 0, 0);
       qf[0][s] = __builtin_bit_cast(bf16x8, v);
     }
-    load_k(k0tok[1], kreg0[1]);
-    load_k(k1tok[0], kreg1[0]);
-    load_k(k1tok[1], kreg1[1]);
-    load_k(k2tok[0], kreg[0]);
-    load_k(k2tok[1], kreg[1]);
     __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      load_k(k0tok[1], kb0, i);
+      load_k(k1tok[0], ka1, i);
+      load_k(k1tok[1], kb1, i);
+      load_v(S0.a.k0, va0, i);
+      load_v(S0.b.k0, vb0, i);
+    }
     // (the zero rows' first look-ups while those are under way)
     if (zfill) start_zero_rows(gen.plain ? q0 / (2 * BN) - 1 : gen.tiles_per_block * longest_list / 2 - 3);
-    __builtin_amdgcn_sched_barrier(0);
-    store_v(va0, vreg0[0]);
-    store_v(vb0, vreg0[1]);
-    store_k(kwa, kreg0[0]);          // a_0 only serves the first S^T below; the slot is free again after the second barrier
-    store_k(kb0, kreg0[1]);
-    store_k(ka1, kreg1[0]);
-    store_k(kb1, kreg1[1]);
   }
-  // (everything but the two tiles of step 2 has landed, on every path, see attend.hip)
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * CH));         // vmcnt(2 CH)
+  wait_loads();                                          // (the next wait is at the end of the first iteration, see attend.hip)
   lds_barrier();
-  if (S0.a.k0 >= 0) qk_half<D, QS>(kwa, k_rd, qf, sA);
+  if (S0.a.k0 >= 0) stg.template qk<QS>(kwa + khalf, qf, sA);
   lds_barrier();
-  // in flight from here on: K of step 2 (V of step 1 and the token ids of step 3 are there)
   if (act(S0.a)) {
     if (S0.a.k0 + koff + 31 > wrow0) mask_half<QS>(sA, S0.a.k0 + koff, hi, wrow0 + lo);
     softmax_max<ND, QS>(sA, c, m, l, o);
@@ -283,25 +232,21 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   static_assert(NS == 8 || NS == 4, "chunk stream is laid out for d = 128 or 64");
   constexpr int CPB = kChunks / 4;
   static_assert(kChunks % kRing == 0 && kRing > kPF && kPF <= CPB, "fragment ring does not fit the chunk stream");
-  static_assert(4 * CH <= CPB, "staging of a step does not fit the last block");
   bf16x8 kfr[kRing];
   // fragment fetch for chunk c: block 0 reads b of the current step (kb_), block 2 a of the next (ka_),
   // blocks 1 and 3 the V tiles a and b of the current step
-  auto fetch = [&](int c, const __bf16* kb_, const __bf16* ka_, const __bf16* va_, const __bf16* vb_) {
+  auto fetch = [&](int c, int kb_, int ka_, int va_, int vb_) {
     const int blk = c / CPB, i = c % CPB, slot = c % kRing;
-    if (blk == 0) kfr[slot] = *(const bf16x8*)(&kb_[k_rd + 16 * i]);
-    else if (blk == 2) kfr[slot] = *(const bf16x8*)(&ka_[k_rd + 16 * i]);
-    else {
-      const int hf = i / ND, dt = i % ND;
-      kfr[slot] = *(const bf16x8*)(&(blk == 1 ? va_ : vb_)[v_rd + (32 * dt) * VS + 16 * hf]);
-    }
+    if (blk == 0) kfr[slot] = stg.k_frag(kb_ + khalf, i);
+    else if (blk == 2) kfr[slot] = stg.k_frag(ka_ + khalf, i);
+    else kfr[slot] = stg.v_frag((blk == 1 ? va_ : vb_) + 64 * kg, i / ND, i % ND);   // (64 bytes: two k-steps)
   };
   auto prime_ring = [&]() {
 #pragma unroll
     for (int c = 0; c < kPF; ++c) fetch(c, kb0, ka1, va0, vb0);
   };
-  // vload_*: byte offsets of the V tiles of step 2; tok_*: first compacted rows of the K tiles of step 4
-  auto fast_iter = [&](const int vload_a, const int vload_b, const int tok_a, const int tok_b) {
+  // v_*: first keys of the V tiles of step 1; tok_*: first compacted rows of the K tiles of step 3
+  auto fast_iter = [&](const int v_a, const int v_b, const int tok_a, const int tok_b) {
     float mxc[QS], mx[QS], ps0[QS], ps1[QS];
     f32x16 acc[QS];
 #pragma unroll
@@ -314,6 +259,13 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
       // the first chunks of the next iteration read b of the next step: complete since the previous barrier
       if (c + kPF < kChunks) fetch(c + kPF, kb0, ka1, va0, vb0);
       else fetch(c + kPF - kChunks, kb1, kwa, vwa, vwb);
+      // K of step 2 -> kwa, kwb; V of step 1 -> vwa, vwb; then the look-ups of step 3
+      if (c < 2 * CH) load_k(ktok[c / CH], c < CH ? kwa : kwb, c % CH);
+      else if (c < 4 * CH) load_v(c < 3 * CH ? v_a : v_b, c < 3 * CH ? vwa : vwb, c % CH);
+      else if (c == 4 * CH) {
+        fetch_tok(ktok[0], tok_a);
+        fetch_tok(ktok[1], tok_b);
+      }
       if (blk == 0 || blk == 2) {
         const f32x16 (&s_in)[QS] = blk == 0 ? sA : sB;
         uint32_t (&p_out)[QS][8] = blk == 0 ? pA : pB;
@@ -349,28 +301,15 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
 #pragma unroll
           for (int e = 0; e < EPC; ++e) mx[0] = fmaxf(mx[0], s_in[0][EPC * i + e]);
         }
-        if (blk == 3) {                 // K of step 2 -> kwa, kwb; V of step 1 -> vwa, vwb; then refill the registers
-          if (i < 2 * CH) {
-            const int j = i / CH, ii = i % CH;
-            *(u32x4*)(&(j == 0 ? kwa : kwb)[lk_off + ii * kRowsPerPass * KS]) = kreg[j][ii];
-            kreg[j][ii] = __builtin_amdgcn_raw_buffer_load_b128(Kr, row_off(ktok[j][ii]) + 16 * st_col, 0, 0);
-            const int tk = j == 0 ? tok_a : tok_b;
-            if (FUSED) ktok[j][ii] = __builtin_amdgcn_raw_buffer_load_b32(Ir, (st_row + ii * kRowsPerPass) * 4, tk * 4, 0);
-            else ktok[j][ii] = tk + st_row + ii * kRowsPerPass;
-          } else if (i < 4 * CH) {
-            const int j = (i - 2 * CH) / CH, ii = (i - 2 * CH) % CH;
-            *(u32x4*)(&(j == 0 ? vwa : vwb)[lv_off + ii * kVRowsPerPass * VS]) = vreg[j][ii];
-            vreg[j][ii] = __builtin_amdgcn_raw_buffer_load_b128(Vr, gv_off + ii * kThreads * 16, j == 0 ? vload_a : vload_b, 0);
-          }
-        }
-        if (FUSED && blk == 3 && i == CPB - 1 && zfill && --z_count <= 0) {
-          zero_step();
-          z_count = z_every;
-        }
         if (i == CPB - 1) mxc[0] = fmaxf(mx[0], __shfl_xor(mx[0], 32));
       }
       __builtin_amdgcn_sched_barrier(0);
       if (c == 2 * CPB - 1) raise_max_rel<ND, QS>(mxc, m, l, o, sB);
+    }
+    wait_loads();
+    if (FUSED && zfill && --z_count <= 0) {              // behind the wait, see attend.hip
+      zero_step();
+      z_count = z_every;
     }
     lds_barrier();
     raise_max_rel<ND, QS>(mxc, m, l, o, sA);
@@ -386,54 +325,50 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
       for (int r = 0; r < 16; ++r) sA[0][r] = fmaf(sA[0][r], c_, -m[0]);
       prime_ring();
       do {
-        const Step S4 = next_step();
-        fast_iter(max(S2.a.k0, 0) * ROWB, max(S2.b.k0, 0) * ROWB, max(S4.a.k0, 0), max(S4.b.k0, 0));
-        S0 = S1; S1 = S2; S2 = S3; S3 = S4;
+        const Step S3 = next_step();
+        fast_iter(S1.a.k0, S1.b.k0, S3.a.k0, S3.b.k0);
+        S0 = S1; S1 = S2; S2 = S3;
       } while (pipelined(S0) && pipelined(S1));
       if (S0.a.k0 < 0) break;
 #pragma unroll
       for (int r = 0; r < 16; ++r) sA[0][r] = (sA[0][r] + m[0]) * inv_c;
     }
     // general iteration: masks and per-wavefront decisions
-    if (S0.b.k0 >= 0) qk_half<D, QS>(kb0, k_rd, qf, sB);
+    const Step S3 = next_step();
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      if (S2.a.k0 >= 0) {
+        load_k(ktok[0], kwa, i);
+        load_k(ktok[1], kwb, i);
+      }
+      if (S1.a.k0 >= 0) {
+        load_v(S1.a.k0, vwa, i);
+        load_v(S1.b.k0, vwb, i);
+      }
+    }
+    if (S3.a.k0 >= 0) {
+      fetch_tok(ktok[0], S3.a.k0);
+      fetch_tok(ktok[1], S3.b.k0);
+    }
+    if (S0.b.k0 >= 0) stg.template qk<QS>(kb0 + khalf, qf, sB);
     if (act(S0.a)) {
       softmax_exp<QS>(sA, c, m, l, pA);
-      pv_half<D, QS>(va0, v_rd, pA, o);
+      stg.template pv<QS>(va0 + 64 * kg, 0, pA, o);
     }
     if (act(S0.b)) {
       if (S0.b.k0 + koff + 31 > wrow0) mask_half<QS>(sB, S0.b.k0 + koff, hi, wrow0 + lo);
       softmax_max<ND, QS>(sB, c, m, l, o);
       softmax_exp<QS>(sB, c, m, l, pB);
-      pv_half<D, QS>(vb0, v_rd, pB, o);
+      stg.template pv<QS>(vb0 + 64 * kg, 0, pB, o);
     }
-    if (S1.a.k0 >= 0) qk_half<D, QS>(ka1, k_rd, qf, sA);
+    if (S1.a.k0 >= 0) stg.template qk<QS>(ka1 + khalf, qf, sA);
     if (act(S1.a)) {
       if (S1.a.k0 + koff + 31 > wrow0) mask_half<QS>(sA, S1.a.k0 + koff, hi, wrow0 + lo);
       softmax_max<ND, QS>(sA, c, m, l, o);
     }
-    if (S2.a.k0 >= 0) {
-      store_k(kwa, kreg[0]);
-      store_k(kwb, kreg[1]);
-    }
-    if (S1.a.k0 >= 0) {
-      store_v(vwa, vreg[0]);
-      store_v(vwb, vreg[1]);
-    }
-    if (S3.a.k0 >= 0) {
-      load_k(ktok[0], kreg[0]);
-      load_k(ktok[1], kreg[1]);
-    }
-    if (S2.a.k0 >= 0) {
-      load_v(vreg[0], S2.a.k0);
-      load_v(vreg[1], S2.b.k0);
-    }
-    const Step S4 = next_step();
-    if (S4.a.k0 >= 0) {
-      fetch_tok(ktok[0], S4.a.k0);
-      fetch_tok(ktok[1], S4.b.k0);
-    }
+    wait_loads();
     lds_barrier();
-    S0 = S1; S1 = S2; S2 = S3; S3 = S4;
+    S0 = S1; S1 = S2; S2 = S3;
     rotate();
   }
 
@@ -467,7 +402,7 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   constexpr int NX = ND / 2;                             // d sub-tiles a wavefront keeps
   constexpr int NF = 2 + 16 * NX;                        // floats a lane hands over
   using Out = RowOut<D, NX, FUSED>;
-  static_assert(8 * NF * 256 <= (NKT * KTILE + NVT * VTILE) * 2 && Out::kLds <= NF * 256, "the exchange does not fit the tile rings");
+  static_assert(8 * NF * 256 <= NKT * KTILE + NVT * VTILE && Out::kLds <= NF * 256, "the exchange does not fit the tile rings");
   Out out;
   out.look_up(idx_row, wrow0, Lc, lane);
   __syncthreads();                                       // every wavefront is done with the tiles
