@@ -60,6 +60,7 @@ struct ScoreArgs {
   float* lse2;        // [B*Hq][QP]
   int Hq, Hkv, L, Lq, nchunks, chunk;      // chunk = keys per workgroup
   int g;              // query heads per KV head
+  int most_heads;     // heads a workgroup may serve at a time
   FastDiv by_Hkv;
   int pool_w;
   float* pooled;      // final output when pool_w > 1 (scores then points at a raw buffer)
@@ -711,7 +712,7 @@ hipError_t run(const ScoreArgs& a, int BH, hipStream_t st) {
   const int g = a.Hq / a.Hkv;
   const long long wgs = (long long)a.nchunks * (BH / g);
   int hpw = g >= 4 ? 4 : (g >= 2 ? 2 : 1);
-  while (hpw > 1 && wgs * ((g + hpw - 1) / hpw) <= kCUs / 2) hpw /= 2;
+  while (hpw > 1 && (hpw > a.most_heads || wgs * ((g + hpw - 1) / hpw) <= kCUs / 2)) hpw /= 2;
   if (hpw == 4) return run_split<D, NQT, 4>(a, BH, st);
   if (hpw == 2) return run_split<D, NQT, 2>(a, BH, st);
   return run_split<D, NQT, 1>(a, BH, st);
@@ -754,6 +755,17 @@ hipError_t launch_common(const Dims& dm, ScoreArgs& a, const void* K, float* sco
   a.by_Hkv = FastDiv(dm.Hkv, (uint64_t)dm.B * dm.Hkv);
   a.chunk = chunk_for(dm);
   a.nchunks = (dm.L + a.chunk - 1) / a.chunk;
+  // Workgroups of two heads instead of four on chunks twice as long are as many; where that leaves few enough chunks for
+  // pass 2 to fold, the launch in between falls away, which is worth the second staging of every key as long as the passes
+  // are short.  Whole scoring, 64 queries, four / two heads, us: 32 heads over 8 of K x 10007 tokens 33.0 / 29.7, 12345 33.3 / 32.1, 20000 (chunks of
+  // 384 keys) 41.2 / 41.2, 32768 (512) 56.1 / 56.7, 131072 156 / 169; d = 64 x 32768 41.9 / 39.1; 28 over 4 x 12000 32.7 / 29.8; 40 over 8 x
+  // 16000 50.5 / 45.5; 16 over 2 x 12000 23.7 / 21.0.  (One head on chunks four times as long: 28 over 4 x 30000 57 / 62.)
+  a.most_heads = 4;
+  if (dm.Hq / dm.Hkv >= 4 && a.nchunks > kFoldChunks && a.nchunks <= 2 * kFoldChunks && a.chunk * dm.d <= 384 * 128) {
+    a.most_heads = 2;
+    a.chunk *= 2;
+    a.nchunks = (dm.L + a.chunk - 1) / a.chunk;
+  }
   a.c = dm.scale * kLog2e;
   const size_t BH = (size_t)dm.B * dm.Hq;
   a.part = (float2*)ws;
