@@ -438,17 +438,23 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
       if (T1.k0 >= 0) load_v(T1.k0, vn, i);
     }
     if (T3.k0 >= 0) fetch_tok(T3.k0, ktok);
-    stg.template qk<QS>(kh(0), qf, sB);
+    // A wavefront computes what its rows see and nothing else: the others of its SIMD need the matrix pipe.  (Every product of
+    // every tile by every wavefront: 32 heads x 8192 rows 476 us instead of 470, x 4096 133 instead of 131, 64 x 2401 with four wavefronts
+    // 111.3 instead of 110.1.)
     if (wave_active(T0)) {
-      if (T0.k0 + BN - 1 > wrow0) mask_half<QS>(sB, T0.k0 + 32, hi, wrow0 + lo);
+      const bool second = T0.k0 + 32 <= wrow0 + RW - 1;    // some row of the wavefront sees the second half
+      if (second) stg.template qk<QS>(kh(0), qf, sB);
       softmax_exp<QS>(sA, c, m, l, pA);
       stg.template pv<QS>(vc, 0, pA, o);
-      softmax_max<ND, QS>(sB, c, m, l, o);
-      softmax_exp<QS>(sB, c, m, l, pB);
-      stg.template pv<QS>(vc, 1, pB, o);
+      if (second) {
+        if (T0.k0 + BN - 1 > wrow0) mask_half<QS>(sB, T0.k0 + 32, hi, wrow0 + lo);
+        softmax_max<ND, QS>(sB, c, m, l, o);
+        softmax_exp<QS>(sB, c, m, l, pB);
+        stg.template pv<QS>(vc, 1, pB, o);
+      }
     }
-    if (T1.k0 >= 0) stg.template qk<QS>(kh(1), qf, sA);
     if (wave_active(T1)) {
+      stg.template qk<QS>(kh(1), qf, sA);
       if (T1.k0 + 31 > wrow0) mask_half<QS>(sA, T1.k0, hi, wrow0 + lo);
       softmax_max<ND, QS>(sA, c, m, l, o);
     }

@@ -350,7 +350,7 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
       fetch_tok(ktok[0], S3.a.k0);
       fetch_tok(ktok[1], S3.b.k0);
     }
-    if (S0.b.k0 >= 0) stg.template qk<QS>(kb0 + khalf, qf, sB);
+    if (act(S0.b)) stg.template qk<QS>(kb0 + khalf, qf, sB);   // (what the wavefront's rows see and nothing else, see attend.hip)
     if (act(S0.a)) {
       softmax_exp<QS>(sA, c, m, l, pA);
       stg.template pv<QS>(va0 + 64 * kg, 0, pA, o);
@@ -361,8 +361,8 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
       softmax_exp<QS>(sB, c, m, l, pB);
       stg.template pv<QS>(vb0 + 64 * kg, 0, pB, o);
     }
-    if (S1.a.k0 >= 0) stg.template qk<QS>(ka1 + khalf, qf, sA);
     if (act(S1.a)) {
+      stg.template qk<QS>(ka1 + khalf, qf, sA);
       if (S1.a.k0 + koff + 31 > wrow0) mask_half<QS>(sA, S1.a.k0 + koff, hi, wrow0 + lo);
       softmax_max<ND, QS>(sA, c, m, l, o);
     }
