@@ -492,8 +492,8 @@ int tsa_layer_drift(const void* h_in, const void* h_out, int64_t n_tokens, int32
   if (!(eps >= 0.0f) || !std::isfinite(eps)) return fail(TSA_ERR_ARG, "eps must be finite and >= 0");
   if ((rc = check_ptr(h_in, "h_in")) || (rc = check_ptr(h_out, "h_out"))) return rc;
   if (!drift_out || ((uintptr_t)drift_out & 3u)) return fail(TSA_ERR_ARG, "drift_out is NULL or not 4-byte aligned");
-  if ((rc = check_ws(ws, ws_bytes, tsa::drift_ws_bytes(n_tokens)))) return rc;
-  return hip_status(tsa::launch_drift(h_in, h_out, n_tokens, width, eps, drift_out, ws, (hipStream_t)stream), "tsa_layer_drift");
+  if ((rc = check_ws(ws, ws_bytes, tsa::drift_min_ws_bytes(n_tokens)))) return rc;
+  return hip_status(tsa::launch_drift(h_in, h_out, n_tokens, width, eps, drift_out, ws, ws_bytes, (hipStream_t)stream), "tsa_layer_drift");
 }
 
 int tsa_sparse_layers(const float* drift, int32_t n_layers, double delta, int32_t* is_sparse) {

@@ -5,6 +5,8 @@
 // order (the result is deterministic), a last small kernel adds the partials in fp64.
 #include "tsa_internal.h"
 
+#include <algorithm>
+
 namespace tsa {
 
 namespace {
@@ -24,6 +26,7 @@ constexpr int kRowsPerBlock = 64;     // rows per workgroup (4 per wavefront), f
 // out), us with 1 / 2 / 4 pieces (4: one workgroup per CU): 65536 x 64 17.2 / 19.7 / 33.6, x 512 24.0 / 24.6 / 35.4, x 1024 43.3 / 42.8 / 47.8,
 // 300000 x 64 61 / 72 / 141, 16384 x 4096 (in the memory-side cache) 40.2 / 40.8 / 40.9, 20000 x 3584 53.6 / 52.5 / 54.1.
 constexpr int kNarrow = 512;
+constexpr int kResident = 512;        // workgroups of a launch that run at once (two per CU)
 
 template <int kBatch>
 __global__ __launch_bounds__(kThreads, 8) void drift_rows_kernel(const u32x4* __restrict__ hin, const u32x4* __restrict__ hout,
@@ -109,15 +112,26 @@ __global__ void drift_final_kernel(const double* partial, int n_partial, long lo
 
 }  // namespace
 
-size_t drift_ws_bytes(long long n_tokens) {
+// Partials of workgroups of kRowsPerBlock rows: what a workspace has to hold.
+size_t drift_min_ws_bytes(long long n_tokens) {
   const size_t blocks = (size_t)((n_tokens + kRowsPerBlock - 1) / kRowsPerBlock);
   return (blocks * sizeof(double) + 255) & ~(size_t)255;
 }
+size_t drift_ws_bytes(long long n_tokens) {
+  // Up to 8192 rows: one per wavefront, in up to 512 workgroups.  More than 16384: 512 equal shares (shares of 64 rows are a
+  // second, nearly empty round on some CUs).  In between one workgroup of 64 rows per CU.  Both kernels, shares of 64 rows / these, inputs
+  // from HBM: 1024 x 8192 16.7 / 12.2 us, 2048 x 4096 17.3 / 11.3, 4096 x 4096 27.4 / 16.1, 8192 x 4096 30.7 / 27.0, 20000 x 3584 60.8 / 52.0,
+  // 30000 x 8192 167 / 166; in between 512 shares against 64 rows: 12000 x 4096 36.9 / 37.5 (in the memory-side cache 32.2 / 31.2),
+  // 16384 x 4096 49.9 / 49.4 (47.1 / 42.6).
+  const long long want = n_tokens <= (long long)kResident * kWaves ? (n_tokens + kWaves - 1) / kWaves
+                         : n_tokens > (long long)kResident * kRowsPerBlock / 2 ? kResident : 0;
+  return std::max(drift_min_ws_bytes(n_tokens), ((size_t)want * sizeof(double) + 255) & ~(size_t)255);
+}
 
 hipError_t launch_drift(const void* h_in, const void* h_out, long long n_tokens, int width, float eps, float* out,
-                        void* ws, hipStream_t st) {
-  // the workspace holds a partial per 64 rows, 32 at least: short calls spread over all of those
-  const long long slots = (long long)(drift_ws_bytes(n_tokens) / sizeof(double));
+                        void* ws, size_t ws_bytes, hipStream_t st) {
+  // as many workgroups as the workspace has room for partials, and as there are rows for their wavefronts
+  const long long slots = (long long)(std::min(ws_bytes, drift_ws_bytes(n_tokens)) / sizeof(double));
   const int rows = (int)((n_tokens + slots - 1) / slots);
   const int blocks = (int)((n_tokens + rows - 1) / rows);
   auto* kernel = width <= kNarrow ? drift_rows_kernel<1> : drift_rows_kernel<2>;

@@ -85,9 +85,10 @@ hipError_t launch_budget(const Dims& dm, const float* scores, double tau_cov, in
                          int k_max = 0, int k_min = 0);
 
 // drift.hip
+size_t drift_min_ws_bytes(long long n_tokens);   // required; drift_ws_bytes() is the size that fills the chip
 size_t drift_ws_bytes(long long n_tokens);
 hipError_t launch_drift(const void* h_in, const void* h_out, long long n_tokens, int width, float eps, float* out,
-                        void* ws, hipStream_t st);
+                        void* ws, size_t ws_bytes, hipStream_t st);
 
 // gather_scatter.hip
 hipError_t launch_compress(const Dims& dm, const void* Q, const void* K, const void* V, const int32_t* idx,
