@@ -36,8 +36,8 @@ namespace tsa {
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kWaves = 4;
+constexpr int kSetThreads = 256;             // threads and wavefronts of a workgroup per set of queries (below)
+constexpr int kSetWaves = 4;
 constexpr int kMinChunk = 256;               // keys per workgroup: at least this, a multiple of 128 (every tile size divides it)
 constexpr float kNegBig = -1.0e30f;
 constexpr float kSumLimit = 1073741824.0f;   // 2^30: a unit's sum of exponentials beyond this means the running max lags too far
@@ -67,14 +67,14 @@ struct ScoreArgs {
   float c;            // scale * log2(e)
 };
 
-// Q fragments of one head: rows q_row0 .. q_row0 + Lq - 1 through a buffer descriptor that ends after row
+// Q fragments of one head: scoring queries q_first .. Lq - 1 through a buffer descriptor that ends after row
 // Lq - 1, so the padding rows of the last query sub-tile arrive as zeros without a select (nothing here
 // waits for the loads).
 template <int D, int NQT>
-__device__ __forceinline__ void load_q_frags(const ScoreArgs& a, int b, int h, int lo, int hi, bf16x8 (&qf)[NQT][D / 16]) {
+__device__ __forceinline__ void load_q_frags(const ScoreArgs& a, int b, int h, int q_first, int lo, int hi, bf16x8 (&qf)[NQT][D / 16]) {
   const int pitch = (int)a.qs.l * 2;
-  const __bf16* base = a.Q + a.qs.head(b, h) + (long long)a.q_row0 * a.qs.l;
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, a.Lq * pitch, 0x00020000);
+  const __bf16* base = a.Q + a.qs.head(b, h) + (long long)(a.q_row0 + q_first) * a.qs.l;
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (a.Lq - q_first) * pitch, 0x00020000);
 #pragma unroll
   for (int qt = 0; qt < NQT; ++qt) {
     const int off = (32 * qt + lo) * pitch + 16 * hi;
@@ -83,20 +83,26 @@ __device__ __forceinline__ void load_q_frags(const ScoreArgs& a, int b, int h, i
   }
 }
 
-// How a workgroup of (KV head, chunk of keys) spreads its four wavefronts over the g query heads
-// that share the KV head: `hpw` heads are processed at a time, one per wavefront, and the
+// How a workgroup of (KV head, chunk of keys) spreads its wavefronts over the g query heads that share the KV head: `hpw`
+// heads are processed at a time by the four wavefronts of a set, one each, and the
 // remaining factor splits the keys of every staged tile.  Heads beyond hpw take further rounds, which the
 // workgroups of the grid's third dimension share.
+// More than 64 queries are two sets of up to 64, each with four wavefronts of its own over the same staged keys: two
+// wavefronts per SIMD, where all of them in one (128 registers of query fragments) left one, whose chains of dependent
+// MFMAs and exponentials nothing else filled.  Whole scoring, us: 100 queries, 32 heads over 8 of K x 3001 tokens 31.3 -> 24.6, 2 x 6001 47.0 ->
+// 39.5, 32768 92.5 -> 76.7; 128 queries 131072 294 -> 256, 32 x 8192 43.1 -> 36.2, 28 over 4 x 20000, d = 64, 74.0 -> 58.6.  (The sets one
+// after the other in four wavefronts: pass 2 of 2 x 6001 tokens 24 -> 35.)
 struct WaveRole {
-  int hpw, ksplit, hslot, kpart;
+  int hpw, ksplit, hslot, kpart, set;
 };
 template <int HPW>
 __device__ __forceinline__ WaveRole wave_role(int wave) {
   WaveRole r;
   r.hpw = HPW;
-  r.ksplit = kWaves / r.hpw;
-  r.hslot = wave % r.hpw;
-  r.kpart = wave / r.hpw;
+  r.ksplit = kSetWaves / r.hpw;
+  r.set = wave / kSetWaves;
+  r.hslot = wave % kSetWaves % r.hpw;
+  r.kpart = wave % kSetWaves / r.hpw;
   return r;
 }
 
@@ -105,12 +111,12 @@ __device__ __forceinline__ WaveRole wave_role(int wave) {
 // every group of 16 lanes (16 consecutive rows, the same piece) the positions differ in the bits that
 // select the bank, for D = 128 (256-byte rows: swz = r mod 16) and for D = 64 (128-byte rows, two per 256
 // bytes: swz = (r / 2) mod 8) alike.
-template <int D, int TK>
+template <int D, int TK, int W>                  // W: wavefronts that stage
 struct Geo {
   static constexpr int RB = 2 * D;               // bytes of a row
   static constexpr int CPR = D / 8;              // 16-byte pieces of a row
   static constexpr int RPW = 64 / CPR;           // rows one wavefront-wide load covers (1 KiB)
-  static constexpr int RPI = kWaves * RPW;       // rows one workgroup-wide round of loads covers
+  static constexpr int RPI = W * RPW;            // rows one workgroup-wide round of loads covers
   static constexpr int NLD = TK / RPI;           // loads per thread and tile
   static constexpr int TILE = TK * D;            // elements of a tile
   static_assert(TK % RPI == 0 && RPI % 16 == 0, "a round of loads covers whole periods of the swizzle");
@@ -138,12 +144,12 @@ __device__ __forceinline__ void wait_vm() {
 
 // The ring of staged tiles of one workgroup and chunk: tile t (keys c_begin + t TK ..) lives in slot
 // t % NB, and up to NB - 1 tiles are in flight ahead of the one being read.  Lane l of wavefront w asks, in
-// round j of a tile, for the piece that belongs at LDS byte (j kWaves + w) 1024 + 16 l of the tile: row
+// round j of a tile, for the piece that belongs at LDS byte (j W + w) 1024 + 16 l of the tile: row
 // j RPI + w RPW + l / CPR, position l % CPR.  Rows at or beyond L lie outside the buffer descriptor and
 // arrive as zeros.
-template <int D, int TK, int NB>
+template <int D, int TK, int NB, int W>
 struct Ring {
-  using G = Geo<D, TK>;
+  using G = Geo<D, TK, W>;
   __amdgpu_buffer_rsrc_t rsrc;
   __bf16* tiles;               // LDS, NB tiles
   int voff, pitch, wave, c_begin, n_tiles;
@@ -160,7 +166,7 @@ struct Ring {
     const int k0 = c_begin + t * TK;
 #pragma unroll
     for (int j = 0; j < G::NLD; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)((char*)(tiles + slot * G::TILE) + (j * kWaves + wave) * 1024), 16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)((char*)(tiles + slot * G::TILE) + (j * W + wave) * 1024), 16,
                                                voff, (k0 + j * G::RPI) * pitch, 0, 0);
 #endif
   }
@@ -236,11 +242,11 @@ struct UnitPipe {
 // Pass 1, lane = query: z[qt] += sum over the tile's keys of exp2(x c - m[qt]).  `acc` holds unit 0 of the
 // tile on entry if `primed`; with `chain_next` the tile after this one is entered inside and its unit 0 is
 // left in `acc`.
-template <int D, int NQT, int SPT, int TK, int NB, int SLOT>
-__device__ __forceinline__ void fast_tile_pass1(const Ring<D, TK, NB>& ring, int t, bool& primed, bool chain_next,
+template <int D, int NQT, int SPT, int TK, int NB, int W, int SLOT>
+__device__ __forceinline__ void fast_tile_pass1(const Ring<D, TK, NB, W>& ring, int t, bool& primed, bool chain_next,
                                                 UnitPipe<D, NQT, SPT, true>& pp, f32x16& acc,
                                                 const bf16x8 (&qf)[NQT][D / 16], float c, float (&m)[NQT], float (&z)[NQT]) {
-  constexpr int NS = D / 16, EPC = 16 / NS, U = SPT * NQT, kNextSlot = (SLOT + 1) % NB, TILE = Geo<D, TK>::TILE;
+  constexpr int NS = D / 16, EPC = 16 / NS, U = SPT * NQT, kNextSlot = (SLOT + 1) % NB, TILE = Geo<D, TK, W>::TILE;
   const __bf16* cur = ring.tiles + SLOT * TILE;
   const __bf16* nxt_tile = ring.tiles + kNextSlot * TILE;
   if (!primed) pp.prime(cur, qf, acc);
@@ -303,13 +309,14 @@ __device__ __forceinline__ void fast_tile_pass1(const Ring<D, TK, NB>& ring, int
   primed = chain_next;
 }
 
-// Pass 2, lane = key: s[t] = sum over the queries of exp2(x c - lse[query]); one store per sub-tile.
-template <int D, int NQT, int SPT, int TK, int NB, int SLOT>
-__device__ __forceinline__ void fast_tile_pass2(const Ring<D, TK, NB>& ring, int t, bool& primed, bool chain_next,
+// Pass 2, lane = key: s[t] = sum over the queries of exp2(x c - lse[query]); one `emit` per sub-tile, which is one store to
+// memory (STORES) or to LDS.
+template <int D, int NQT, int SPT, int TK, int NB, int W, int SLOT, bool STORES, typename Emit>
+__device__ __forceinline__ void fast_tile_pass2(const Ring<D, TK, NB, W>& ring, int t, bool& primed, bool chain_next,
                                                 UnitPipe<D, NQT, SPT, false>& pp, f32x16& acc,
                                                 const bf16x8 (&qf)[NQT][D / 16], float c, const float (&lse)[NQT][16],
-                                                float* out, int hi) {
-  constexpr int NS = D / 16, EPC = 16 / NS, U = SPT * NQT, kNextSlot = (SLOT + 1) % NB, TILE = Geo<D, TK>::TILE;
+                                                Emit&& emit) {
+  constexpr int NS = D / 16, EPC = 16 / NS, U = SPT * NQT, kNextSlot = (SLOT + 1) % NB, TILE = Geo<D, TK, W>::TILE;
   const __bf16* cur = ring.tiles + SLOT * TILE;
   const __bf16* nxt_tile = ring.tiles + kNextSlot * TILE;
   if (!primed) pp.prime(cur, qf, acc);
@@ -335,7 +342,7 @@ __device__ __forceinline__ void fast_tile_pass2(const Ring<D, TK, NB>& ring, int
       }
     } else if (chain_next) {
       // the stores of this tile's earlier sub-tiles (SPT - 1 of them) were issued after the loads waited for
-      ring.template enter<kNextSlot, SPT - 1>(t + 1);
+      ring.template enter<kNextSlot, STORES ? SPT - 1 : 0>(t + 1);
       pp.load_all(nxt_tile);
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
@@ -351,7 +358,7 @@ __device__ __forceinline__ void fast_tile_pass2(const Ring<D, TK, NB>& ring, int
     if (qt == NQT - 1) {
       float colsum = s0 + s1;
       colsum += __shfl_xor(colsum, 32);
-      if (hi == 0) out[32 * sb] = colsum;
+      emit(sb, colsum);
       s0 = s1 = 0.f;
     }
   }
@@ -373,15 +380,16 @@ template <int HPW>
 struct TileCfg {
   static constexpr int TK = 128;
   static constexpr int NB = 2;
-  static constexpr int SPT = (TK / 32) / (kWaves / HPW);   // 32-key sub-tiles of a tile per wavefront
+  static constexpr int SPT = (TK / 32) / (kSetWaves / HPW);   // 32-key sub-tiles of a tile per wavefront
 };
 
-template <int D, int NQT, int HPW>
-__global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass1(ScoreArgs a) {
+template <int D, int NQT, int NSET, int HPW>
+__global__ __launch_bounds__(NSET * kSetThreads, 2) void score_pass1(ScoreArgs a) {
   using C = TileCfg<HPW>;
   constexpr int TK = C::TK, NB = C::NB, SPT = C::SPT;
-  using G = Geo<D, TK>;
-  constexpr int QP = 32 * NQT;
+  constexpr int kWaves = NSET * kSetWaves, kThreads = NSET * kSetThreads;
+  using G = Geo<D, TK, kWaves>;
+  constexpr int QP = 32 * NQT, QPA = NSET * QP;          // queries of a set, of all sets
   __shared__ __attribute__((aligned(1024))) __bf16 Ks[NB * G::TILE];
   __shared__ float2 red[kWaves][QP];
   const int chunk = blockIdx.x;
@@ -393,11 +401,11 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass1(ScoreA
   const int c_begin = chunk * a.chunk, c_end = min(c_begin + a.chunk, a.L);
   const int n_tiles = (c_end - c_begin + TK - 1) / TK;
   const int n_fast = fast_tiles<TK>(a, c_begin, n_tiles);
-  const int first_sub = role.kpart * SPT;
+  const int first_sub = role.kpart * SPT, q_first = role.set * QP;
   int my_pos[NQT];                                       // position of this lane's query in each query sub-tile
 #pragma unroll
-  for (int qt = 0; qt < NQT; ++qt) my_pos[qt] = a.qpos[32 * qt + lo];
-  Ring<D, TK, NB> ring;
+  for (int qt = 0; qt < NQT; ++qt) my_pos[qt] = a.qpos[q_first + 32 * qt + lo];
+  Ring<D, TK, NB, kWaves> ring;
   ring.init(a.K + a.ks.head(b, kv), a.ks.l, a.L, tid, Ks, c_begin, n_tiles);
   const int fbase = G::frag_base(lo, hi);
 
@@ -407,7 +415,7 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass1(ScoreA
     const int head = kv * g + (act ? hh : 0);
     bf16x8 qf[NQT][D / 16];
     __syncthreads();                                   // the previous round is done with the ring and with red[]
-    load_q_frags<D, NQT>(a, b, head, lo, hi, qf);           // the Q fragments (served by the L2) ahead of the first K tiles
+    load_q_frags<D, NQT>(a, b, head, q_first, lo, hi, qf);           // the Q fragments (served by the L2) ahead of the first K tiles
     ring.start();
     float m[NQT], z[NQT];
 #pragma unroll
@@ -423,7 +431,7 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass1(ScoreA
       if (t < n_fast) {
         const bool chain_next = t + 1 < n_fast;
         if (act) {
-          fast_tile_pass1<D, NQT, SPT, TK, NB, SLOT>(ring, t, primed, chain_next, pp, acc, qf, a.c, m, z);
+          fast_tile_pass1<D, NQT, SPT, TK, NB, kWaves, SLOT>(ring, t, primed, chain_next, pp, acc, qf, a.c, m, z);
         } else {
           if (chain_next) ring.template enter<kNextSlot, 0>(t + 1);
           primed = chain_next;
@@ -482,15 +490,15 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass1(ScoreA
     }
     __syncthreads();
     // fold the key parts of every head of this round
-    for (int i = tid; i < role.hpw * QP; i += kThreads) {
-      const int slot = i / QP, q = i % QP;
+    for (int i = tid; i < role.hpw * QPA; i += kThreads) {
+      const int slot = i / QPA, q = i % QP, w0 = slot + kSetWaves * (i % QPA / QP);
       if (r0 + slot < g) {
         float mn = kNegBig;
-        for (int j = 0; j < role.ksplit; ++j) mn = fmaxf(mn, red[slot + role.hpw * j][q].x);
+        for (int j = 0; j < role.ksplit; ++j) mn = fmaxf(mn, red[w0 + role.hpw * j][q].x);
         float zs = 0.f;
-        for (int j = 0; j < role.ksplit; ++j) zs += red[slot + role.hpw * j][q].y * fast_exp2(red[slot + role.hpw * j][q].x - mn);
+        for (int j = 0; j < role.ksplit; ++j) zs += red[w0 + role.hpw * j][q].y * fast_exp2(red[w0 + role.hpw * j][q].x - mn);
         const long long bh2 = (long long)b * a.Hq + kv * g + r0 + slot;
-        a.part[(bh2 * a.nchunks + chunk) * QP + q] = make_float2(mn, zs);
+        a.part[(bh2 * a.nchunks + chunk) * QPA + i % QPA] = make_float2(mn, zs);
       }
     }
   }
@@ -547,14 +555,18 @@ __device__ __forceinline__ float fold_chunks(const float2* __restrict__ p, int s
   return mn + log2f(zs);
 }
 
-template <int D, int NQT, int HPW>
-__global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreArgs a) {
+template <int D, int NQT, int NSET, int HPW>
+__global__ __launch_bounds__(NSET * kSetThreads, 2) void score_pass2(ScoreArgs a) {
   using C = TileCfg<HPW>;
   constexpr int TK = C::TK, NB = C::NB, SPT = C::SPT;
-  using G = Geo<D, TK>;
-  constexpr int QP = 32 * NQT;
+  constexpr int kWaves = NSET * kSetWaves, kThreads = NSET * kSetThreads;
+  using G = Geo<D, TK, kWaves>;
+  constexpr int QP = 32 * NQT, QPA = NSET * QP;          // queries of a set, of all sets
   __shared__ __attribute__((aligned(1024))) __bf16 Ks[NB * G::TILE];
-  __shared__ float lse_s[HPW * QP];
+  __shared__ float lse_s[HPW * QPA];
+  // Two sets: their column sums of a tile meet here.  The sums of tile t are complete before the barrier in front of tile t + 2,
+  // behind which they are added up and stored, so four tiles' worth are enough.
+  __shared__ float sums[NSET > 1 ? 4 : 1][NSET > 1 ? NSET : 1][NSET > 1 ? HPW : 1][NSET > 1 ? TK : 1];
   __shared__ int qpos_s[kMaxQueries];                  // the position table, for the search of the masked tiles
   if (threadIdx.x < kMaxQueries) qpos_s[threadIdx.x] = a.qpos[threadIdx.x];   // visible after the first barrier below
   // Pass 2 walks the (KV head, chunk) pairs in the reverse of pass 1's order: the workgroups that start
@@ -569,8 +581,8 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
   const int c_begin = chunk * a.chunk, c_end = min(c_begin + a.chunk, a.L);
   const int n_tiles = (c_end - c_begin + TK - 1) / TK;
   const int n_fast = fast_tiles<TK>(a, c_begin, n_tiles);
-  const int first_sub = role.kpart * SPT;
-  Ring<D, TK, NB> ring;
+  const int first_sub = role.kpart * SPT, q_first = role.set * QP;
+  Ring<D, TK, NB, kWaves> ring;
   ring.init(a.K + a.ks.head(b, kv), a.ks.l, a.L, tid, Ks, c_begin, n_tiles);
   const int fbase = G::frag_base(lo, hi);
 
@@ -581,23 +593,23 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
     const long long bh = (long long)b * a.Hq + head;
     __syncthreads();                                   // the previous round is done with the ring and with lse_s
     bf16x8 qf[NQT][D / 16];
-    load_q_frags<D, NQT>(a, b, head, lo, hi, qf);           // Q fragments (served by the L2) ahead of the first K tiles
+    load_q_frags<D, NQT>(a, b, head, q_first, lo, hi, qf);           // Q fragments (served by the L2) ahead of the first K tiles
     ring.start();
     // log2-sum-exp of the round's queries, through LDS: a few partials per query are folded here, many by score_lse
-    for (int i = tid; i < HPW * QP; i += kThreads) {
-      const int slot = i / QP, q = i % QP;
+    for (int i = tid; i < HPW * QPA; i += kThreads) {
+      const int slot = i / QPA, q = i % QPA;
       if (r0 + slot >= g) break;
       const long long bhs = (long long)b * a.Hq + kv * g + r0 + slot;
       float x = INFINITY;
-      if (a.nchunks > kFoldChunks) x = a.lse2[bhs * QP + q];
-      else if (q < a.Lq) x = fold_chunks(a.part + bhs * a.nchunks * QP + q, QP, a.nchunks);
+      if (a.nchunks > kFoldChunks) x = a.lse2[bhs * QPA + q];
+      else if (q < a.Lq) x = fold_chunks(a.part + bhs * a.nchunks * QPA + q, QPA, a.nchunks);
       lse_s[i] = x;
     }
     __syncthreads();
     // ... of the queries this lane sees as accumulator rows.  (One address and constant offsets here, and constants in the
     // comparisons of the masked tiles below: formed per row, the indices lived in 39 registers across the rounds, and 6 to 11
     // others spilled; 8 KV heads of 16384 tokens, one query head each, whole scoring: 26.4 -> 24.3 us.)
-    const float* my_lse = lse_s + role.hslot * QP + 4 * hi;
+    const float* my_lse = lse_s + role.hslot * QPA + q_first + 4 * hi;
     float lse[NQT][16];
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt)
@@ -608,15 +620,28 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
     pp.first_sub = first_sub;
     f32x16 acc = {0};
     bool primed = false;
+    auto store_sums = [&](int t) {
+      if (NSET == 1 || t < 0) return;
+      for (int i = tid; i < HPW * TK; i += kThreads) {
+        const int slot = i / TK, key = c_begin + t * TK + i % TK;
+        if (r0 + slot < g && key < a.L)
+          a.scores[((long long)b * a.Hq + kv * g + r0 + slot) * a.L + key] = sums[t & 3][0][slot][i % TK] + sums[t & 3][NSET - 1][slot][i % TK];
+      }
+    };
     auto tile = [&](int t, auto slot_tag) {
       constexpr int SLOT = decltype(slot_tag)::value, kNextSlot = (SLOT + 1) % NB;
       if (!primed) ring.template enter<SLOT, 0>(t);
+      store_sums(t - 2);
       const int k0 = c_begin + t * TK;
       if (t < n_fast) {
         const bool chain_next = t + 1 < n_fast;
         if (act) {
           float* out = a.scores + bh * a.L + k0 + 32 * first_sub + lo;
-          fast_tile_pass2<D, NQT, SPT, TK, NB, SLOT>(ring, t, primed, chain_next, pp, acc, qf, a.c, lse, out, hi);
+          fast_tile_pass2<D, NQT, SPT, TK, NB, kWaves, SLOT, NSET == 1>(ring, t, primed, chain_next, pp, acc, qf, a.c, lse, [&](int sb, float sum) {
+            if (hi) return;
+            if (NSET == 1) out[32 * sb] = sum;
+            else sums[t & 3][role.set][role.hslot][32 * (first_sub + sb) + lo] = sum;
+          });
         } else {
           if (chain_next) ring.template enter<kNextSlot, 0>(t + 1);
           primed = chain_next;
@@ -639,7 +664,7 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
           int lo_i = 0, hi_i = QP;
           while (lo_i < hi_i) {
             const int mid = (lo_i + hi_i) >> 1;
-            if (qpos_s[mid] < tk) lo_i = mid + 1; else hi_i = mid;
+            if (qpos_s[q_first + mid] < tk) lo_i = mid + 1; else hi_i = mid;
           }
           n_hidden = lo_i - 4 * hi;                        // (accumulator row r of this lane is query c_row(r, 0) + 4 hi)
         }
@@ -657,13 +682,21 @@ __global__ __launch_bounds__(kThreads, NQT <= 2 ? 2 : 1) void score_pass2(ScoreA
           }
         }
         colsum += __shfl_xor(colsum, 32);
-        if (hi == 0 && tk < a.L) a.scores[bh * a.L + tk] = colsum;
+        if (hi == 0 && tk < a.L) {
+          if (NSET == 1) a.scores[bh * a.L + tk] = colsum;
+          else sums[t & 3][role.set][role.hslot][32 * sub + lo] = colsum;
+        }
       }
     };
     for (int t0 = 0; t0 < n_tiles; t0 += NB)
       static_for<0, NB>([&](auto s) {
         if (t0 + decltype(s)::value < n_tiles) tile(t0 + decltype(s)::value, s);
       });
+    if (NSET > 1) {
+      __syncthreads();
+      store_sums(n_tiles - 2);
+      store_sums(n_tiles - 1);
+    }
   }
 }
 
@@ -680,22 +713,23 @@ __global__ void pool_kernel(const float* __restrict__ raw, float* __restrict__ o
 }
 
 constexpr int kCUs = 256;
-// workgroups that the LDS tiles and the registers allow to be resident: two per CU with up to 64 queries, else one
+// workgroups that the LDS tiles and the registers allow to be resident: two per CU with up to 64 queries, else one of twice
+// the wavefronts
 inline int resident_workgroups(int QP) { return QP <= 64 ? 2 * kCUs : kCUs; }
 
-template <int D, int NQT, int HPW>
+template <int D, int NQT, int NSET, int HPW>
 hipError_t run_split(const ScoreArgs& a, int BH, hipStream_t st) {
-  constexpr int QP = 32 * NQT;
+  constexpr int QP = 32 * NQT * NSET, kThreads = NSET * kSetThreads;
   const int g = a.Hq / a.Hkv;
   // One workgroup per (KV head, chunk); its rounds of heads go to workgroups of their own as long as all of them are
-  // resident at once (NQT <= 2: two per CU).
+  // resident at once.
   dim3 grid(a.nchunks, BH / g);
   const int rounds = (g + HPW - 1) / HPW;
-  grid.z = (unsigned)max(1, min(rounds, resident_workgroups(32 * NQT) / (int)(grid.x * grid.y)));
-  score_pass1<D, NQT, HPW><<<grid, kThreads, 0, st>>>(a);
+  grid.z = (unsigned)max(1, min(rounds, resident_workgroups(QP) / (int)(grid.x * grid.y)));
+  score_pass1<D, NQT, NSET, HPW><<<grid, kThreads, 0, st>>>(a);
   const long long n = (long long)BH * QP;
   if (a.nchunks > kFoldChunks) score_lse<<<(unsigned)((n + 3) / 4), 256, 0, st>>>(a, QP, n);
-  score_pass2<D, NQT, HPW><<<grid, kThreads, 0, st>>>(a);
+  score_pass2<D, NQT, NSET, HPW><<<grid, kThreads, 0, st>>>(a);
   if (a.pool_w > 1) {
     const long long nt = (long long)BH * a.L;
     pool_kernel<<<(unsigned)((nt + 255) / 256), 256, 0, st>>>(a.scores, a.pooled, a.L, a.pool_w, nt);
@@ -707,15 +741,15 @@ hipError_t run_split(const ScoreArgs& a, int BH, hipStream_t st) {
 // the group has, unless the chunks leave CUs idle: then a workgroup takes fewer heads, and its wavefronts split the keys of
 // every tile instead.  8 KV heads x 3001 tokens are 96 workgroups with four heads each: passes of 11.4 and 12.0 us; 192 with
 // two: 9.8 and 9.8; 384 with one: 10.2 and 11.3, so half the CUs busy is where the line lies.
-template <int D, int NQT>
+template <int D, int NQT, int NSET>
 hipError_t run(const ScoreArgs& a, int BH, hipStream_t st) {
   const int g = a.Hq / a.Hkv;
   const long long wgs = (long long)a.nchunks * (BH / g);
   int hpw = g >= 4 ? 4 : (g >= 2 ? 2 : 1);
   while (hpw > 1 && (hpw > a.most_heads || wgs * ((g + hpw - 1) / hpw) <= kCUs / 2)) hpw /= 2;
-  if (hpw == 4) return run_split<D, NQT, 4>(a, BH, st);
-  if (hpw == 2) return run_split<D, NQT, 2>(a, BH, st);
-  return run_split<D, NQT, 1>(a, BH, st);
+  if (hpw == 4) return run_split<D, NQT, NSET, 4>(a, BH, st);
+  if (hpw == 2) return run_split<D, NQT, NSET, 2>(a, BH, st);
+  return run_split<D, NQT, NSET, 1>(a, BH, st);
 }
 
 // Keys per workgroup: long enough that the start-up of a workgroup (Q fragments, first K tile)
@@ -746,7 +780,7 @@ size_t score_ws_bytes(const Dims& dm) {
 namespace {
 
 hipError_t launch_common(const Dims& dm, ScoreArgs& a, const void* K, float* scores, void* ws, hipStream_t st) {
-  const int nqt = nqt_for(dm.last_q);
+  const int nqt = nqt_for(dm.last_q);                    // query sub-tiles; 4: two sets of two
   const int QP = 32 * nqt;
   a.K = (const __bf16*)K; a.scores = scores;
   a.ks = dm.kv;
@@ -778,13 +812,13 @@ hipError_t launch_common(const Dims& dm, ScoreArgs& a, const void* K, float* sco
   }
   const int bh = (int)BH;
   if (dm.d == 128) {
-    if (nqt == 1) return run<128, 1>(a, bh, st);
-    if (nqt == 2) return run<128, 2>(a, bh, st);
-    return run<128, 4>(a, bh, st);
+    if (nqt == 1) return run<128, 1, 1>(a, bh, st);
+    if (nqt == 2) return run<128, 2, 1>(a, bh, st);
+    return run<128, 2, 2>(a, bh, st);
   }
-  if (nqt == 1) return run<64, 1>(a, bh, st);
-  if (nqt == 2) return run<64, 2>(a, bh, st);
-  return run<64, 4>(a, bh, st);
+  if (nqt == 1) return run<64, 1, 1>(a, bh, st);
+  if (nqt == 2) return run<64, 2, 1>(a, bh, st);
+  return run<64, 2, 2>(a, bh, st);
 }
 
 }  // namespace
