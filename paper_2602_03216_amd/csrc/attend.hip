@@ -2,9 +2,10 @@
 // operation on Q^, K^, V^ with cost O(L'^2 d)), also used unchanged as the dense baseline.
 //
 // Flash-style: one workgroup owns 256 query rows (8 wavefronts x 32 rows, two wavefronts per
-// SIMD; a second form: four wavefronts, 128 rows), streams 64-key tiles through LDS (K in a ring of three tiles, with
-// four wavefronts of five half tiles, V in a ring of two tiles, one barrier per tile), keeps the running max / sum and the output accumulator in registers
-// (online softmax) and never materialises the score matrix.
+// SIMD; a second form: four wavefronts, 128 rows), streams 64-key tiles through LDS (loaded straight into it, in swizzled
+// order: LdsRows; K in a ring of three tiles, with four wavefronts of five half tiles, V in a ring of two tiles, one barrier per
+// tile), keeps the running max / sum and the output accumulator in registers (online softmax) and never materialises the
+// score matrix.
 //
 // Both products run on v_mfma_f32_32x32x16_bf16 in the TRANSPOSED orientation:
 //   S^T = K Q^T   rows = keys, cols = queries  -> a lane owns ONE query of the wavefront's 32
@@ -44,8 +45,8 @@ namespace {
 // rows, one per SIMD, every LDS fragment feeds two MFMAs.  QS = 1: wavefronts of 32 rows, which share
 // the SIMD's issue slots (a lone wavefront issues one vector instruction every ~8 clocks, two
 // together one every ~5) at the price of one LDS fragment per MFMA.  NW = 8: 256 rows, the two wavefronts of a SIMD
-// belong to one workgroup.  NW = 4: 128 rows; the LDS holds two such workgroups (2 x 80384 bytes of 160 KiB, with K
-// in a ring of five half tiles instead of three tiles), three at d = 64 (168 VGPRs: the fused forms spill 8, with lists 13), which wait
+// belong to one workgroup.  NW = 4: 128 rows; the LDS holds two such workgroups (2 x 78336 bytes of 160 KiB, with K
+// in a ring of five half tiles instead of three tiles), three at d = 64 (39168 bytes each; 168 VGPRs, of which the fused forms spill 4, with lists 5), which wait
 // at their own barriers and start and end one under the other; every K / V tile is staged for half as many rows.
 // Which one runs, and what both measured: use_pair_form below.
 // LISTS: the launch has a block list.  The plain causal form is a kernel of its own: the look-ups of the tile
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   //   QK(T0, half 1)      with  exp(sA)
   //   PV(T0, half 0)      with  max(sB)            [then the rare raise of m, rescale of O]
   //   QK(T1, half 0)      with  exp(sB)
-  //   PV(T0, half 1)      with  max(sA of T1), staging  [then the rare raise of m]
+  //   PV(T0, half 1)      with  max(sA of T1)            [then the rare raise of m]
 
   // ---- the pipelined iteration: one key tile that lies entirely below the workgroup's first
   // row and is used by all its wavefronts (as is the tile after it) needs no mask and no
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   //    0.. 7  S^T(T0, half 1) -> sB      with  exp(sA) -> pA
   //    8..15  O^T += V^T(T0, half 0) pA  with  row max of sB          [then the rare raise of m]
   //   16..23  S^T(T1, half 0) -> sA      with  exp(sB) -> pB
-  //   24..31  O^T += V^T(T0, half 1) pB  with  row max of sA, staging  [barrier, rare raise of m]
+  //   24..31  O^T += V^T(T0, half 1) pB  with  row max of sA         [wait for the tiles requested, barrier, rare raise of m]
   // Inside this loop sA and sB hold s * c - m by the time their exponentials are due (formed by an fma
   // per element in the PV block after the chain, or, with scaled Q, by a chain that starts from -m), so the
   // exponent is the register itself and the row max is relative to m; a raise of m between the two shifts
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   // slot = chunk % kRing must mean the same slot in consecutive iterations; a fragment must not be
   // overwritten before it is consumed; and the fragments fetched across the iteration boundary
   // must all belong to block 0 (K of the next tile, complete since the previous barrier), not to
-  // the V tile that this iteration is still writing
+  // the V tile that is still arriving during this iteration
   static_assert(kChunks % kRing == 0 && kRing > kPF && kPF <= CPB, "fragment ring does not fit the chunk stream");
   bf16x8 kfr[kRing];
   // fragment fetch for chunk c of the iteration whose half tiles of K and tile of V sit in (k1_, k2_, vc_)
@@ -528,36 +529,42 @@ double chain_ratio(const AttendArgs& a) {
 // The split form pays where the longest chain and not the chip's throughput is the launch: it halves that chain, and stages
 // every K / V tile for half as many rows and half as many keys per wavefront.  The ratio from which it does rises with
 // the number of heads: the more heads, the fewer rows at the same ratio, and the more the start and the merge of its
-// workgroups weigh.  us of the launch, fused, d = 128, split / four wavefronts / 256 rows: 4 heads x 18894 rows (ratio 1.71) 413 / 434 / 446,
-// x 20942 (1.54) 505 / 505 / 515; 8 x 9422 (1.68) 221 / 223 / 232, x 9934 (1.60) 243 / 241 / 249; 16 x 4046 (1.88) 87 / 98 / 105, x 4302 (1.78)
-// 108 / 106 / 112; 20 x 3278 (1.83) 87.7 / 81.5 / 87.8; 32 x 901 (3.2) 26.3 / 28 / 35.4, x 1742 (2.0) 48.4 / 47.2 / 53.5 (at d = 64
-// 37.2 / 38.4 / 44.3, plain x 1792 31.7 / 33.6: hence 2.0 up to 32 heads); 40 x 1250 (2.13)
-// 40.2 / 36.4 / 42.1; 64 x 738 (2.0) 33.0 / 26.9 / 31.7.  tsa_attend on compacted tensors crosses at the same ratios, at d = 64 0.1 to 0.15 lower
-// and the fused launch as much higher; one rule for all keeps tsa_forward and the separate calls the same bit for bit.
-// Under a block list a window bounds the chains, so that the ratio says little: the form pays only while all of its
+// workgroups weigh.  us of the launch, fused, d = 128, split / four wavefronts / 256 rows: 4 heads x 18894 rows (ratio 1.71) 391 / 410 / 436,
+// x 20942 (1.54) 469 / 480 / 503; 8 x 9422 (1.68) 205 / 211 / 227, x 9934 (1.60) 225 / 226 / 242; 16 x 4046 (1.88) 86 / 91 / 101, x 4302 (1.78)
+// 96 / 98 / 108; 20 x 3278 (1.83) 77.7 / 77.0 / 84.7; 32 x 901 (3.2) 22.0 / 23.4 / 30.5, x 1742 (2.0) 43.1 / 44.8 / 49.4 (at d = 64
+// 31.1 / 32.6 / 36.9, plain x 1792 28.7 / 31.8); 40 x 1250 (2.13) 35.1 / 34.0 / 38.6; 64 x 738 (2.0) 28.1 / 24.8 / 28.0.  One rule for
+// tsa_attend on compacted tensors and the fused launch keeps tsa_forward and the separate calls the same bit for bit.
+// A block list whose rows have room for every block of the set need not bound the chains (a window as long as a short set):
+// the same ratio decides, 0.05 higher, since the split form's workgroups count twice as many lists.  Window 4096, split / four wavefronts /
+// 256 rows: fused, d = 128, 12 heads x 4096 rows (2.5), blocks of 64 77.4 / 91.9 / 114.5, of 256 70.5 / 85.6 / 100.4; with a residual
+// stream 16 x 4096 (1.88), blocks of 128, 86.7 / 96.4 / 103.7, 28 x 1000 (3.7) 25.5 / 29.2 / 35.3, x 2048 (2.03) 53.8 / 52.1 / 57.2, x 4096 (1.08)
+// 158 / 132 / 138; d = 64, 12 x 4096 56.9 / 70.3 / 81.5.
+// Under a shorter list its window bounds the chains, so that the ratio says little: the form pays only while all of its
 // workgroups, one per CU, run at once, and not with blocks of 64, where a workgroup of four wavefronts walks shorter lists.
-// d = 128, plain, split / four wavefronts / 256 rows: 4 heads x 8192 rows (256 workgroups), blocks of 128 39.6 / 39.8 / 51.6,
-// of 256 54.9 / 58.7 / 70.9, of 64 35.3 / 34.2 / 44.6; 8 x 8192 (512), blocks of 128 74.2 / 61.2 / 63.3, of 256 108.7 / 93.0 / 88.4;
-// 12 x 4096 (384), blocks of 128 63.3 / 47.2 / 49.7, of 256 72.2 / 64.2 / 69.5.
+// d = 128, plain, window 4096: 4 heads x 8192 rows (256 workgroups), blocks of 128 76.9 / 83.2 / 108.3, of 256 75.2 / 84.9 / 107.1; 8 x 8192
+// (512), blocks of 128 141.8 / 124.7 / 116.8, of 256 139.3 / 126.5 / 117.0; fused, blocks of 128, 16 x 4096 (512) with a window of 2000
+// 82.3 / 68.2 / 70.2, 28 x 2048 (448) with one of 1024 51.9 / 41.8 / 47.0.
 bool use_split_form(const AttendArgs& a) {
   if (g_attend_form) return g_attend_form == 2;
-  if (a.block_list) return a.block >= 128 && (long long)a.BH * ((a.Lc + 127) / 128) <= 256 && chain_ratio(a) >= 1.8;
-  const double line = 1.5 + 0.0175 * a.BH;
-  return chain_ratio(a) >= (a.BH <= 32 ? std::min(line, 2.0) : line);
+  const double line = a.BH <= 32 ? std::min(1.5 + 0.0175 * a.BH, 2.0) : 1.5 + 0.0175 * a.BH;
+  if (!a.block_list) return chain_ratio(a) >= line;
+  if ((long long)a.max_blocks * a.block >= a.Lc && chain_ratio(a) >= line + 0.05) return true;
+  return a.block >= 128 && (long long)a.BH * ((a.Lc + 127) / 128) <= 256 && chain_ratio(a) >= 1.8;
 }
 
 // Four wavefronts per workgroup (two or three workgroups per CU) against 256 rows, us of the fused launch:
-//   d = 64 (three wavefronts per SIMD instead of two): 32 heads x 4096 rows 91.9 / 104.7, x 8192 328 / 372, x 16384
-//     1209 / 1384, sink + window lists 28 x 16384 575 / 662 (blocks of 256), 598 / 714 (128): always.  (tsa_attend loses 3 to
-//     5 % to a second, nearly empty round just above 768 workgroups: 12 x 9000 169 / 162; tsa_forward there 172 / 189.)
+//   d = 64 (three wavefronts per SIMD instead of two): 32 heads x 4096 rows 88.0 / 87.4, x 8192 313 / 319, x 16384
+//     1180 / 1223, 96 x 1500 48.2 / 53.2, sink + window lists 28 x 16384 527 / 568 (blocks of 256), 518 / 596 (128): always.  (Just above
+//     768 workgroups a second, nearly empty round costs 5 %: 12 x 9000 167 / 158; 32 x 3277 66.4 / 63.0.)
 //   d = 128, block lists with blocks of 64 or 128: a workgroup walks the lists of one or two row blocks instead of the
-//     union of up to four: 28 x 16384 598 / 696 (blocks of 64), 958 / 997 (128), 28 x 4096 89 / 113 (64); with blocks of 256
-//     (955 / 940) only for few heads, by the ratio below (plain 12 x 4096 64.2 / 69.5, 8 x 8192 93.0 / 88.4).
+//     union of up to four, which counts where the window is short: 28 x 16384 with a window of 1024 333 / 371 (blocks of 64), 340 / 378 (128),
+//     of 4096 with the residual stream 881 / 894 (64), 862 / 854 (128), 28 x 4096, 1024, 84.5 / 98.8 (64); with blocks of 256
+//     only for few heads, by the ratio below.
 //   d = 128, plain: a start and an end hidden under the other workgroup are worth more than the second staging of
-//     the tiles as long as the chains are short: 128 heads x 600 rows 45.4 / 56.0, 96 x 1000 50 / 55, 64 x 1500 56 / 59,
-//     32 x 2500 71.5 / 76.2, 96 x 2400 171 / 187, 40 x 3000 112 / 114, 64 x 3300 198 / 200; 32 x 3500 115 / 113,
-//     64 x 4000 282 / 279, 32 x 8192 537 / 522, x 32768 8000 / 7750; and where few heads leave the longest chain
-//     in charge (16 x 5000 132 / 136, ratio 1.52).
+//     the tiles as long as the chains are short: 128 heads x 600 rows 30.7 / 37.2, 96 x 1000 43.4 / 44.1, 64 x 1500 52.4 / 52.0,
+//     32 x 2500 67.5 / 72.3, 96 x 2400 163 / 174, 40 x 3000 105.5 / 104.2, 32 x 3277 109 / 109, 64 x 3300 189 / 189; 32 x 3500 113 / 111,
+//     64 x 4000 289 / 275, 32 x 8192 521 / 504, x 32768 8090 / 7750; and where few heads leave the longest chain
+//     in charge (16 x 5000 122 / 131, ratio 1.52).
 constexpr int kPairRows = 3328;
 
 bool use_pair_form(const AttendArgs& a, int d) {
