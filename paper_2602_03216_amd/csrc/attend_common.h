@@ -119,9 +119,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// Workgroup barrier that waits for this wavefront's LDS traffic only.  __syncthreads() also waits
-// for every outstanding global load, which would expose the latency of the tile prefetch that
-// was issued just before it; those loads land in registers and are consumed a tile later.
+// Workgroup barrier that waits for this wavefront's LDS traffic only.  __syncthreads() also waits for every outstanding
+// global access, the zero rows' stores and the next look-ups among them; the tiles that are loaded into LDS are waited for
+// where they have to be (wait_loads).
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }

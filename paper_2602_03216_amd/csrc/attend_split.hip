@@ -13,12 +13,12 @@
 //
 // The iteration is the one of the 256-row kernel (attend.hip): per wavefront a stream of 32 chunks,
 //    S^T(half 1) with exp(half 0) | PV(half 0) with the row max of half 1 | S^T(next half 0) with
-//    exp(half 1) | PV(half 1) with the row max of the next half 0 and the staging,
+//    exp(half 1) | PV(half 1) with the row max of the next half 0,
 // where "half 0 / half 1" of an iteration are the wavefront's 32 keys of the step's first / second
 // tile: one step = two 64-key tiles (a, b) = 128 keys, one barrier per step.
 // LDS: K tiles of three steps are resident (ring of five tiles: b of the current step, a and b of the
-// next one readable, a and b of the step after being written), V tiles of two steps (ring of four):
-// what an iteration prefetches across its closing barrier was written an iteration earlier.
+// next one readable, a and b of the step after arriving), V tiles of two steps (ring of four): the tiles go straight into
+// LDS (Stage), and the fragments an iteration reads ahead across its closing barrier arrived an iteration earlier.
 #include "attend_common.h"
 
 #include <type_traits>

@@ -10,9 +10,9 @@
 //           queries inside the lane, one cross-half add, coalesced store of s[h, t]
 // The two orientations use the same register fragments (a lane holds 8 consecutive d-values of
 // one row), only the operand order of the MFMA is swapped, so neither pass needs a cross-lane
-// reduction longer than one step.  A workgroup serves one KV head and one chunk of keys for all
-// the query heads of the group: K tiles are staged in LDS once and every wavefront (one query
-// head each) reads its fragments from there.
+// reduction longer than one step.  A workgroup serves one KV head and one chunk of keys for the
+// query heads of the group: K tiles are staged in LDS once and every wavefront (which query head, which keys of a
+// tile, which set of up to 64 queries: wave_role) reads its fragments from there.
 // Staging: tiles of 128 keys go from global memory straight into LDS (buffer loads with the LDS
 // modifier: no staging registers, no LDS store instructions, no address arithmetic in the loop), into a
 // ring of two tiles, the load of tile t + 1 in flight while tile t is computed.  Such a load writes the
