@@ -177,7 +177,9 @@ int tsa_compress(const tsa_desc* desc, const void* Q, const void* K, const void*
  *   tsa_desc.block_list_per_head): row qb lists, in ascending order and padded with -1,
  *   the key blocks that query block qb may see (composition with a block-sparse pattern in
  *   compacted index space, Section 1 / Appendix "other sparse attention methods").  Entries > qb
- *   are ignored; the diagonal block is causal inside.  block_size: 64, 128 or 256.
+ *   are ignored; the diagonal block is causal inside.  block_size: 64, 128 or 256.  max_blocks_per_row is
+ *   the stride of the table: the same lists in wider rows cost no more (and round alike, except that blocks of
+ *   64 may take another form of the kernel once a row has room for every block of the set).
  * The dense baseline is this same call with Qc=Q, Kc=K, Vc=V, Lc=L, kv_heads=Hkv.
  *   ws: tsa_attend_workspace_bytes(desc, Lc, kv_heads) bytes (only B, Hq, d of desc are used): the
  *   call first rewrites Vc into 64-key transposed tiles there, the layout the kernel's matrix

@@ -32,6 +32,7 @@
 // per SIMD, every LDS fragment feeds two MFMAs); it measures slower and is not instantiated
 // by default.
 #include <algorithm>
+#include <numeric>
 
 #include "attend_common.h"
 
@@ -534,22 +535,25 @@ double chain_ratio(const AttendArgs& a) {
 // 96 / 98 / 108; 20 x 3278 (1.83) 77.7 / 77.0 / 84.7; 32 x 901 (3.2) 22.0 / 23.4 / 30.5, x 1742 (2.0) 43.1 / 44.8 / 49.4 (at d = 64
 // 31.1 / 32.6 / 36.9, plain x 1792 28.7 / 31.8); 40 x 1250 (2.13) 35.1 / 34.0 / 38.6; 64 x 738 (2.0) 28.1 / 24.8 / 28.0.  One rule for
 // tsa_attend on compacted tensors and the fused launch keeps tsa_forward and the separate calls the same bit for bit.
-// A block list whose rows have room for every block of the set need not bound the chains (a window as long as a short set):
-// the same ratio decides, 0.05 higher, since the split form's workgroups count twice as many lists.  Window 4096, split / four wavefronts /
-// 256 rows: fused, d = 128, 12 heads x 4096 rows (2.5), blocks of 64 77.4 / 91.9 / 114.5, of 256 70.5 / 85.6 / 100.4; with a residual
-// stream 16 x 4096 (1.88), blocks of 128, 86.7 / 96.4 / 103.7, 28 x 1000 (3.7) 25.5 / 29.2 / 35.3, x 2048 (2.03) 53.8 / 52.1 / 57.2, x 4096 (1.08)
-// 158 / 132 / 138; d = 64, 12 x 4096 56.9 / 70.3 / 81.5.
-// Under a shorter list its window bounds the chains, so that the ratio says little: the form pays only while all of its
-// workgroups, one per CU, run at once, and not with blocks of 64, where a workgroup of four wavefronts walks shorter lists.
-// d = 128, plain, window 4096: 4 heads x 8192 rows (256 workgroups), blocks of 128 76.9 / 83.2 / 108.3, of 256 75.2 / 84.9 / 107.1; 8 x 8192
-// (512), blocks of 128 141.8 / 124.7 / 116.8, of 256 139.3 / 126.5 / 117.0; fused, blocks of 128, 16 x 4096 (512) with a window of 2000
-// 82.3 / 68.2 / 70.2, 28 x 2048 (448) with one of 1024 51.9 / 41.8 / 47.0.
+// Under a block list the windows bound the chains, and how long they are only the device knows: a row of the list may be
+// mostly -1, so its room for entries says nothing.  The form is taken where it is the faster one for every window, which is
+// while all of its workgroups run at once, one per CU.  Split / four wavefronts / 256 rows, us, fused with a residual stream, rows of the
+// list with room for the whole set: 8 heads x 4096 rows, d = 128, (256 workgroups) window 256, blocks of 64 25.4 / 27.5 / 35.1,
+// of 128 24.1 / 26.8 / 34.1; whole set 78.9 / 92.3 / 118.2 and 71.3 / 87.0 / 106.7; 64 x 512, blocks of 64, window 64 and whole set: 0.90 and 0.93 of
+// four wavefronts.  With more workgroups it loses on short windows what it gains on long ones: 12 x 4096 (384), blocks of 64, 256 44.2 / 31.9 /
+// 35.9, 1024 67.3 / 49.3 / 54.6, 2048 76.9 / 67.2 / 79.1, whole set 82.1 / 95.9 / 118.9; 16 x 4096 (512), blocks of 128, 2048 88.0 / 73.4 / 74.8, whole
+// set 93.2 / 100.1 / 108.6.
+// Blocks of 64 take it only under rows with room for the whole set, and count the workgroups without a tile too: where a head's
+// tiles do not divide evenly into its parts (map_workgroups), those hold CUs back (12 x 2600, 252 workgroups in a grid of 264, blocks of
+// 64, window 128: 30.8 / 24.6 / 30.3).  Blocks of 128 and more go by the workgroups that have one: in such a grid the form is
+// faster on long windows (12 x 2600, blocks of 128, 2688 51.6 / 62.3 / 72.0) and slower on short ones (128 30.1 / 24.3 / 30.0).
 bool use_split_form(const AttendArgs& a) {
   if (g_attend_form) return g_attend_form == 2;
-  const double line = a.BH <= 32 ? std::min(1.5 + 0.0175 * a.BH, 2.0) : 1.5 + 0.0175 * a.BH;
-  if (!a.block_list) return chain_ratio(a) >= line;
-  if ((long long)a.max_blocks * a.block >= a.Lc && chain_ratio(a) >= line + 0.05) return true;
-  return a.block >= 128 && (long long)a.BH * ((a.Lc + 127) / 128) <= 256 && chain_ratio(a) >= 1.8;
+  if (!a.block_list) return chain_ratio(a) >= (a.BH <= 32 ? std::min(1.5 + 0.0175 * a.BH, 2.0) : 1.5 + 0.0175 * a.BH);
+  const bool small_blocks = a.block < 128;
+  if (small_blocks && (long long)a.max_blocks * a.block < a.Lc) return false;
+  const int nq = (a.Lc + 127) / 128, parts = small_blocks ? 8 / std::gcd(a.BH, 8) : 1;
+  return (long long)a.BH * parts * ((nq + parts - 1) / parts) <= 256 && chain_ratio(a) >= 1.8;
 }
 
 // Four wavefronts per workgroup (two or three workgroups per CU) against 256 rows, us of the fused launch:
