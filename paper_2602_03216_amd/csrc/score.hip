@@ -28,6 +28,7 @@
 // last two units of a tile).  In pass 1 that body does not compute a row max at all: the running max only
 // has to keep the exponentials in range, so the sum itself is the detector (a unit whose sum leaves the
 // range is redone the exact way, with the true max; this happens once per row in practice).
+#include "score_plan.h"
 #include "tsa_internal.h"
 
 #include <type_traits>
@@ -38,16 +39,10 @@ namespace {
 
 constexpr int kSetThreads = 256;             // threads and wavefronts of a workgroup per set of queries (below)
 constexpr int kSetWaves = 4;
-constexpr int kMinChunk = 256;               // keys per workgroup: at least this, a multiple of 128 (every tile size divides it)
 constexpr float kNegBig = -1.0e30f;
 constexpr float kSumLimit = 1073741824.0f;   // 2^30: a unit's sum of exponentials beyond this means the running max lags too far
 
 constexpr int kMaxQueries = 128;
-// Up to that many chunk partials per query are folded at the start of pass 2 instead of in a launch of their own (5 us):
-// 16 chunks cost pass 2 about 2 us (8K tokens x 32 KV heads: 4.7 + 15.8 -> 18.0 us for both), 49 to 64 chunks what the
-// launch costs (12345 tokens x 8: 23.7 -> 24.3, 128K: 80.9 -> 82.1).
-constexpr int kFoldChunks = 32;
-
 struct ScoreArgs {
   const __bf16* Q;             // scoring queries: row i of head (b, h) at Q + qs.head(b, h) + (q_row0 + i) * qs.l
   Strides qs, ks;              // layout of Q (or of the caller's query rows) and of K
@@ -60,7 +55,6 @@ struct ScoreArgs {
   float* lse2;        // [B*Hq][QP]
   int Hq, Hkv, L, Lq, nchunks, chunk;      // chunk = keys per workgroup
   int g;              // query heads per KV head
-  int most_heads;     // heads a workgroup may serve at a time
   FastDiv by_Hkv;
   int pool_w;
   float* pooled;      // final output when pool_w > 1 (scores then points at a raw buffer)
@@ -712,11 +706,6 @@ __global__ void pool_kernel(const float* __restrict__ raw, float* __restrict__ o
   out[i] = acc / (float)w;
 }
 
-constexpr int kCUs = 256;
-// workgroups that the LDS tiles and the registers allow to be resident: two per CU with up to 64 queries, else one of twice
-// the wavefronts
-inline int resident_workgroups(int QP) { return QP <= 64 ? 2 * kCUs : kCUs; }
-
 template <int D, int NQT, int NSET, int HPW>
 hipError_t run_split(const ScoreArgs& a, int BH, hipStream_t st) {
   constexpr int QP = 32 * NQT * NSET, kThreads = NSET * kSetThreads;
@@ -737,32 +726,12 @@ hipError_t run_split(const ScoreArgs& a, int BH, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The kernels are built per number of query heads a workgroup serves at a time (wave_role: 4, 2 or 1).  As many as
-// the group has, unless the chunks leave CUs idle: then a workgroup takes fewer heads, and its wavefronts split the keys of
-// every tile instead.  8 KV heads x 3001 tokens are 96 workgroups with four heads each: passes of 11.4 and 12.0 us; 192 with
-// two: 9.8 and 9.8; 384 with one: 10.2 and 11.3, so half the CUs busy is where the line lies.
+// The kernels are built per number of query heads a workgroup serves at a time (wave_role: 4, 2 or 1).
 template <int D, int NQT, int NSET>
-hipError_t run(const ScoreArgs& a, int BH, hipStream_t st) {
-  const int g = a.Hq / a.Hkv;
-  const long long wgs = (long long)a.nchunks * (BH / g);
-  int hpw = g >= 4 ? 4 : (g >= 2 ? 2 : 1);
-  while (hpw > 1 && (hpw > a.most_heads || wgs * ((g + hpw - 1) / hpw) <= kCUs / 2)) hpw /= 2;
-  if (hpw == 4) return run_split<D, NQT, NSET, 4>(a, BH, st);
-  if (hpw == 2) return run_split<D, NQT, NSET, 2>(a, BH, st);
+hipError_t run(const ScoreArgs& a, int heads, int BH, hipStream_t st) {
+  if (heads == 4) return run_split<D, NQT, NSET, 4>(a, BH, st);
+  if (heads == 2) return run_split<D, NQT, NSET, 2>(a, BH, st);
   return run_split<D, NQT, NSET, 1>(a, BH, st);
-}
-
-// Keys per workgroup: long enough that the start-up of a workgroup (Q fragments, first K tile)
-// is amortised, short enough for as many workgroups as are resident, so the launch runs as a single round (65..128
-// queries, one per CU, 2 x 6001 tokens x 8 KV heads: 1.5 rounds of 256 keys 35.0 and 31.2 us, one round of 384 keys 24.8 and 22.3).
-inline int nqt_for(int last_q) { return last_q <= 32 ? 1 : (last_q <= 64 ? 2 : 4); }
-inline int chunk_for(const Dims& dm) {
-  const long long total = (long long)dm.L * dm.B * dm.Hkv;
-  long long c = total / resident_workgroups(32 * nqt_for(dm.last_q));
-  c = (c + 127) / 128 * 128;
-  if (c < kMinChunk) c = kMinChunk;
-  if (c > 8192) c = 8192;
-  return (int)c;
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -780,26 +749,16 @@ size_t score_ws_bytes(const Dims& dm) {
 namespace {
 
 hipError_t launch_common(const Dims& dm, ScoreArgs& a, const void* K, float* scores, void* ws, hipStream_t st) {
-  const int nqt = nqt_for(dm.last_q);                    // query sub-tiles; 4: two sets of two
+  const int nqt = nqt_for(dm.last_q);
   const int QP = 32 * nqt;
   a.K = (const __bf16*)K; a.scores = scores;
   a.ks = dm.kv;
   a.Hq = dm.Hq; a.Hkv = dm.Hkv; a.L = dm.L; a.Lq = dm.last_q;
   a.g = dm.Hq / dm.Hkv;
   a.by_Hkv = FastDiv(dm.Hkv, (uint64_t)dm.B * dm.Hkv);
-  a.chunk = chunk_for(dm);
-  a.nchunks = (dm.L + a.chunk - 1) / a.chunk;
-  // Workgroups of two heads instead of four on chunks twice as long are as many; where that leaves few enough chunks for
-  // pass 2 to fold, the launch in between falls away, which is worth the second staging of every key as long as the passes
-  // are short.  Whole scoring, 64 queries, four / two heads, us: 32 heads over 8 of K x 10007 tokens 33.0 / 29.7, 12345 33.3 / 32.1, 20000 (chunks of
-  // 384 keys) 41.2 / 41.2, 32768 (512) 56.1 / 56.7, 131072 156 / 169; d = 64 x 32768 41.9 / 39.1; 28 over 4 x 12000 32.7 / 29.8; 40 over 8 x
-  // 16000 50.5 / 45.5; 16 over 2 x 12000 23.7 / 21.0.  (One head on chunks four times as long: 28 over 4 x 30000 57 / 62.)
-  a.most_heads = 4;
-  if (dm.Hq / dm.Hkv >= 4 && a.nchunks > kFoldChunks && a.nchunks <= 2 * kFoldChunks && a.chunk * dm.d <= 384 * 128) {
-    a.most_heads = 2;
-    a.chunk *= 2;
-    a.nchunks = (dm.L + a.chunk - 1) / a.chunk;
-  }
+  const ScorePlan plan = plan_score(dm.B * dm.Hkv, a.g, dm.L, dm.d, dm.last_q);
+  a.chunk = plan.chunk;
+  a.nchunks = plan.nchunks;
   a.c = dm.scale * kLog2e;
   const size_t BH = (size_t)dm.B * dm.Hq;
   a.part = (float2*)ws;
@@ -812,13 +771,13 @@ hipError_t launch_common(const Dims& dm, ScoreArgs& a, const void* K, float* sco
   }
   const int bh = (int)BH;
   if (dm.d == 128) {
-    if (nqt == 1) return run<128, 1, 1>(a, bh, st);
-    if (nqt == 2) return run<128, 2, 1>(a, bh, st);
-    return run<128, 2, 2>(a, bh, st);
+    if (nqt == 1) return run<128, 1, 1>(a, plan.heads, bh, st);
+    if (nqt == 2) return run<128, 2, 1>(a, plan.heads, bh, st);
+    return run<128, 2, 2>(a, plan.heads, bh, st);
   }
-  if (nqt == 1) return run<64, 1, 1>(a, bh, st);
-  if (nqt == 2) return run<64, 2, 1>(a, bh, st);
-  return run<64, 2, 2>(a, bh, st);
+  if (nqt == 1) return run<64, 1, 1>(a, plan.heads, bh, st);
+  if (nqt == 2) return run<64, 2, 1>(a, plan.heads, bh, st);
+  return run<64, 2, 2>(a, plan.heads, bh, st);
 }
 
 }  // namespace
