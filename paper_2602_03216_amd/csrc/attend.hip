@@ -28,9 +28,10 @@
 // waiting half tile by the same amount.
 // Very short compacted sets (up to 1792 tokens at 32 heads) take the 128-row form of attend_split.hip
 // instead (use_split_form below).
-// The template also holds the layout with 64 rows per wavefront (QS = 2: four wavefronts, one
-// per SIMD, every LDS fragment feeds two MFMAs); it measures slower and is not instantiated
-// by default.
+// The template is written for QS query sub-tiles per wavefront; QS = 1 is the one that is built.  (QS = 2, 64 rows per wavefront,
+// one per SIMD, every LDS fragment feeding two MFMAs, measured slower with the tiles still staged through registers; with
+// the loads into LDS it was not timed.  Taking the parameter out gives the fused kernels other registers and costs 1 to
+// 1.7 % of their long launches: 32 heads x 16384 rows 2033 -> 2068 us for the layer.)
 #include <algorithm>
 #include <numeric>
 
@@ -42,8 +43,7 @@ using namespace attend_detail;
 
 namespace {
 
-// QS = query sub-tiles (of 32 rows) per wavefront, NW = wavefronts per workgroup.  QS = 2, NW = 4: wavefronts of 64
-// rows, one per SIMD, every LDS fragment feeds two MFMAs.  QS = 1: wavefronts of 32 rows, which share
+// QS = query sub-tiles (of 32 rows) per wavefront, NW = wavefronts per workgroup.  QS = 1: wavefronts of 32 rows, which share
 // the SIMD's issue slots (a lone wavefront issues one vector instruction every ~8 clocks, two
 // together one every ~5) at the price of one LDS fragment per MFMA.  NW = 8: 256 rows, the two wavefronts of a SIMD
 // belong to one workgroup.  NW = 4: 128 rows; the LDS holds two such workgroups (2 x 78336 bytes of 160 KiB, with K
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   //   16..23  S^T(T1, half 0) -> sA      with  exp(sB) -> pB
   //   24..31  O^T += V^T(T0, half 1) pB  with  row max of sA         [wait for the tiles requested, barrier, rare raise of m]
   // Inside this loop sA and sB hold s * c - m by the time their exponentials are due (formed by an fma
-  // per element in the PV block after the chain, or, with scaled Q, by a chain that starts from -m), so the
+  // per element in the PV block after the chain), so the
   // exponent is the register itself and the row max is relative to m; a raise of m between the two shifts
   // the pending half tile by the same amount.
   // Each chunk consumes one 16-byte LDS fragment per lane (a K fragment or a V^T fragment);
@@ -531,8 +531,8 @@ double chain_ratio(const AttendArgs& a) {
 // every K / V tile for half as many rows and half as many keys per wavefront.  The ratio from which it does rises with
 // the number of heads: the more heads, the fewer rows at the same ratio, and the more the start and the merge of its
 // workgroups weigh.  us of the launch, fused, d = 128, split / four wavefronts / 256 rows: 4 heads x 18894 rows (ratio 1.71) 391 / 410 / 436,
-// x 20942 (1.54) 469 / 480 / 503; 8 x 9422 (1.68) 205 / 211 / 227, x 9934 (1.60) 225 / 226 / 242; 16 x 4046 (1.88) 86 / 91 / 101, x 4302 (1.78)
-// 96 / 98 / 108; 20 x 3278 (1.83) 77.7 / 77.0 / 84.7; 32 x 901 (3.2) 22.0 / 23.4 / 30.5, x 1742 (2.0) 43.1 / 44.8 / 49.4 (at d = 64
+// x 20942 (1.54) 469 / 480 / 503 (below the line, which is 1.57 for 4 heads: 2 % given away to one line for all); 8 x 9422 (1.68)
+// 205 / 211 / 227, x 9934 (1.60) 225 / 226 / 242; 16 x 4046 (1.88) 86 / 91 / 101, x 4302 (1.78) 96 / 98 / 108; 20 x 3278 (1.83) 77.7 / 77.0 / 84.7; 32 x 901 (3.2) 22.0 / 23.4 / 30.5, x 1742 (2.0) 43.1 / 44.8 / 49.4 (at d = 64
 // 31.1 / 32.6 / 36.9, plain x 1792 28.7 / 31.8); 40 x 1250 (2.13) 35.1 / 34.0 / 38.6; 64 x 738 (2.0) 28.1 / 24.8 / 28.0.  One rule for
 // tsa_attend on compacted tensors and the fused launch keeps tsa_forward and the separate calls the same bit for bit.
 // Under a block list the windows bound the chains, and how long they are only the device knows: a row of the list may be

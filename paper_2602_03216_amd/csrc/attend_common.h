@@ -406,8 +406,7 @@ __device__ __forceinline__ void softmax_max(const f32x16 (&s)[QS], float c, floa
   raise_max<ND, QS>(mxc, m, l, o);
 }
 
-// p = exp2(s*c - m), packed to bf16 pairs in accumulator order; row sums into l.  (c is 1 in the
-// kernel, whose scores come out of the MFMAs already scaled.)
+// p = exp2(s*c - m), packed to bf16 pairs in accumulator order; row sums into l.
 template <int QS>
 __device__ __forceinline__ void softmax_exp(const f32x16 (&s)[QS], float c, const float (&m)[QS], float (&l)[QS], uint32_t (&pb)[QS][8]) {
 #pragma unroll
