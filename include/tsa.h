@@ -270,8 +270,11 @@ int tsa_forward_dynamic(const tsa_desc* desc, const void* Q, const void* K, cons
  * tsa_layer_drift -- Eq. 1, Inter-Layer Representation Drift of one layer:
  *   R = mean_t ||h_out[t] - h_in[t]||_2 / (||h_in[t]||_2 + eps)
  *   h_in, h_out [n_tokens, width] bf16, device (the layer's input and output hidden states);
- *   width a multiple of 8;  drift_out: one fp32 on the device;  ws: tsa_layer_drift_workspace_bytes().
- *   fp32 sums of squares per token, fp64 mean; deterministic. */
+ *   width a multiple of 8;  drift_out: one fp32 on the device.
+ *   ws: tsa_layer_drift_workspace_bytes() bytes.  Less is accepted down to 8 bytes per 64 tokens (rounded up to
+ *   256 bytes), on which the call runs with fewer workgroups.
+ *   fp32 sums of squares per token, fp64 mean; deterministic: the same inputs and the same ws_bytes give the same
+ *   bits (ws_bytes below the full size regroups the fp64 sums, which may move the last bit; more makes no difference). */
 size_t tsa_layer_drift_workspace_bytes(int64_t n_tokens);
 int tsa_layer_drift(const void* h_in, const void* h_out, int64_t n_tokens, int32_t width, float eps,
                     float* drift_out, void* ws, size_t ws_bytes, void* stream);
