@@ -261,8 +261,9 @@ __global__ void bud_final_kernel(BudArgs a) {
 // pass in practice, three at most (2^32 -> 2^21 -> 2^10 -> 1).
 // Bound by the chain of its steps on one CU: load, range, a pass (clear, count, scan), ranking.
 constexpr int kRowBins = 2 * kThreads;
-// 16 keys per thread; beyond, one CU's share of the row (0.6 us per 1000 tokens) outweighs the launches.  Whole budget with 32 heads,
-// one launch / five: 4096 tokens 10.6 / 23.2 us, 8192 13.8 / 22.9, 12345 15.7 / 22.6, 16384 16.7 / 22.9, 20000 20.4 / 23.7, 32768 26.1 / 23.8.
+// 16 keys per thread are the most that is built; that, and not a crossing, is the line.  Whole budget with 32 heads, one launch /
+// five: 4096 tokens 10.6 / 23.2 us, 8192 13.8 / 22.9, 12345 15.7 / 22.6, 16384 16.7 / 22.9; with more keys per thread 20000 20.4 / 23.7, 32768
+// 26.1 / 23.8, so the two cross between these.
 constexpr int kRowTokens = 16 * kThreads;
 constexpr int kCountShift = 44;
 constexpr int kHot = 16;                      // keys of a wavefront in one bin from which they are added up first

@@ -1,5 +1,6 @@
-"""The budget of rows that one workgroup takes in one launch (up to 16384 tokens), and the first row length beyond: one head, so
-that the summed scores are the scores themselves and the count must be the oracle's."""
+"""The budget of rows that one workgroup takes in one launch (up to 16384 tokens), and the first row length beyond, where a chain of
+launches takes over: against the oracle, and against each other on the same row.  One head, so that the summed scores are the
+scores themselves and the count must be the oracle's."""
 import numpy as np
 import pytest
 
@@ -39,3 +40,27 @@ def test_scores_over_many_binades(tsa, L):
         if tau <= 1e-12 or asc[n - 1] / cum[-1] < 1e-12:
             continue
         assert bud._budget(tsa, s, tau)[0] == L - n == bud.orc.coverage_budget(s, tau)[0]
+
+
+@pytest.mark.parametrize("L", [2, 65, 4096, 4097, 16384])
+def test_one_launch_and_the_chain_agree(tsa, L):
+    """Tokens of score zero lie under every positive threshold: a row padded with them until the chain of launches takes it
+    keeps the same number of tokens."""
+    r = np.random.Generator(np.random.PCG64(840 + L))
+    rows = [r.integers(0, 5, size=L) / 8.0,                                # runs of equal scores, zeros among them
+            np.floor(r.random(L) ** 4 * 2.0 ** 20) / 2.0 ** 20,
+            2.0 ** -10 + r.integers(0, 90, size=L) * 2.0 ** -33,           # one bin of the chain's first digit
+            np.where(r.random(L) < 0.5, -0.0, 2.0 ** -149 * r.integers(0, 9, size=L))]     # below the smallest normal number
+    rows.append(rows[1].copy())
+    rows[-1][L // 2] = np.inf                                              # no answer in the definition, but one of them
+    for i, row in enumerate(rows):
+        s = row.astype(np.float32)
+        s[0] = max(s[0], 2.0 ** -145) if i == 3 else 1.0
+        padded = np.zeros(16385 + L % 7, dtype=np.float32)
+        padded[:L] = s
+        padded = r.permutation(padded)
+        for tau in TAUS[1:]:
+            got, want = bud._budget(tsa, s[None, None], tau), bud._budget(tsa, padded[None, None], tau)
+            assert np.array_equal(got, want), (i, tau, got, want)
+            if i < 3:
+                assert np.array_equal(got, bud.orc.coverage_budget(s[None, None], tau)), (i, tau)
