@@ -564,12 +564,18 @@ def test_forward_random_shapes(tsa, Hq, Hkv, L, d, Lq, k, group_mode, plant, poo
     (1, 4, 2, 2100, 128, 1100, 0, True),
     (3, 2, 1, 777, 64, 200, 0, True),
     (2, 4, 2, 520, 128, 1, 0, False),
+    # block lists of the other sizes; windows long enough for the pipelined iteration under a list
+    (1, 4, 2, 2100, 128, 1100, 0, (64, 512)),
+    (1, 4, 2, 2100, 128, 1100, 0, (256, 512)),
+    (2, 2, 1, 4500, 64, 2500, 1, (64, 1024)),
+    (1, 4, 2, 6000, 128, 3000, 0, (256, 1024)),
+    (1, 3, 1, 4100, 128, 2305, 0, (64, 1024)),
 ])
 def test_fused_path_equals_the_separate_calls(tsa, attend_form, B, Hq, Hkv, L, d, k, group_mode, with_blocks):
     """tsa_forward / tsa_compress_v_tiles + tsa_attend_fused against tsa_score -> tsa_select ->
     tsa_compress -> tsa_attend -> tsa_decompress on the same inputs: gather and scatter are copies
     and the arithmetic is the same, so every output must match bit for bit (the separate calls are
-    the ones checked against the oracle above)."""
+    the ones checked against the oracle above).  with_blocks: a block list, of 128 with a window of 256 or (size, window)."""
     r = _rng(900 + L)
     Lq = 64
     Q, K, V = (gu.to_dev(gu.rand_bits(r, (B, h, L, d))) for h in (Hq, Hkv, Hkv))
@@ -579,8 +585,9 @@ def test_fused_path_equals_the_separate_calls(tsa, attend_form, B, Hq, Hkv, L, d
     bl = bl_kw = None
     kw = {}
     if with_blocks:
-        bl = torch.from_numpy(orc.lambda_block_list(k, 128, 256, 1)).to(gu.DEV)
-        kw = dict(block_list=bl, block_size=128, max_blocks_per_row=bl.shape[1])
+        size, window = (128, 256) if with_blocks is True else with_blocks
+        bl = torch.from_numpy(orc.lambda_block_list(k, size, window, 1)).to(gu.DEV)
+        kw = dict(block_list=bl, block_size=size, max_blocks_per_row=bl.shape[1])
     # separate calls
     s = torch.empty((B, Hq, L), dtype=torch.float32, device=gu.DEV)
     idx = torch.empty((B, Hs, k), dtype=torch.int32, device=gu.DEV)
