@@ -532,8 +532,9 @@ double chain_ratio(const AttendArgs& a) {
 // the number of heads: the more heads, the fewer rows at the same ratio, and the more the start and the merge of its
 // workgroups weigh.  us of the launch, fused, d = 128, split / four wavefronts / 256 rows: 4 heads x 18894 rows (ratio 1.71) 391 / 410 / 436,
 // x 20942 (1.54) 469 / 480 / 503 (below the line, which is 1.57 for 4 heads: 2 % given away to one line for all); 8 x 9422 (1.68)
-// 205 / 211 / 227, x 9934 (1.60) 225 / 226 / 242; 16 x 4046 (1.88) 86 / 91 / 101, x 4302 (1.78) 96 / 98 / 108; 20 x 3278 (1.83) 77.7 / 77.0 / 84.7; 32 x 901 (3.2) 22.0 / 23.4 / 30.5, x 1742 (2.0) 43.1 / 44.8 / 49.4 (at d = 64
-// 31.1 / 32.6 / 36.9, plain x 1792 28.7 / 31.8); 40 x 1250 (2.13) 35.1 / 34.0 / 38.6; 64 x 738 (2.0) 28.1 / 24.8 / 28.0.  One rule for
+// 205 / 211 / 227, x 9934 (1.60) 225 / 226 / 242; 16 x 4046 (1.88) 86 / 91 / 101, x 4302 (1.78) 96 / 98 / 108;
+// 20 x 3278 (1.83) 77.7 / 77.0 / 84.7; 32 x 901 (3.2) 22.0 / 23.4 / 30.5, x 1742 (2.0) 43.1 / 44.8 / 49.4 (at d = 64 31.1 / 32.6 / 36.9,
+// plain x 1792 28.7 / 31.8); 40 x 1250 (2.13) 35.1 / 34.0 / 38.6; 64 x 738 (2.0) 28.1 / 24.8 / 28.0.  One rule for
 // tsa_attend on compacted tensors and the fused launch keeps tsa_forward and the separate calls the same bit for bit.
 // Under a block list the windows bound the chains, and how long they are only the device knows: a row of the list may be
 // mostly -1, so its room for entries says nothing.  The form is taken where it is the faster one for every window, which is
