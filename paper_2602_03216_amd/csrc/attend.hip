@@ -58,7 +58,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2 / QS) void atte
   constexpr int kThreads = 64 * NW;
   constexpr int RW = 32 * QS;                     // query rows per wavefront
   constexpr int BM = RW * NW;                     // query rows per workgroup
-  using Stg = Stage<D, NW>;
+  using Stg = Stage<D, NW, LISTS>;
   constexpr int KHALF = Stg::KHALF, VTILE = Stg::VTILE, CH = Stg::CH;
   constexpr int NS = D / 16;                      // MFMA k-steps of the QK product
   constexpr int ND = D / 32;                      // d sub-tiles of the output

@@ -151,15 +151,22 @@ struct LdsRows {
 // tracks: whoever reads the block waits (s_waitcnt vmcnt, then the workgroup barrier) himself.  In assembly because the
 // compiler, which cannot tell the slots of a ring apart, would wait for these loads before every fragment read; there is no
 // output register that it could reuse while the load is in flight.
-// The compiler's hazard pass does not look inside: the five wait states that a load needs behind a vector instruction that
-// wrote one of its scalar operands (a readfirstlane here, a scalar that comes back from a spill) are in the assembly, whatever
-// stands in front of it.  m0 is an operand, so that the compiler writes it and knows that it did.  (Against two wait states
-// behind an m0 set inside: nothing to 0.4 % of a layer, 0.8 % of one under a block list, 1072 -> 1081 us.)
+// The compiler's hazard pass does not look inside, and a load needs five wait states behind a vector instruction that wrote one
+// of its scalar operands (a readfirstlane here, a scalar that comes back from a spill).  PAD: they are in the assembly, whatever
+// stands in front of it: for the kernels with block lists, which spill scalars and whose tile numbers come out of a search.
+// They cost 0.3 to 0.8 % there (layer under a list 1103 -> 1106 us).  The others hold their operands in scalars that only scalar
+// instructions write, and would pay 2.5 % where one long chain is the launch (4 heads x 24071 rows, d = 64, 389 -> 399 us); that
+// their assembly is as it should be is tested (test_load_to_lds.py).  m0 is an operand, so that the compiler writes it and
+// knows that it did; one wait state in front of the load is due to that.
+template <bool PAD>
 __device__ __forceinline__ void load_to_lds(u32x4 rsrc, int voff, int soff, int lds) {
 #if defined(__HIP_DEVICE_COMPILE__)
   soff = __builtin_amdgcn_readfirstlane(soff);           // (the same in all lanes already; nothing where the compiler knows)
   lds = __builtin_amdgcn_readfirstlane(lds);
-  asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+  if constexpr (PAD)
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+  else
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 #endif
 }
 // The descriptor of head_rsrc (below) as plain words.
@@ -252,7 +259,7 @@ __device__ __forceinline__ bf16x8 p_operand(const uint32_t (&pb)[8], int hf) {
 // consecutive keys (one look-up in idx for all of them), and the fragment reads undo that together with k_row_perm.  A
 // V^T tile is one contiguous [d][64] block of the tiled tensor.  Offsets that all lanes share go into the scalar offset of
 // the load.  Slots of the rings are byte offsets into `smem`.
-template <int D, int NW>
+template <int D, int NW, bool LISTS>
 struct Stage {
   using KRows = LdsRows<2 * D>;                   // K tile: [key][d]
   using VRows = LdsRows<2 * BN>;                  // V^T tile: [d][key]
@@ -306,10 +313,10 @@ struct Stage {
   }
   // block i of this wavefront's share; row_off: byte offset of the row of K; half0, half1, tile: slots
   __device__ __forceinline__ void load_k(u32x4 K, int row_off, int half0, int half1, int i) const {
-    load_to_lds(K, row_off + col, 0, lds0 + (half ? half1 : half0) + k_lds + i * kBlock);
+    load_to_lds<LISTS>(K, row_off + col, 0, lds0 + (half ? half1 : half0) + k_lds + i * kBlock);
   }
   __device__ __forceinline__ void load_v(u32x4 Vt, int k0, int tile, int i) const {
-    load_to_lds(Vt, v_off, k0 * 2 * D + v_block + i * 1024, lds0 + tile + v_lds + i * kBlock);
+    load_to_lds<LISTS>(Vt, v_off, k0 * 2 * D + v_block + i * 1024, lds0 + tile + v_lds + i * kBlock);
   }
   __device__ __forceinline__ bf16x8 k_frag(int half_slot, int i) const { return *(const bf16x8*)(smem + half_slot + KRows::read_off(k_rd, i)); }
   // 16 keys from 16 hf on (hf 0 .. 3 over the tile's 64 keys), d sub-tile dt

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kThreadsS, 2) void attend_split_kernel(AttendArgs a
   constexpr int QS = 1;
   constexpr int kThreads = kThreadsS;
   constexpr int RW = 32;
-  using Stg = Stage<D, kThreads / 64>;
+  using Stg = Stage<D, kThreads / 64, LISTS>;
   constexpr int KHALF = Stg::KHALF, KTILE = 2 * KHALF, VTILE = Stg::VTILE, CH = Stg::CH;
   constexpr int NS = D / 16;
   constexpr int ND = D / 32;
